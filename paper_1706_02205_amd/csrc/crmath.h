@@ -1,8 +1,12 @@
 // Correctly rounded exponential and the Matern closed forms for gfx950.
 //
 // The factorization must start from bit-identical covariance entries for its
-// results to be reproducible entry by entry, so exp is evaluated to about 100
-// bits in double-double arithmetic and rounded once:
+// results to be reproducible entry by entry, so exp is correctly rounded, in two
+// phases (Ziv, ACM TOMS 17(3), 1991).  The first (exp_fast) reaches about 68 bits
+// with a 256-entry table and some 30 FP64 operations and accepts its result
+// when the error bound leaves the rounding no choice.  One argument in 2^13 goes
+// on to the second (exp_full), about 100 bits in double-double arithmetic (some
+// 300 operations), rounded once:
 //   x = k ln2 + r            Cody-Waite reduction, ln2 split into three parts
 //   r' = r / 2^8             exact
 //   expm1(r') = r' + r'^2 P(r'),  P the Taylor series to degree 10 (double-double)
@@ -13,11 +17,11 @@
 // rounding midpoint; such cases are reported through `hard` (probability about
 // 2^-40 per call).  Results below the normal range are rounded onto the
 // subnormal grid with integer arithmetic so they are correctly rounded too.
-// The extra arithmetic (~300 FP64 operations per entry) is cheap next to the
-// memory traffic of the factorization it feeds.
 #pragma once
 
 #include <hip/hip_runtime.h>
+
+#include "exp_table.h"
 
 namespace kcdev {
 
@@ -80,8 +84,50 @@ __device__ __forceinline__ dd expm1_small(dd r) {
     return dd_add(r, dd_mul(dd_mul(r, r), p));
 }
 
-// Correctly rounded exp(x).  hard |= 1 when the rounding could not be certified.
-__device__ inline double cr_exp(double x, int& hard) {
+// Whether hi is the rounding of every value within tol of hi + lo (|lo| <= ulp(hi)/2).
+__device__ __forceinline__ bool rounding_certain(double hi, double lo, double tol) {
+    const long long bits = __double_as_longlong(hi);
+    const int ex = int((bits >> 52) & 0x7ff);
+    const double ulp = __longlong_as_double((long long)(ex - 52) << 52);
+    const bool pow2 = (bits & 0xfffffffffffffLL) == 0;
+    const double half = (lo < 0.0 && pow2) ? 0.25 * ulp : 0.5 * ulp;
+    return half - __builtin_fabs(lo) > tol;
+}
+
+// First phase, -700 < x <= 0: x = n ln2/256 + r with |r| <= ln2/512 (2^-9.5),
+// n = 256 m + j, exp(x) = 2^m 2^(j/256) exp(r).  ln2/256 = D1 + D2 with 34 bits
+// in D1, so n D1 and x - n D1 are exact and r = rh + rl is good to 2^-78.
+// exp(r) - 1 = rh + (rl + rh^2 q(rh)), q the Taylor series through r^6/6!
+// (truncation 2^-78); what is neglected or rounded there (rh rl, rh^2, q, the
+// sum) is below 2^-71 together.  2^(j/256) = hi + lo from the table, and the
+// products are carried in two doubles: the result is within 2^-69 relative.
+constexpr double kLn2d256D1 = 0x1.62e42fef80000p-9;
+constexpr double kLn2d256D2 = 0x1.1cf79abc9e3b4p-44;
+constexpr double k256dLn2 = 0x1.71547652b82fep+8;
+
+__device__ __forceinline__ bool exp_fast(double x, double& out) {
+    const double kf = __builtin_rint(x * k256dLn2);
+    const double t = __builtin_fma(-kf, kLn2d256D1, x);  // exact
+    const dd p2 = two_prod(kf, kLn2d256D2);
+    dd r = two_sum(t, -p2.hi);
+    r.lo -= p2.lo;
+    double q = __builtin_fma(r.hi, 1.0 / 720.0, 1.0 / 120.0);
+    q = __builtin_fma(r.hi, q, 1.0 / 24.0);
+    q = __builtin_fma(r.hi, q, 1.0 / 6.0);
+    q = __builtin_fma(r.hi, q, 0.5);
+    const dd e = quick_two_sum(r.hi, __builtin_fma(r.hi * r.hi, q, r.lo));  // exp(r) - 1
+    const int n = int(kf);
+    const ExpPair w = kExp2Table[n & 255];
+    const dd me = two_prod(w.hi, e.hi);
+    const dd h = quick_two_sum(w.hi, me.hi);
+    const double lo = h.lo + (__builtin_fma(w.hi, e.lo, me.lo) + __builtin_fma(w.lo, e.hi, w.lo));
+    const dd v = quick_two_sum(h.hi, lo);
+    out = __builtin_ldexp(v.hi, n >> 8);  // above 2^-1011: normal
+    return rounding_certain(v.hi, v.lo, v.hi * 0x1p-67);
+}
+
+// Second phase.  hard |= 1 when the rounding could not be certified.
+__device__ inline double exp_full(double x, int& hard) {
     if (x != x) return x;
     if (x < -745.2) return 0.0;          // below half the smallest subnormal
     if (x > 709.79) return __builtin_inf();
@@ -102,14 +148,7 @@ __device__ inline double cr_exp(double x, int& hard) {
     }
     dd v = dd_add({1.0, 0.0}, e);        // exp(r), normalised: |lo| <= ulp(hi)/2
     if (k >= -1021) {  // 2^k * [0.7, 1.42] is a normal number: the scaling is exact
-        // hi is RN(v) unless |lo| is within the error bound of half an ulp
-        long long bits = __double_as_longlong(v.hi);
-        int ex = int((bits >> 52) & 0x7ff);
-        double ulp = __longlong_as_double((long long)(ex - 52) << 52);
-        bool pow2 = (bits & 0xfffffffffffffLL) == 0;
-        double half = (v.lo < 0.0 && pow2) ? 0.25 * ulp : 0.5 * ulp;
-        double tol = v.hi * 0x1p-92;
-        if (half - __builtin_fabs(v.lo) <= tol) hard = 1;
+        if (!rounding_certain(v.hi, v.lo, v.hi * 0x1p-92)) hard = 1;
         return __builtin_ldexp(v.hi, k);
     }
     // result below 2^-1021 * 1.42: round (hi + lo) * 2^(k+1074) to an integer number
@@ -125,6 +164,13 @@ __device__ inline double cr_exp(double x, int& hard) {
     else if (h.hi == -0.5 && h.lo == 0.0) nn = (__builtin_fmod(nn, 2.0) == 0.0) ? nn : nn - 1.0;
     if (__builtin_fabs(__builtin_fabs(h.hi) - 0.5) < 0x1p-40) hard = 1;
     return nn * 0x1p-1074;
+}
+
+// Correctly rounded exp(x).
+__device__ __forceinline__ double cr_exp(double x, int& hard) {
+    double v;
+    if (x > -700.0 && x <= 0.0 && exp_fast(x, v)) return v;
+    return exp_full(x, hard);
 }
 
 // Euclidean distance, coordinates summed in ascending order without fusion

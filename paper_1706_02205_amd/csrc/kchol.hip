@@ -75,13 +75,19 @@ __device__ __forceinline__ unsigned long long wave_sum(unsigned long long v) {
 }
 
 // ---------------------------------------------------------------------------
-// A1: Theta on S in CSC order, one wavefront per 64-entry column chunk.
-template <int TWONU>
+// A1: Theta on S in CSC order, one wavefront per 64-entry column chunk: for
+// kc_theta into the caller's array, and for a factorization into Lcsc, where the
+// kernels below pick an entry's starting value up before they overwrite it with
+// L.  One launch over all of S keeps the exponential's registers and some 100
+// dependent FP64 operations out of the level launches.  VT = float (MIXED): the
+// FP32 kernel value.  In a batch each instance has its own lengthscale.
+template <int TWONU, typename VT>
 __global__ __launch_bounds__(kBlock) void theta_kernel(const Unit* __restrict__ units, int64_t nunits,
                                                        const int64_t* __restrict__ colptr,
                                                        const int32_t* __restrict__ rowidx,
                                                        const double* __restrict__ xh, int d, double ell,
-                                                       double* __restrict__ theta,
+                                                       const int32_t* __restrict__ inst,
+                                                       const double* __restrict__ ells, VT* __restrict__ theta,
                                                        unsigned long long* __restrict__ counters) {
     int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     int64_t u = int64_t(blockIdx.x) * kWavesPerBlock + wave;
@@ -92,10 +98,15 @@ __global__ __launch_bounds__(kBlock) void theta_kernel(const Unit* __restrict__ 
     int64_t e = colptr[j] + first + lane;
     if (e >= colptr[j + 1]) return;
     int k = rowidx[e];
-    int hard = 0;
+    if (ells) ell = ells[inst[j]];
     double r = kcdev::dist(xh + int64_t(k) * d, xh + int64_t(j) * d, d);
-    theta[e] = kcdev::matern<TWONU>(r, ell, hard);
-    if (hard) atomicAdd(counters + kExpHard, 1ull);
+    if constexpr (sizeof(VT) == 8) {
+        int hard = 0;
+        theta[e] = kcdev::matern<TWONU>(r, ell, hard);
+        if (hard) atomicAdd(counters + kExpHard, 1ull);
+    } else {
+        theta[e] = kcdev::matern_f32<TWONU>(float(r), float(ell));
+    }
 }
 
 // The longest walk of each 64-entry work unit: over the unit's entries (k,j),
@@ -191,7 +202,7 @@ __device__ __forceinline__ int xcd_block() {
 }
 
 // ---------------------------------------------------------------------------
-// A1+A2: Theta on S fused into ICHOL(0), one DAG level per launch.
+// A2: ICHOL(0) of Theta on S (left in Lcsc by theta_kernel), one DAG level per launch.
 //
 // Left-looking form of the paper's incomplete Cholesky: entry (k,j) of column j
 // starts at Theta_kj and receives, for every parent i < j with (j,i) and (k,i)
@@ -226,11 +237,6 @@ struct IcholArgs {
     VT* Lv;
     VT* Lcsc;
     double* diag;
-    const double* xh;
-    int d;
-    double ell;
-    const int32_t* inst;
-    const double* ells;
     int policy;
     double tau;
     int cap;
@@ -463,7 +469,7 @@ __device__ __forceinline__ int build_buckets(const int32_t* sidx, int np, int j,
 // 64 consecutive entries of column j starting at `first` (first < length of the
 // column), one per lane of the wave; sval/sidx hold row j's np parents (and sb,
 // when BUCKETS, their directory with the given shift).
-template <int TWONU, bool COUNT, typename VT, bool BUCKETS>
+template <bool COUNT, typename VT, bool BUCKETS>
 __device__ __forceinline__ void factor_entries(const IcholArgs<VT>& a, int j, int first, int np, int lane,
                                                const VT* sval, const int32_t* sidx, const uint16_t* sb,
                                                int shift) {
@@ -477,10 +483,8 @@ __device__ __forceinline__ void factor_entries(const IcholArgs<VT>& a, int j, in
     VT* __restrict__ Lv = a.Lv;
     VT* __restrict__ Lcsc = a.Lcsc;
     double* __restrict__ diag = a.diag;
-    const double* __restrict__ xh = a.xh;
-    const int d = a.d, policy = a.policy;
+    const int policy = a.policy;
     const double tau = a.tau;
-    double ell = a.ell;
     unsigned long long* __restrict__ counters = a.counters;
 
     double dacc = 1.0;  // Theta_jj
@@ -492,13 +496,7 @@ __device__ __forceinline__ void factor_entries(const IcholArgs<VT>& a, int j, in
     const int64_t e = colptr[j] + first + lane;
     const bool active = e < colptr[j + 1];
     const int k = active ? rowidx[e] : j;
-    if (a.ells) ell = a.ells[a.inst[j]];  // a batch: lengthscale of j's instance
-    int hard = 0;
-    VT acc;
-    if constexpr (sizeof(VT) == 8)
-        acc = kcdev::matern<TWONU>(kcdev::dist(xh + int64_t(k) * d, xh + int64_t(j) * d, d), ell, hard);
-    else
-        acc = kcdev::matern_f32<TWONU>(float(kcdev::dist(xh + int64_t(k) * d, xh + int64_t(j) * d, d)), float(ell));
+    VT acc = active ? Lcsc[e] : VT(0);  // Theta_kj
 
     unsigned long long hits = 0;
     if (active) {
@@ -603,7 +601,6 @@ __device__ __forceinline__ void factor_entries(const IcholArgs<VT>& a, int j, in
         const unsigned long long tot = wave_sum(hits);
         if (lane == 0 && tot) atomicAdd(counters + kUpdates, tot);
     }
-    if (hard && active) atomicAdd(counters + kExpHard, 1ull);
 }
 
 // Row j's parent values alone (the masked factorization needs no indices).
@@ -622,15 +619,13 @@ __device__ __forceinline__ int stage_values(const IcholArgs<VT>& a, int j, VT* s
 // no set bit is not loaded.  Every loop is bounded by the masks' lengths and
 // every read checked against them, so inconsistent masks are counted
 // (kMatchErr), never followed outside row j or the mask buffer.
-template <int TWONU, bool COUNT, typename VT>
+template <bool COUNT, typename VT>
 __device__ __forceinline__ void factor_entries_mask(const IcholArgs<VT>& a, int j, int first, int np, int lane,
                                                     const VT* sval) {
     const int64_t* __restrict__ colptr = a.colptr;
     const uint32_t* __restrict__ csc2csr = a.csc2csr;
     VT* __restrict__ Lv = a.Lv;
-    const double* __restrict__ xh = a.xh;
-    const int d = a.d, policy = a.policy;
-    double ell = a.ell;
+    const int policy = a.policy;
     unsigned long long* __restrict__ counters = a.counters;
 
     double dacc = 1.0;  // Theta_jj
@@ -642,13 +637,7 @@ __device__ __forceinline__ void factor_entries_mask(const IcholArgs<VT>& a, int 
     const int64_t e = colptr[j] + first + lane;
     const bool active = e < colptr[j + 1];
     const int k = active ? a.rowidx[e] : j;
-    if (a.ells) ell = a.ells[a.inst[j]];
-    int hard = 0;
-    VT acc;
-    if constexpr (sizeof(VT) == 8)
-        acc = kcdev::matern<TWONU>(kcdev::dist(xh + int64_t(k) * d, xh + int64_t(j) * d, d), ell, hard);
-    else
-        acc = kcdev::matern_f32<TWONU>(float(kcdev::dist(xh + int64_t(k) * d, xh + int64_t(j) * d, d)), float(ell));
+    VT acc = active ? a.Lcsc[e] : VT(0);  // Theta_kj
 
     unsigned long long hits = 0;
     bool inconsistent = false;
@@ -745,7 +734,6 @@ __device__ __forceinline__ void factor_entries_mask(const IcholArgs<VT>& a, int 
         const unsigned long long tot = wave_sum(hits);
         if (lane == 0 && tot) atomicAdd(counters + kUpdates, tot);
     }
-    if (hard && active) atomicAdd(counters + kExpHard, 1ull);
 }
 
 // A row j with more parents than a.stage_max (at most a.cap - 2: what the LDS
@@ -758,20 +746,20 @@ __device__ __forceinline__ bool row_unstaged(const IcholArgs<VT>& a, int j) {
     return a.rowend[j] - 1 - a.rowptr[j] > a.stage_max;
 }
 
-template <int TWONU, bool COUNT, typename VT, bool MASK>
+template <bool COUNT, typename VT, bool MASK>
 __device__ __forceinline__ void factor_unstaged(const IcholArgs<VT>& a, int j, int first, int lane) {
     const int64_t t0 = a.rowptr[j];
     const int np = int(a.rowend[j] - 1 - t0);
     if (a.colptr[j] + first >= a.colptr[j + 1]) return;
-    if constexpr (MASK) factor_entries_mask<TWONU, COUNT, VT>(a, j, first, np, lane, a.Lv + t0);
-    else factor_entries<TWONU, COUNT, VT, false>(a, j, first, np, lane, a.Lv + t0, a.colidx + t0, nullptr, 0);
+    if constexpr (MASK) factor_entries_mask<COUNT, VT>(a, j, first, np, lane, a.Lv + t0);
+    else factor_entries<COUNT, VT, false>(a, j, first, np, lane, a.Lv + t0, a.colidx + t0, nullptr, 0);
 }
 
 // One DAG level per launch.  A workgroup owns a block unit: 64 * WPB consecutive
 // entries of one column, 64 per wave, with the column's row staged once in LDS.
 // MASK: the factorization with match masks (factor_entries_mask; only the
 // values of row j are staged); else the index merge (factor_entries).
-template <int TWONU, bool COUNT, typename VT, int WPB, bool MASK>
+template <bool COUNT, typename VT, int WPB, bool MASK>
 __global__ __launch_bounds__(WPB * kWave) void ichol_level(IcholArgs<VT> a, const Unit* __restrict__ bunits,
                                                            int64_t ubeg, int64_t uend) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -785,13 +773,13 @@ __global__ __launch_bounds__(WPB * kWave) void ichol_level(IcholArgs<VT> a, cons
     const int j = __builtin_amdgcn_readfirstlane(bunits[bu].col);
     const int first = __builtin_amdgcn_readfirstlane(bunits[bu].first) + wave * kWave;
     if (row_unstaged(a, j)) {
-        factor_unstaged<TWONU, COUNT, VT, MASK>(a, j, first, lane);
+        factor_unstaged<COUNT, VT, MASK>(a, j, first, lane);
         return;
     }
     if constexpr (MASK) {
         const int np = stage_values(a, j, sval);
         __syncthreads();
-        if (a.colptr[j] + first < a.colptr[j + 1]) factor_entries_mask<TWONU, COUNT, VT>(a, j, first, np, lane, sval);
+        if (a.colptr[j] + first < a.colptr[j + 1]) factor_entries_mask<COUNT, VT>(a, j, first, np, lane, sval);
     } else {
         const int np = stage_row(a, j, sval, sidx);
         __syncthreads();
@@ -801,8 +789,8 @@ __global__ __launch_bounds__(WPB * kWave) void ichol_level(IcholArgs<VT> a, cons
             __syncthreads();
         }
         if (a.colptr[j] + first < a.colptr[j + 1]) {
-            if (a.nbuck) factor_entries<TWONU, COUNT, VT, true>(a, j, first, np, lane, sval, sidx, sb, shift);
-            else factor_entries<TWONU, COUNT, VT, false>(a, j, first, np, lane, sval, sidx, sb, shift);
+            if (a.nbuck) factor_entries<COUNT, VT, true>(a, j, first, np, lane, sval, sidx, sb, shift);
+            else factor_entries<COUNT, VT, false>(a, j, first, np, lane, sval, sidx, sb, shift);
         }
     }
 }
@@ -810,7 +798,7 @@ __global__ __launch_bounds__(WPB * kWave) void ichol_level(IcholArgs<VT> a, cons
 // Levels [l0, l1) in one persistent launch: the workgroups of a grid that is
 // resident as a whole (cooperative launch) stride over each level's block units,
 // and a grid-wide barrier separates consecutive levels.
-template <int TWONU, bool COUNT, typename VT, int WPB, bool MASK>
+template <bool COUNT, typename VT, int WPB, bool MASK>
 __global__ __launch_bounds__(WPB * kWave) void ichol_persistent(IcholArgs<VT> a, const Unit* __restrict__ bunits,
                                                                 const int64_t* __restrict__ boff, int l0, int l1) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -827,14 +815,14 @@ __global__ __launch_bounds__(WPB * kWave) void ichol_persistent(IcholArgs<VT> a,
             const int j = __builtin_amdgcn_readfirstlane(bunits[bu].col);
             const int first = __builtin_amdgcn_readfirstlane(bunits[bu].first) + wave * kWave;
             if (row_unstaged(a, j)) {
-                factor_unstaged<TWONU, COUNT, VT, MASK>(a, j, first, lane);
+                factor_unstaged<COUNT, VT, MASK>(a, j, first, lane);
                 continue;  // no LDS touched: the workgroup needs no barrier before its next unit
             }
             if constexpr (MASK) {
                 const int np = stage_values(a, j, sval);
                 __syncthreads();
                 if (a.colptr[j] + first < a.colptr[j + 1])
-                    factor_entries_mask<TWONU, COUNT, VT>(a, j, first, np, lane, sval);
+                    factor_entries_mask<COUNT, VT>(a, j, first, np, lane, sval);
             } else {
                 const int np = stage_row(a, j, sval, sidx);
                 __syncthreads();
@@ -845,9 +833,9 @@ __global__ __launch_bounds__(WPB * kWave) void ichol_persistent(IcholArgs<VT> a,
                 }
                 if (a.colptr[j] + first < a.colptr[j + 1]) {
                     if (a.nbuck)
-                        factor_entries<TWONU, COUNT, VT, true>(a, j, first, np, lane, sval, sidx, sb, shift);
+                        factor_entries<COUNT, VT, true>(a, j, first, np, lane, sval, sidx, sb, shift);
                     else
-                        factor_entries<TWONU, COUNT, VT, false>(a, j, first, np, lane, sval, sidx, sb, shift);
+                        factor_entries<COUNT, VT, false>(a, j, first, np, lane, sval, sidx, sb, shift);
                 }
             }
             __syncthreads();  // the staged row is free again
@@ -884,7 +872,8 @@ constexpr int kGroupKC = 64;    // parents per LDS chunk
 typedef float mfma_f4 __attribute__((ext_vector_type(4)));
 
 template <int TWONU>
-__global__ __launch_bounds__(kWave) void ichol_group(IcholArgs<float> a, const kc::GroupDesc* __restrict__ groups,
+__global__ __launch_bounds__(kWave) void ichol_group(IcholArgs<float> a, const double* __restrict__ xh, int d,
+                                                     float ell, const kc::GroupDesc* __restrict__ groups,
                                                      const int2* __restrict__ gunits, int64_t ubeg, int64_t uend) {
     __shared__ float As[kWave][kGroupKC + 1];
     __shared__ float Bs[kGroupCols][kGroupKC + 1];
@@ -994,16 +983,23 @@ __global__ __launch_bounds__(kWave) void ichol_group(IcholArgs<float> a, const k
         for (int i = 0; i < 4; ++i) Cs[rb * 16 + 4 * (lane / 16) + i][lane % 16] = acc[rb][i];
     wave_lds_sync();
 
-    // external part: a_g = Theta_kg - C_kg
+    // External part: a_g = Theta_kg - C_kg.  A panel row's Theta is in Lcsc, which
+    // this unit alone overwrites; the diagonal rows are recomputed by every unit of
+    // the group while its first unit writes their L there, so theirs is evaluated here.
     float av[kGroupCols], Lr[kGroupCols];
-    double ell = a.ell;
+    // CSC entry of (k, g0 + g): a row of the supernode by its distance from the diagonal, a row below by its place
+    auto entry = [&](int g) {
+        const int j = g0 + g;
+        return k < G.s1 ? a.colptr[j] + (k - j) : a.colptr[j] + (G.s1 - j) + (eoff - (G.s1 - g0));
+    };
 #pragma unroll
     for (int g = 0; g < kGroupCols; ++g) {
         av[g] = 0.f;
         Lr[g] = 0.f;
-        if (k >= 0 && g < m && k != g0 + g) {
-            const float th = kcdev::matern_f32<TWONU>(
-                float(kcdev::dist(a.xh + int64_t(k) * a.d, a.xh + int64_t(g0 + g) * a.d, a.d)), float(ell));
+        if (k >= 0 && g < m && (panel || lane > g)) {
+            const float th = panel ? a.Lcsc[entry(g)]
+                                   : kcdev::matern_f32<TWONU>(
+                                         float(kcdev::dist(xh + int64_t(k) * d, xh + int64_t(g0 + g) * d, d)), ell);
             av[g] = th - Cs[lane][g];
         }
     }
@@ -1045,12 +1041,11 @@ __global__ __launch_bounds__(kWave) void ichol_group(IcholArgs<float> a, const k
 #pragma unroll
         for (int g = 0; g < kGroupCols; ++g) {
             if (g < m && (panel || lane >= g)) {
-                const int j = g0 + g;
-                const int64_t e = k < G.s1 ? a.colptr[j] + (k - j) : a.colptr[j] + (G.s1 - j) + (eoff - (G.s1 - g0));
+                const int64_t e = entry(g);
                 const float out = lane == g ? float(piv[g]) : Lr[g];
                 a.Lcsc[e] = out;
                 a.Lv[a.csc2csr[e]] = out;
-                if (lane == g) a.diag[j] = piv[g];
+                if (lane == g) a.diag[g0 + g] = piv[g];
                 bad = bad || !__builtin_isfinite(out);
             }
         }
@@ -1868,7 +1863,7 @@ size_t factor_lds(const kc_factor* f, size_t vt) { return factor_lds(f, vt, f->m
 constexpr size_t kMaxLdsBytes = 160 * 1024;
 
 template <typename VT>
-IcholArgs<VT> ichol_args(const kc_factor* f, double ell, const double* ells, int pol, double tau) {
+IcholArgs<VT> ichol_args(const kc_factor* f, int pol, double tau) {
     IcholArgs<VT> a;
     a.colptr = f->colptr;
     a.rowidx = f->rowidx;
@@ -1882,11 +1877,6 @@ IcholArgs<VT> ichol_args(const kc_factor* f, double ell, const double* ells, int
     a.Lv = static_cast<VT*>(f->L);
     a.Lcsc = static_cast<VT*>(f->Lcsc);
     a.diag = f->diag;
-    a.xh = f->xh;
-    a.d = f->d;
-    a.ell = ell;
-    a.inst = f->inst;
-    a.ells = ells;
     a.policy = pol;
     a.tau = tau;
     a.cap = f->cap;
@@ -1901,18 +1891,18 @@ IcholArgs<VT> ichol_args(const kc_factor* f, double ell, const double* ells, int
 
 // One level (block units [ub, ue)) as its own launch, or levels [l0, l1) (at
 // most maxb block units each) as one cooperative persistent launch.
-template <int TN, bool C, typename VT, int WPB, bool MASK>
+template <bool C, typename VT, int WPB, bool MASK>
 kc_status launch_one(const kc_factor* f, const IcholArgs<VT>& a, int64_t ub, int64_t ue, int l0, int l1,
                      int64_t maxb, bool persistent, hipStream_t s) {
     const size_t lds = factor_lds(f, sizeof(VT), MASK);
     const int w = wpb_slot(WPB);
     if (!persistent) {
         if (ue <= ub) return KC_OK;
-        ichol_level<TN, C, VT, WPB, MASK><<<unsigned(ue - ub), WPB * kWave, lds, s>>>(a, f->bunits[f->order][w], ub, ue);
+        ichol_level<C, VT, WPB, MASK><<<unsigned(ue - ub), WPB * kWave, lds, s>>>(a, f->bunits[f->order][w], ub, ue);
         KC_LAUNCH_CHECK();
         return KC_OK;
     }
-    const void* fn = reinterpret_cast<const void*>(&ichol_persistent<TN, C, VT, WPB, MASK>);
+    const void* fn = reinterpret_cast<const void*>(&ichol_persistent<C, VT, WPB, MASK>);
     int per_cu = 0;
     KC_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, WPB * kWave, lds));
     if (per_cu < 1) {
@@ -1930,19 +1920,19 @@ kc_status launch_one(const kc_factor* f, const IcholArgs<VT>& a, int64_t ub, int
     return KC_OK;
 }
 
-template <int TN, bool C, typename VT, bool MASK>
+template <bool C, typename VT, bool MASK>
 kc_status launch_wpb(const kc_factor* f, const IcholArgs<VT>& a, int64_t ub, int64_t ue, int l0, int l1, int64_t maxu,
                      bool persistent, hipStream_t s) {
-    if (f->wpb == 4) return launch_one<TN, C, VT, 4, MASK>(f, a, ub, ue, l0, l1, maxu, persistent, s);
-    if (f->wpb == 2) return launch_one<TN, C, VT, 2, MASK>(f, a, ub, ue, l0, l1, maxu, persistent, s);
-    return launch_one<TN, C, VT, 1, MASK>(f, a, ub, ue, l0, l1, maxu, persistent, s);
+    if (f->wpb == 4) return launch_one<C, VT, 4, MASK>(f, a, ub, ue, l0, l1, maxu, persistent, s);
+    if (f->wpb == 2) return launch_one<C, VT, 2, MASK>(f, a, ub, ue, l0, l1, maxu, persistent, s);
+    return launch_one<C, VT, 1, MASK>(f, a, ub, ue, l0, l1, maxu, persistent, s);
 }
 
-template <int TN, bool C, typename VT>
+template <bool C, typename VT>
 kc_status launch_mask(const kc_factor* f, const IcholArgs<VT>& a, int64_t ub, int64_t ue, int l0, int l1,
                       int64_t maxu, bool persistent, hipStream_t s) {
-    if (a.mmeta) return launch_wpb<TN, C, VT, true>(f, a, ub, ue, l0, l1, maxu, persistent, s);
-    return launch_wpb<TN, C, VT, false>(f, a, ub, ue, l0, l1, maxu, persistent, s);
+    if (a.mmeta) return launch_wpb<C, VT, true>(f, a, ub, ue, l0, l1, maxu, persistent, s);
+    return launch_wpb<C, VT, false>(f, a, ub, ue, l0, l1, maxu, persistent, s);
 }
 
 struct NoAfter {
@@ -1953,18 +1943,11 @@ struct NoAfter {
 // its own launch; each run of consecutive smaller levels is one persistent launch.
 // after(l0, l1) is called once the launch covering levels [l0, l1) is enqueued.
 template <typename VT, typename After = NoAfter>
-kc_status launch_levels(const kc_factor* f, int tn, bool cnt, double ell, const double* ells, int pol, double tau,
-                        hipStream_t s, After after = After()) {
-    const IcholArgs<VT> a = ichol_args<VT>(f, ell, ells, pol, tau);
+kc_status launch_levels(const kc_factor* f, bool cnt, int pol, double tau, hipStream_t s, After after = After()) {
+    const IcholArgs<VT> a = ichol_args<VT>(f, pol, tau);
     auto go = [&](int64_t ub, int64_t ue, int l0, int l1, int64_t maxu, bool persistent) {
-        if (cnt) {
-            if (tn == 1) return launch_mask<1, true, VT>(f, a, ub, ue, l0, l1, maxu, persistent, s);
-            if (tn == 3) return launch_mask<3, true, VT>(f, a, ub, ue, l0, l1, maxu, persistent, s);
-            return launch_mask<5, true, VT>(f, a, ub, ue, l0, l1, maxu, persistent, s);
-        }
-        if (tn == 1) return launch_mask<1, false, VT>(f, a, ub, ue, l0, l1, maxu, persistent, s);
-        if (tn == 3) return launch_mask<3, false, VT>(f, a, ub, ue, l0, l1, maxu, persistent, s);
-        return launch_mask<5, false, VT>(f, a, ub, ue, l0, l1, maxu, persistent, s);
+        if (cnt) return launch_mask<true, VT>(f, a, ub, ue, l0, l1, maxu, persistent, s);
+        return launch_mask<false, VT>(f, a, ub, ue, l0, l1, maxu, persistent, s);
     };
     const int nl = int(f->unit_off.size()) - 1;
     const std::vector<int64_t>& bo = f->boff[wpb_slot(f->wpb)];
@@ -1993,24 +1976,49 @@ kc_status launch_levels(const kc_factor* f, int tn, bool cnt, double ell, const 
 }
 
 // The factorization by supernodal groups: one launch per level of the group DAG.
-template <int TN>
-kc_status launch_groups_tn(const kc_factor* f, const IcholArgs<float>& a, hipStream_t s) {
+kc_status launch_groups(const kc_factor* f, int tn, double ell, int pol, double tau, hipStream_t s) {
+    const IcholArgs<float> a = ichol_args<float>(f, pol, tau);
     const size_t lds = (size_t(f->cap) + 1) * sizeof(int32_t);
     const size_t nl = f->goff.size() - 1;
     for (size_t v = 0; v < nl; ++v) {
         const int64_t ub = f->goff[v], ue = f->goff[v + 1];
         if (ue <= ub) continue;
-        ichol_group<TN><<<unsigned(ue - ub), kWave, lds, s>>>(a, f->groups, f->gunits, ub, ue);
+        auto go = [&](auto kernel) {
+            kernel<<<unsigned(ue - ub), kWave, lds, s>>>(a, f->xh, f->d, float(ell), f->groups, f->gunits, ub, ue);
+        };
+        if (tn == 1) go(ichol_group<1>);
+        else if (tn == 3) go(ichol_group<3>);
+        else go(ichol_group<5>);
         KC_LAUNCH_CHECK();
     }
     return KC_OK;
 }
 
-kc_status launch_groups(const kc_factor* f, int tn, double ell, int pol, double tau, hipStream_t s) {
-    const IcholArgs<float> a = ichol_args<float>(f, ell, nullptr, pol, tau);
-    if (tn == 1) return launch_groups_tn<1>(f, a, s);
-    if (tn == 3) return launch_groups_tn<3>(f, a, s);
-    return launch_groups_tn<5>(f, a, s);
+// Theta on S into `theta` (CSC order), from the points in xh.
+template <typename VT>
+kc_status launch_theta(const kc_factor* f, int tn, double ell, const double* ells, VT* theta, hipStream_t s) {
+    if (f->nunits <= 0) return KC_OK;
+    auto go = [&](auto kernel) {
+        kernel<<<grid_for(f->nunits, kWavesPerBlock), kBlock, 0, s>>>(f->units, f->nunits, f->colptr, f->rowidx, f->xh,
+                                                                      f->d, ell, f->inst, ells, theta, f->counters);
+    };
+    if (tn == 1) go(theta_kernel<1, VT>);
+    else if (tn == 3) go(theta_kernel<3, VT>);
+    else go(theta_kernel<5, VT>);
+    KC_LAUNCH_CHECK();
+    return KC_OK;
+}
+
+// What every factorization starts with: counters cleared, the points in maximin
+// order, Theta on S in Lcsc.
+kc_status launch_start(const kc_factor* f, const double* x_dev, int tn, double ell, const double* ells,
+                       hipStream_t s) {
+    zero_u64<<<1, 64, 0, s>>>(f->counters, kNumCounters);
+    KC_LAUNCH_CHECK();
+    gather_points<<<grid_for(f->n * f->d, kBlock), kBlock, 0, s>>>(x_dev, f->perm, f->n, f->d, f->xh);
+    KC_LAUNCH_CHECK();
+    return f->prec == KC_FP64 ? launch_theta<double>(f, tn, ell, ells, static_cast<double*>(f->Lcsc), s)
+                              : launch_theta<float>(f, tn, ell, ells, static_cast<float*>(f->Lcsc), s);
 }
 
 // Whether a factorization of f runs by supernodal groups (not for update counting).
@@ -2115,8 +2123,8 @@ kc_status solve_typed(const kc_factor* f, const double* b, double* x, int nrhs, 
 // writes them, so the two streams never touch the same data out of order.  The
 // backward sweep needs the whole factor and runs on s after both.
 template <typename VT>
-kc_status factorize_solve_typed(kc_factor* f, int tn, double ell, const double* ells, int pol, double tau,
-                                const double* b, double* x, int nrhs, double* y, double* partial, hipStream_t s) {
+kc_status factorize_solve_typed(kc_factor* f, int pol, double tau, const double* b, double* x, int nrhs, double* y,
+                                double* partial, hipStream_t s) {
     hipStream_t aux = f->aux;
     hipEvent_t ev = f->aux_ev;
     auto after = [&](int l0, int l1) -> kc_status {
@@ -2127,7 +2135,7 @@ kc_status factorize_solve_typed(kc_factor* f, int tn, double ell, const double* 
             return fwd_levels<VT, NR>(f, b, nrhs, r0, y, size_t(l0), size_t(l1), aux);
         });
     };
-    kc_status st = launch_levels<VT>(f, tn, false, ell, ells, pol, tau, s, after);
+    kc_status st = launch_levels<VT>(f, false, pol, tau, s, after);
     // whatever was enqueued on aux must finish before s goes on, also after an error
     KC_HIP(hipEventRecord(ev, aux));
     KC_HIP(hipStreamWaitEvent(s, ev, 0));
@@ -2565,14 +2573,12 @@ static kc_status factorize_impl(kc_factor* f, const double* x_dev, double nu, do
         return KC_EINVAL;
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    zero_u64<<<1, 64, 0, s>>>(f->counters, kNumCounters);
-    KC_LAUNCH_CHECK();
-    gather_points<<<grid_for(f->n * f->d, kBlock), kBlock, 0, s>>>(x_dev, f->perm, f->n, f->d, f->xh);
-    KC_LAUNCH_CHECK();
     const bool cnt = count_updates != 0;
-    const kc_status st = groups_on(f, cnt) ? launch_groups(f, tn, ell, int(pivot), tau, s)
-                         : f->prec == KC_FP64 ? launch_levels<double>(f, tn, cnt, ell, ells, int(pivot), tau, s)
-                                              : launch_levels<float>(f, tn, cnt, ell, ells, int(pivot), tau, s);
+    kc_status st = launch_start(f, x_dev, tn, ell, ells, s);
+    if (st != KC_OK) return st;
+    st = groups_on(f, cnt)      ? launch_groups(f, tn, ell, int(pivot), tau, s)
+         : f->prec == KC_FP64 ? launch_levels<double>(f, cnt, int(pivot), tau, s)
+                              : launch_levels<float>(f, cnt, int(pivot), tau, s);
     if (st != KC_OK) return st;
     f->factorized = true;
     f->counted = cnt;
@@ -2613,14 +2619,8 @@ kc_status kc_theta(kc_factor* f, const double* x_dev, kc_kernel kernel, double* 
     KC_LAUNCH_CHECK();
     gather_points<<<grid_for(f->n * f->d, kBlock), kBlock, 0, s>>>(x_dev, f->perm, f->n, f->d, f->xh);
     KC_LAUNCH_CHECK();
-    if (f->nunits > 0) {
-        const dim3 grid(grid_for(f->nunits, kWavesPerBlock));
-        const double ell = kernel.lengthscale;
-        if (tn == 1) theta_kernel<1><<<grid, kBlock, 0, s>>>(f->units, f->nunits, f->colptr, f->rowidx, f->xh, f->d, ell, theta_dev, f->counters);
-        else if (tn == 3) theta_kernel<3><<<grid, kBlock, 0, s>>>(f->units, f->nunits, f->colptr, f->rowidx, f->xh, f->d, ell, theta_dev, f->counters);
-        else theta_kernel<5><<<grid, kBlock, 0, s>>>(f->units, f->nunits, f->colptr, f->rowidx, f->xh, f->d, ell, theta_dev, f->counters);
-        KC_LAUNCH_CHECK();
-    }
+    const kc_status st = launch_theta<double>(f, tn, kernel.lengthscale, nullptr, theta_dev, s);
+    if (st != KC_OK) return st;
     f->last = s;
     return KC_OK;
 }
@@ -2766,22 +2766,18 @@ kc_status kc_factorize_solve(kc_factor* f, const double* x_dev, kc_kernel kernel
         }
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    zero_u64<<<1, 64, 0, s>>>(f->counters, kNumCounters);
-    KC_LAUNCH_CHECK();
-    gather_points<<<grid_for(f->n * f->d, kBlock), kBlock, 0, s>>>(x_dev, f->perm, f->n, f->d, f->xh);
-    KC_LAUNCH_CHECK();
     double* y = static_cast<double*>(scratch_dev);
     double* partial = reinterpret_cast<double*>(static_cast<char*>(scratch_dev) +
                                                 align256(size_t(f->n) * size_t(nrhs) * sizeof(double)));
-    const double ell = ell_dev ? 0.0 : kernel.lengthscale;
-    kc_status st;
+    kc_status st = launch_start(f, x_dev, tn, ell_dev ? 0.0 : kernel.lengthscale, ell_dev, s);
+    if (st != KC_OK) return st;
     if (groups_on(f, false)) {  // the group DAG has its own levels: factor, then both sweeps
-        st = launch_groups(f, tn, ell, int(pivot), tau, s);
+        st = launch_groups(f, tn, kernel.lengthscale, int(pivot), tau, s);
         if (st == KC_OK) st = solve_typed<float>(f, b_dev, x_out, nrhs, y, partial, s);
     } else {
         st = f->prec == KC_FP64
-                 ? factorize_solve_typed<double>(f, tn, ell, ell_dev, int(pivot), tau, b_dev, x_out, nrhs, y, partial, s)
-                 : factorize_solve_typed<float>(f, tn, ell, ell_dev, int(pivot), tau, b_dev, x_out, nrhs, y, partial, s);
+                 ? factorize_solve_typed<double>(f, int(pivot), tau, b_dev, x_out, nrhs, y, partial, s)
+                 : factorize_solve_typed<float>(f, int(pivot), tau, b_dev, x_out, nrhs, y, partial, s);
     }
     if (st != KC_OK) return st;
     f->factorized = true;
