@@ -11,6 +11,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -43,10 +44,12 @@ def build(verbose: bool = False) -> str:
         obj = os.path.join(BUILD, src + ".o")
         _run(["g++", *HOST_FLAGS, *inc, "-c", os.path.join(CSRC, src), "-o", obj], verbose)
         objs.append(obj)
-    for src in ("kchol.hip", "pcg.hip"):
-        obj = os.path.join(BUILD, src + ".o")
-        _run([HIPCC, *HIP_FLAGS, *inc, "-c", os.path.join(CSRC, src), "-o", obj], verbose)
-        objs.append(obj)
+    hips = ("kchol.hip", "team.hip", "pcg.hip")
+    cmds = [[HIPCC, *HIP_FLAGS, *inc, "-c", os.path.join(CSRC, src), "-o", os.path.join(BUILD, src + ".o")]
+            for src in hips]
+    with ThreadPoolExecutor(max_workers=len(cmds)) as pool:  # one compiler process per source
+        list(pool.map(lambda c: _run(c, verbose), cmds))
+    objs += [os.path.join(BUILD, src + ".o") for src in hips]
     tmp = LIB + ".tmp"
     _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", tmp, "-pthread"], verbose)
     os.replace(tmp, LIB)

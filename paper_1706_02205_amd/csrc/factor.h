@@ -9,6 +9,14 @@
 #include "kchol.h"
 #include "plan.h"
 
+// Device counters of a factor.
+namespace kc::counter {
+enum Counter {
+    kNonpos = 0, kShifted = 1, kUpdates = 2, kExpHard = 3, kNonfinite = 4, kMatchErr = 5, kMatchTotal = 6,
+    kNumCounters = 8
+};
+}
+
 struct kc_factor {
     int64_t n = 0, nnz = 0, nnz_rows = 0, nunits = 0;
     int32_t d = 0;
@@ -61,6 +69,7 @@ struct kc_factor {
     int32_t ninst = 1;
     // host schedule
     std::vector<int64_t> unit_off, fwd_off, short_off, top_off, tchunk_off;
+    std::vector<int32_t> level_last;  // last column of each level
     int64_t nfine = 0;        // pieces of the top columns' rows below the top block (first in bwd_chunks)
     int64_t max_slots = 0;    // partial sums the backward sweep needs at once
     // match masks (kc_factor_match_build), in a caller-owned buffer; null: index merge

@@ -32,9 +32,12 @@
 
 #include "crmath.h"
 #include "factor.h"
+#include "pivot.h"
 #include "plan.h"
+#include "team.h"
 
 using kc::Unit;
+using namespace kc::counter;
 
 namespace {
 
@@ -46,11 +49,6 @@ constexpr int64_t kChunk = 512;                // entries per partial dot produc
 constexpr int64_t kFinePiece = 2048;           // entries per piece of a top column's rows below the top block
 constexpr int64_t kBandRows = 32768;           // rows per band of those pieces (8 RHS: 2 MB of x per band)
 constexpr int kMaxRhsPerPass = 8;
-
-enum Counter {
-    kNonpos = 0, kShifted = 1, kUpdates = 2, kExpHard = 3, kNonfinite = 4, kMatchErr = 5, kMatchTotal = 6,
-    kNumCounters = 8
-};
 
 // ---------------------------------------------------------------------------
 // small kernels
@@ -445,6 +443,7 @@ __device__ __forceinline__ int stage_row(const IcholArgs<VT>& a, int j, VT* sval
         sidx[t] = a.colidx[t0 + t];
         sval[t] = a.Lv[t0 + t];
     }
+    kcdev::pad_row(sval, np, int(threadIdx.x));
     if (threadIdx.x == 0) sidx[np] = INT_MAX;  // sentinel ends every cursor walk
     return np;
 }
@@ -466,10 +465,25 @@ __device__ __forceinline__ int build_buckets(const int32_t* sidx, int np, int j,
     return shift;
 }
 
+// A_jj from row j: Theta_jj = 1 less the squares of its parents' values, in order.
+template <typename VT, bool STAGED>
+__device__ __forceinline__ double row_pivot(const VT* sval, int np) {
+    if constexpr (STAGED) {
+        return kcdev::pivot_sum(sval, np, 1.0);
+    } else {  // in device memory, not padded
+        double acc = 1.0;
+        for (int t = 0; t < np; ++t) {
+            const double v = double(sval[t]);
+            acc = __builtin_fma(-v, v, acc);
+        }
+        return acc;
+    }
+}
+
 // 64 consecutive entries of column j starting at `first` (first < length of the
 // column), one per lane of the wave; sval/sidx hold row j's np parents (and sb,
 // when BUCKETS, their directory with the given shift).
-template <bool COUNT, typename VT, bool BUCKETS>
+template <bool COUNT, typename VT, bool BUCKETS, bool STAGED>
 __device__ __forceinline__ void factor_entries(const IcholArgs<VT>& a, int j, int first, int np, int lane,
                                                const VT* sval, const int32_t* sidx, const uint16_t* sb,
                                                int shift) {
@@ -487,11 +501,7 @@ __device__ __forceinline__ void factor_entries(const IcholArgs<VT>& a, int j, in
     const double tau = a.tau;
     unsigned long long* __restrict__ counters = a.counters;
 
-    double dacc = 1.0;  // Theta_jj
-    for (int t = 0; t < np; ++t) {
-        double v = double(sval[t]);
-        dacc = __builtin_fma(-v, v, dacc);
-    }
+    const double dacc = row_pivot<VT, STAGED>(sval, np);
 
     const int64_t e = colptr[j] + first + lane;
     const bool active = e < colptr[j + 1];
@@ -609,6 +619,7 @@ __device__ __forceinline__ int stage_values(const IcholArgs<VT>& a, int j, VT* s
     const int64_t t0 = a.rowptr[j];
     const int np = int(a.rowend[j] - 1 - t0);
     for (int t = threadIdx.x; t < np; t += blockDim.x) sval[t] = a.Lv[t0 + t];
+    kcdev::pad_row(sval, np, int(threadIdx.x));
     return np;
 }
 
@@ -619,7 +630,7 @@ __device__ __forceinline__ int stage_values(const IcholArgs<VT>& a, int j, VT* s
 // no set bit is not loaded.  Every loop is bounded by the masks' lengths and
 // every read checked against them, so inconsistent masks are counted
 // (kMatchErr), never followed outside row j or the mask buffer.
-template <bool COUNT, typename VT>
+template <bool COUNT, typename VT, bool STAGED>
 __device__ __forceinline__ void factor_entries_mask(const IcholArgs<VT>& a, int j, int first, int np, int lane,
                                                     const VT* sval) {
     const int64_t* __restrict__ colptr = a.colptr;
@@ -628,11 +639,7 @@ __device__ __forceinline__ void factor_entries_mask(const IcholArgs<VT>& a, int 
     const int policy = a.policy;
     unsigned long long* __restrict__ counters = a.counters;
 
-    double dacc = 1.0;  // Theta_jj
-    for (int t = 0; t < np; ++t) {
-        double v = double(sval[t]);
-        dacc = __builtin_fma(-v, v, dacc);
-    }
+    const double dacc = row_pivot<VT, STAGED>(sval, np);
 
     const int64_t e = colptr[j] + first + lane;
     const bool active = e < colptr[j + 1];
@@ -751,8 +758,8 @@ __device__ __forceinline__ void factor_unstaged(const IcholArgs<VT>& a, int j, i
     const int64_t t0 = a.rowptr[j];
     const int np = int(a.rowend[j] - 1 - t0);
     if (a.colptr[j] + first >= a.colptr[j + 1]) return;
-    if constexpr (MASK) factor_entries_mask<COUNT, VT>(a, j, first, np, lane, a.Lv + t0);
-    else factor_entries<COUNT, VT, false>(a, j, first, np, lane, a.Lv + t0, a.colidx + t0, nullptr, 0);
+    if constexpr (MASK) factor_entries_mask<COUNT, VT, false>(a, j, first, np, lane, a.Lv + t0);
+    else factor_entries<COUNT, VT, false, false>(a, j, first, np, lane, a.Lv + t0, a.colidx + t0, nullptr, 0);
 }
 
 // One DAG level per launch.  A workgroup owns a block unit: 64 * WPB consecutive
@@ -779,7 +786,7 @@ __global__ __launch_bounds__(WPB * kWave) void ichol_level(IcholArgs<VT> a, cons
     if constexpr (MASK) {
         const int np = stage_values(a, j, sval);
         __syncthreads();
-        if (a.colptr[j] + first < a.colptr[j + 1]) factor_entries_mask<COUNT, VT>(a, j, first, np, lane, sval);
+        if (a.colptr[j] + first < a.colptr[j + 1]) factor_entries_mask<COUNT, VT, true>(a, j, first, np, lane, sval);
     } else {
         const int np = stage_row(a, j, sval, sidx);
         __syncthreads();
@@ -789,8 +796,8 @@ __global__ __launch_bounds__(WPB * kWave) void ichol_level(IcholArgs<VT> a, cons
             __syncthreads();
         }
         if (a.colptr[j] + first < a.colptr[j + 1]) {
-            if (a.nbuck) factor_entries<COUNT, VT, true>(a, j, first, np, lane, sval, sidx, sb, shift);
-            else factor_entries<COUNT, VT, false>(a, j, first, np, lane, sval, sidx, sb, shift);
+            if (a.nbuck) factor_entries<COUNT, VT, true, true>(a, j, first, np, lane, sval, sidx, sb, shift);
+            else factor_entries<COUNT, VT, false, true>(a, j, first, np, lane, sval, sidx, sb, shift);
         }
     }
 }
@@ -822,7 +829,7 @@ __global__ __launch_bounds__(WPB * kWave) void ichol_persistent(IcholArgs<VT> a,
                 const int np = stage_values(a, j, sval);
                 __syncthreads();
                 if (a.colptr[j] + first < a.colptr[j + 1])
-                    factor_entries_mask<COUNT, VT>(a, j, first, np, lane, sval);
+                    factor_entries_mask<COUNT, VT, true>(a, j, first, np, lane, sval);
             } else {
                 const int np = stage_row(a, j, sval, sidx);
                 __syncthreads();
@@ -833,9 +840,9 @@ __global__ __launch_bounds__(WPB * kWave) void ichol_persistent(IcholArgs<VT> a,
                 }
                 if (a.colptr[j] + first < a.colptr[j + 1]) {
                     if (a.nbuck)
-                        factor_entries<COUNT, VT, true>(a, j, first, np, lane, sval, sidx, sb, shift);
+                        factor_entries<COUNT, VT, true, true>(a, j, first, np, lane, sval, sidx, sb, shift);
                     else
-                        factor_entries<COUNT, VT, false>(a, j, first, np, lane, sval, sidx, sb, shift);
+                        factor_entries<COUNT, VT, false, true>(a, j, first, np, lane, sval, sidx, sb, shift);
                 }
             }
             __syncthreads();  // the staged row is free again
@@ -1935,12 +1942,27 @@ kc_status launch_mask(const kc_factor* f, const IcholArgs<VT>& a, int64_t ub, in
     return launch_wpb<C, VT, false>(f, a, ub, ue, l0, l1, maxu, persistent, s);
 }
 
+// Whether level v (`units` 64-entry units) runs by teams (team.hip): every row
+// staged; at most 12 units per CU (360,000 grid points, FP64 with match masks: 34.3
+// ms with levels of up to 3,000 units by teams, 34.6 without any, 40.1 with up to
+// 4,000; 160,000 points without masks: 17.9 ms, 21.8 with up to 1,500, 18.4 with
+// all); and the bitmap of the level's last column small enough that two workgroups
+// share a CU (columns up to about 200,000).
+constexpr int64_t kTeamUnitsPerCu = 12;
+constexpr size_t kTeamLds = 72 * 1024;
+
+template <typename VT>
+bool team_level(const kc_factor* f, int v, int64_t units) {
+    return f->max_row <= f->stage_max && units <= kTeamUnitsPerCu * std::max(1, f->num_cu) &&
+           kc::team_lds(f->max_row, f->level_last[size_t(v)], sizeof(VT)) <= kTeamLds;
+}
+
 struct NoAfter {
     kc_status operator()(int, int) const { return KC_OK; }
 };
 
 // The levels of the factorization: a level with more than f->persist_max units is
-// its own launch; each run of consecutive smaller levels is one persistent launch.
+// its own launch, by teams where that is faster; each run of consecutive smaller levels is one persistent launch.
 // after(l0, l1) is called once the launch covering levels [l0, l1) is enqueued.
 template <typename VT, typename After = NoAfter>
 kc_status launch_levels(const kc_factor* f, bool cnt, int pol, double tau, hipStream_t s, After after = After()) {
@@ -1955,7 +1977,11 @@ kc_status launch_levels(const kc_factor* f, bool cnt, int pol, double tau, hipSt
     while (v < nl) {
         const int64_t cnt_v = f->unit_off[v + 1] - f->unit_off[v];  // 64-entry units: the grouping criterion
         if (cnt_v > f->persist_max) {
-            kc_status st = go(bo[v], bo[v + 1], v, v + 1, bo[v + 1] - bo[v], false);
+            kc_status st = KC_OK;
+            if (team_level<VT>(f, v, cnt_v))
+                KC_HIP(kc::launch_team<VT>(f, cnt, pol, tau, f->boff[0][v], f->boff[0][v + 1], f->level_last[v], s));
+            else
+                st = go(bo[v], bo[v + 1], v, v + 1, bo[v + 1] - bo[v], false);
             if (st == KC_OK) st = after(v, v + 1);
             if (st != KC_OK) return st;
             ++v;
@@ -2485,6 +2511,8 @@ kc_status kc_factor_create(const kc_plan* plan, kc_prec prec, void* ws_dev, size
     f->ninst = p.ninst;
     f->unit_off = p.unit_off;
     f->fwd_off = p.fwd_off;
+    f->level_last.assign(size_t(p.nlevels), 0);
+    for (int64_t j = 0; j < p.n; ++j) f->level_last[size_t(p.level[size_t(j)])] = int32_t(j);
     f->short_off = bs.short_off;
     f->top_off = bs.top_off;
     f->tchunk_off = bs.tchunk_off;

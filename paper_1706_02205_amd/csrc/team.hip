@@ -1,0 +1,305 @@
+// ICHOL(0) levels with few units: a workgroup per 64 entries of a column (gfx950).
+//
+// ichol_level gives every entry (k,j) one lane, which walks row k alone: a level
+// lasts as long as its longest walk, a few hundred dependent steps of an LDS
+// lookup and an fma each (17 us a level at 2,000 points, 72 us at 20,011 points
+// in 3-D), while most of the chip is idle.  Here 16 lanes read 16 consecutive
+// entries of row k at once and look their column indices up in a
+// bitmap of row j's parents (a word and a value read per lane, all entries'
+// lookups in flight together; a hash table measured slower, since one probe in
+// some lane or other nearly always failed and each further probe cost the whole
+// wavefront an LDS round trip).  What is left in sequence is the fma chain.
+// Measured, a whole factorization: 2,000 points 1.71 -> 0.57 ms, 20,011 in 3-D
+// 29.9 -> 5.35 ms, 50,003 on the sphere (mixed) 8.65 -> 3.6 ms, 90,601 grid points
+// (mixed) 12.1 with match masks -> 6.8 ms without using them, 160,000 (FP64)
+// 22.5 -> 17.9 ms.  Bound now by each level's chain of dependent loads (schedule,
+// row j, row k's place, row k) and the launch.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "pivot.h"
+#include "team.h"
+
+using namespace kc::counter;
+
+namespace {
+
+constexpr int kWave = 64;
+constexpr int kUnit = 64;   // entries of a column per workgroup
+// Row entries an entry's lanes take at once.  A load instruction then serves four
+// entries, and the pairs of a workgroup fit in 17 KB (FP64): with 64 a workgroup
+// took 67 KB and few fitted on a CU (160,000 grid points, FP64: 26.6 ms against
+// 20.9 ms; 32: 25.1 ms; 8: 25.7 ms).
+constexpr int kChunk = 16;
+// Entries per walking wavefront: 8 in levels of at most kNarrow workgroups per CU,
+// where latency is all that counts (20,011 points in 3-D: 5.35 ms against 6.00 ms
+// with 16), 16 in wider ones, where half as many chain instructions are issued per
+// update (160,000 grid points: 17.9 ms against 20.3 ms; 32 entries: 19.5 ms).
+constexpr int64_t kNarrow = 2;
+
+// One update: L_ki and L_ji, (+0, +0) where row k's entry is no parent of j.
+template <typename VT>
+struct __align__(2 * sizeof(VT)) Pair {
+    VT a, b;
+};
+// Pairs of an entry's chunk, padded so that the rows of consecutive entries start
+// four banks apart and the chain's 128-bit reads do not conflict.
+template <typename VT>
+constexpr int kPairStride = sizeof(VT) == 8 ? kChunk + 1 : kChunk + 2;
+
+// Row j's parents as a bitmap over [0, j): per 32 indices the bits of the parents
+// and the position in the row of the first of them.
+struct __align__(8) MapWord {
+    uint32_t bits, rank;
+};
+__host__ __device__ constexpr int map_words(int j) { return j / 32 + 1; }
+
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+template <typename VT>
+struct TeamArgs {
+    const int64_t* colptr;
+    const int32_t* rowidx;
+    const uint32_t* csc2csr;
+    const int64_t* rowptr;
+    const int64_t* rowend;
+    const int32_t* colidx;
+    VT* Lv;
+    VT* Lcsc;
+    double* diag;
+    int policy;
+    double tau;
+    unsigned long long *nonpos, *shifted, *updates, *nonfinite;
+};
+
+// acc <- fma(-a, b, acc) over n pairs (a multiple of 8) in ascending order, the
+// next eight pairs requested from LDS before the current eight's dependent fmas.
+template <typename VT>
+__device__ __forceinline__ VT chain(const Pair<VT>* __restrict__ p, int n, VT acc) {
+    typedef VT vec4 __attribute__((ext_vector_type(16 / sizeof(VT))));
+    constexpr int kRead = sizeof(VT) == 8 ? 1 : 2;  // pairs per 128-bit read
+    constexpr int kVec = 8 / kRead;
+    const vec4* v = reinterpret_cast<const vec4*>(p);
+    vec4 cur[kVec];
+#pragma unroll
+    for (int u = 0; u < kVec; ++u) cur[u] = v[u];
+    for (int t = 0; t < n; t += 8) {
+        vec4 nxt[kVec];
+        const int at = t + 8 < n ? (t + 8) / kRead : 0;
+#pragma unroll
+        for (int u = 0; u < kVec; ++u) nxt[u] = v[at + u];
+#pragma unroll
+        for (int u = 0; u < kVec; ++u) {
+            if constexpr (sizeof(VT) == 8) {
+                acc = __builtin_fma(-cur[u][0], cur[u][1], acc);
+            } else {
+                acc = __builtin_fmaf(-cur[u][0], cur[u][1], acc);
+                acc = __builtin_fmaf(-cur[u][2], cur[u][3], acc);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kVec; ++u) cur[u] = nxt[u];
+    }
+    return acc;
+}
+
+// A workgroup owns 64 entries of column j: 64 / EPW walking wavefronts with EPW
+// entries each and one more for the pivot.  Row j goes into LDS: its parents'
+// values in order, and their indices as a bitmap.  A walking wavefront takes its
+// entries' rows in chunks: each lane looks one index up and writes the pair
+// (L_ki, L_ji) to LDS; then lanes 0 .. EPW-1 run their entries' chains over those
+// pairs.  Indices that are no parents of j leave (+0, +0):
+// fma(-0, +0, acc) adds -0, which leaves every acc as it is, so the updates and
+// their order are those of ichol_level and L is bitwise the same.  The next
+// chunk's indices and values are on their way while the chains run.
+template <bool COUNT, typename VT, int EPW>
+__global__ __launch_bounds__((kUnit / EPW + 1) * kWave) void ichol_team(TeamArgs<VT> a,
+                                                                         const kc::Unit* __restrict__ bunits,
+                                                                         int64_t ubeg, int64_t uend, int cap) {
+    constexpr int kWalkers = kUnit / EPW;
+    constexpr int kAtOnce = kWave / kChunk;  // entries whose chunks one load takes
+    constexpr int kLoads = EPW / kAtOnce;
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ double piv;
+    __shared__ int piv_zero;
+    const int64_t bu = ubeg + int64_t(blockIdx.x);
+    if (bu >= uend) return;  // the whole workgroup
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int lane = threadIdx.x % kWave;
+    const int j = __builtin_amdgcn_readfirstlane(bunits[bu].col);
+    const int first = __builtin_amdgcn_readfirstlane(bunits[bu].first);
+    const int64_t t0 = a.rowptr[j];
+    const int np = int(a.rowend[j] - 1 - t0);
+    VT* sval = reinterpret_cast<VT*>(smem);
+    Pair<VT>* pairs = reinterpret_cast<Pair<VT>*>(smem + size_t(cap) * sizeof(VT));
+    MapWord* map = reinterpret_cast<MapWord*>(smem + size_t(cap) * sizeof(VT) +
+                                              sizeof(Pair<VT>) * size_t(kUnit) * kPairStride<VT>);
+
+    // this wavefront's entries, one per lane: entry e = (k, j), row k from rp, pos entries before (k, j)
+    const int64_t e = a.colptr[j] + first + wave * EPW + lane;
+    const bool mine = wave < kWalkers && lane < EPW && e < a.colptr[j + 1];
+    int k = j, pos = 0;
+    uint32_t rp = 0, pend = 0;
+    VT acc = VT(0);
+    if (mine) {
+        k = a.rowidx[e];
+        pend = a.csc2csr[e];
+        acc = a.Lcsc[e];  // Theta_kj
+        rp = uint32_t(a.rowptr[k]);
+        pos = k == j ? 0 : int(pend - rp);  // the diagonal is the pivot's business
+    }
+
+    for (int s = threadIdx.x; s < map_words(j); s += blockDim.x) map[s] = MapWord{0u, 0u};
+    __syncthreads();
+    for (int t = threadIdx.x; t < np; t += blockDim.x) {
+        const int i = a.colidx[t0 + t];
+        sval[t] = a.Lv[t0 + t];
+        atomicOr(&map[i >> 5].bits, 1u << (i & 31));
+        if (t == 0 || (a.colidx[t0 + t - 1] >> 5) != (i >> 5)) map[i >> 5].rank = uint32_t(t);
+    }
+    kcdev::pad_row(sval, np, int(threadIdx.x));
+    __syncthreads();
+
+    unsigned long long hits = 0;
+    if (wave < kWalkers) {
+        Pair<VT>* mypairs = pairs + size_t(wave) * EPW * kPairStride<VT>;
+        int longest = pos;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) longest = max(longest, __shfl_xor(longest, off, kWave));
+        longest = __builtin_amdgcn_readfirstlane(longest);
+        // load q covers entries q * kAtOnce ..., a chunk of kChunk row entries each
+        const int within = lane % kChunk;
+        uint32_t rq[kLoads];
+        int pq[kLoads];
+#pragma unroll
+        for (int q = 0; q < kLoads; ++q) {
+            rq[q] = uint32_t(__shfl(int(rp), q * kAtOnce + lane / kChunk, kWave));
+            pq[q] = __shfl(pos, q * kAtOnce + lane / kChunk, kWave);
+        }
+        int idx[kLoads];
+        VT val[kLoads];
+        auto fetch = [&](int c) {
+#pragma unroll
+            for (int q = 0; q < kLoads; ++q) {
+                // whole chunks of the row (rows are padded to 64 entries); a finished row's first one
+                const int64_t p = int64_t(rq[q]) + (c < pq[q] ? c : 0) + within;
+                idx[q] = a.colidx[p];
+                val[q] = a.Lv[p];
+            }
+        };
+        if (longest > 0) fetch(0);
+        for (int c = 0; c < longest; c += kChunk) {
+            MapWord mw[kLoads];
+#pragma unroll
+            for (int q = 0; q < kLoads; ++q) {
+                if (c + within >= pq[q]) idx[q] = -1;  // not before (k, j)
+                mw[q] = map[max(idx[q], 0) >> 5];
+            }
+            VT lji[kLoads];
+#pragma unroll
+            for (int q = 0; q < kLoads; ++q) {
+                const uint32_t bit = 1u << (idx[q] & 31);
+                if (!(mw[q].bits & bit)) idx[q] = -1;
+                const int at = int(mw[q].rank) + __popc(mw[q].bits & (bit - 1));
+                lji[q] = sval[idx[q] >= 0 ? at : 0];
+            }
+#pragma unroll
+            for (int q = 0; q < kLoads; ++q) {
+                const bool hit = idx[q] >= 0;
+                const Pair<VT> w{hit ? val[q] : VT(0), hit ? lji[q] : VT(0)};
+                mypairs[(q * kAtOnce + lane / kChunk) * kPairStride<VT> + within] = w;
+                if (COUNT && hit && w.b != VT(0)) ++hits;
+            }
+            if (c + kChunk < longest) fetch(c + kChunk);
+            wave_lds_sync();
+            const int n = min(kChunk, (longest - c + 7) & ~7);
+            if (lane < EPW) acc = chain<VT>(mypairs + lane * kPairStride<VT>, n, acc);
+            wave_lds_sync();
+        }
+    } else {
+        double dacc = kcdev::pivot_sum(sval, np, 1.0);  // from Theta_jj = 1
+        bool zero = false, shift = false;
+        if (a.policy == KC_PIVOT_ZERO) {
+            zero = !(dacc > 0.0);
+        } else if (!(dacc > a.tau)) {
+            dacc = a.tau;
+            shift = true;
+        }
+        if (lane == 0) {
+            piv = zero ? 0.0 : __builtin_sqrt(dacc);
+            piv_zero = zero;
+            if (first == 0 && zero) atomicAdd(a.nonpos, 1ull);
+            if (first == 0 && shift) atomicAdd(a.shifted, 1ull);
+        }
+        if (COUNT && first == 0)
+            for (int t = lane; t < np; t += kWave) hits += sval[t] != VT(0);  // the pivot's own updates
+    }
+    __syncthreads();
+    const double ljj = piv;
+    bool bad = false;
+    if (mine) {
+        VT out;
+        if (piv_zero) out = VT(0);
+        else if (k == j) out = VT(ljj);
+        else if constexpr (sizeof(VT) == 8) out = acc / ljj;
+        else out = float(double(acc) / ljj);
+        a.Lv[pend] = out;
+        a.Lcsc[e] = out;
+        if constexpr (sizeof(VT) == 4)
+            if (k == j) a.diag[j] = ljj;
+        bad = !__builtin_isfinite(out);
+    }
+    const unsigned long long nf = __ballot(bad);
+    if (nf && lane == 0) atomicAdd(a.nonfinite, (unsigned long long)__popcll(nf));
+    if (COUNT) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) hits += __shfl_xor(hits, off, kWave);
+        if (lane == 0 && hits) atomicAdd(a.updates, hits);
+    }
+}
+
+int32_t team_cap(int32_t max_row) { return (max_row + 16) / 16 * 16; }
+
+template <bool COUNT, typename VT, int EPW>
+hipError_t launch_epw(const kc_factor* f, const TeamArgs<VT>& a, int64_t ub, int64_t ue, int32_t max_col,
+                      hipStream_t s) {
+    const size_t lds = kc::team_lds(f->max_row, max_col, sizeof(VT));
+    ichol_team<COUNT, VT, EPW><<<unsigned(ue - ub), (kUnit / EPW + 1) * kWave, lds, s>>>(
+        a, f->bunits[f->order][0], ub, ue, team_cap(f->max_row));
+    return hipGetLastError();
+}
+
+}  // namespace
+
+namespace kc {
+
+size_t team_lds(int32_t max_row, int32_t max_col, size_t vt) {
+    const size_t pair_row = vt == 8 ? kPairStride<double> : kPairStride<float>;
+    return size_t(team_cap(max_row)) * vt + size_t(kUnit) * pair_row * 2 * vt +
+           size_t(map_words(max_col)) * sizeof(MapWord);
+}
+
+template <typename VT>
+hipError_t launch_team(const kc_factor* f, bool count, int policy, double tau, int64_t ub, int64_t ue,
+                       int32_t max_col, hipStream_t s) {
+    if (ue <= ub) return hipSuccess;
+    const TeamArgs<VT> a{f->colptr, f->rowidx, f->csc2csr, f->rowptr, f->rowend, f->colidx,
+                         static_cast<VT*>(f->L), static_cast<VT*>(f->Lcsc), f->diag, policy, tau,
+                         f->counters + kNonpos, f->counters + kShifted, f->counters + kUpdates,
+                         f->counters + kNonfinite};
+    if (ue - ub <= kNarrow * std::max(1, f->num_cu))
+        return count ? launch_epw<true, VT, 8>(f, a, ub, ue, max_col, s) : launch_epw<false, VT, 8>(f, a, ub, ue, max_col, s);
+    return count ? launch_epw<true, VT, 16>(f, a, ub, ue, max_col, s) : launch_epw<false, VT, 16>(f, a, ub, ue, max_col, s);
+}
+
+template hipError_t launch_team<double>(const kc_factor*, bool, int, double, int64_t, int64_t, int32_t,
+                                         hipStream_t);
+template hipError_t launch_team<float>(const kc_factor*, bool, int, double, int64_t, int64_t, int32_t,
+                                         hipStream_t);
+
+}  // namespace kc
