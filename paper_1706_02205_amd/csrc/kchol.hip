@@ -31,12 +31,15 @@
 #include <vector>
 
 #include "crmath.h"
+#include "chain.h"
 #include "factor.h"
-#include "pivot.h"
 #include "plan.h"
+#include "sweep.h"
+#include "sweep_dev.h"
 #include "team.h"
 
 using kc::Unit;
+using namespace kcdev;
 using namespace kc::counter;
 
 namespace {
@@ -184,19 +187,6 @@ __device__ __forceinline__ void load_vals(const float* __restrict__ Lv, int64_t 
         val[4 * q + 2] = v.z;
         val[4 * q + 3] = v.w;
     }
-}
-
-// Workgroups are dealt to the 8 XCDs round-robin (block b runs on XCD b % 8).
-// Renumber them so that each XCD receives one contiguous range of blocks: the
-// rows and columns of a solve level are laid out in spatial order, so each
-// XCD's L2 then serves one region of the point cloud.  (The factorization's
-// units are ordered by length instead, and keep the plain block order.)
-constexpr int kNumXcd = 8;
-__device__ __forceinline__ int xcd_block() {
-    const int b = blockIdx.x, nb = gridDim.x;
-    const int q = nb / kNumXcd, r = nb % kNumXcd;
-    const int x = b % kNumXcd, i = b / kNumXcd;
-    return x * q + (x < r ? x : r) + i;
 }
 
 // ---------------------------------------------------------------------------
@@ -1066,7 +1056,9 @@ __global__ __launch_bounds__(kWave) void ichol_group(IcholArgs<float> a, const d
 // (reverse levels).  A wavefront owns one row (one column): its lanes stage 64
 // entries at a time in LDS -- the L values and the gathered right-hand-side
 // rows -- and lanes r < NR then apply them to right-hand side r in ascending
-// index order, one fma each, exactly the sequential substitution.
+// index order, one fma each, exactly the sequential substitution.  (Here, the
+// backward levels of many columns; small levels and the forward sweep are in
+// sweep.hip.)
 //
 // Long columns are the coarse ones, and each reverse level near the end holds
 // only a few of them: one launch per such level would stream their long row
@@ -1081,12 +1073,6 @@ __global__ __launch_bounds__(kWave) void ichol_group(IcholArgs<float> a, const d
 // levels: a wavefront per column adds up the column's piece sums and its rows
 // below T in a fixed order.  Deterministic, but summed in a different order
 // than the sequential substitution.
-
-template <typename VT>
-__device__ __forceinline__ double diag_value(const VT* Lv, const double* diag, int64_t pos, int k) {
-    if constexpr (sizeof(VT) == 8) return Lv[pos];
-    else return diag[k];
-}
 
 // Staging of one 64-entry chunk in LDS: sL holds the chunk's L values, sY the
 // gathered right-hand-side rows, transposed -- right-hand side r's 64 values
@@ -1171,32 +1157,6 @@ __device__ __forceinline__ double substitute(const int32_t* __restrict__ idx, co
 }
 
 template <typename VT, int NR>
-__global__ __launch_bounds__(kBlock) void fwd_solve(const int32_t* __restrict__ rows, int64_t beg, int64_t end,
-                                                    const int64_t* __restrict__ rowptr,
-                                                    const int64_t* __restrict__ rowend,
-                                                    const int32_t* __restrict__ colidx, const VT* __restrict__ Lv,
-                                                    const double* __restrict__ diag,
-                                                    const int32_t* __restrict__ perm, const double* __restrict__ b,
-                                                    int ld, int r0, double* __restrict__ y) {
-    __shared__ __align__(16) double sL[kWavesPerBlock][kWave];
-    __shared__ __align__(16) double sY[kWavesPerBlock][NR * kYStride];
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int lane = threadIdx.x % kWave;
-    const int64_t t = beg + int64_t(xcd_block()) * kWavesPerBlock + wave;
-    if (t >= end) return;
-    const int k = __builtin_amdgcn_readfirstlane(rows[t]);
-    const int64_t p0 = rowptr[k], pd = rowend[k] - 1;  // pd: the diagonal
-    double acc = 0.0;
-    if (lane < NR) acc = b[int64_t(perm[k]) * ld + r0 + lane];
-    // parents' values are final: earlier levels
-    acc = substitute<VT, NR>(colidx, Lv, p0, pd, y, ld, r0, lane, sL[wave], sY[wave], acc);
-    if (lane < NR) {
-        const double lkk = diag_value(Lv, diag, pd, k);
-        y[int64_t(k) * ld + r0 + lane] = (lkk == 0.0) ? 0.0 : acc / lkk;
-    }
-}
-
-template <typename VT, int NR>
 __global__ __launch_bounds__(kBlock) void bwd_solve(const int32_t* __restrict__ cols, int64_t beg, int64_t end,
                                                     const int64_t* __restrict__ colptr,
                                                     const int32_t* __restrict__ rowidx, const VT* __restrict__ Lcsc,
@@ -1220,50 +1180,6 @@ __global__ __launch_bounds__(kBlock) void bwd_solve(const int32_t* __restrict__ 
         const double v = (ljj == 0.0) ? 0.0 : acc / ljj;
         y[int64_t(j) * ld + r0 + lane] = v;
         x[int64_t(perm[j]) * ld + r0 + lane] = v;
-    }
-}
-
-// s[r] += sum of L_e * y[row_e][r] over this lane's entries e = e, e + STRIDE,
-// ... below e1, in ascending order: four entries in flight at once, and the row
-// indices of the next four requested before this four's values and gathers,
-// so each step waits for one round trip instead of two.
-template <typename VT, int NR, int STRIDE = kWave>
-__device__ __forceinline__ void dot_entries(const int32_t* __restrict__ rowidx, const VT* __restrict__ Lcsc, int64_t e,
-                                            int64_t e1, const double* __restrict__ y, int ld, int r0,
-                                            double (&s)[NR]) {
-    constexpr int kDepth = 4;
-    int ci[kDepth];
-#pragma unroll
-    for (int u = 0; u < kDepth; ++u) {
-        const int64_t eu = e + int64_t(u) * STRIDE;
-        ci[u] = eu < e1 ? rowidx[eu] : -1;
-    }
-    for (; e < e1; e += kDepth * STRIDE) {
-        int cn[kDepth];
-#pragma unroll
-        for (int u = 0; u < kDepth; ++u) {
-            const int64_t en = e + int64_t(kDepth + u) * STRIDE;
-            cn[u] = en < e1 ? rowidx[en] : -1;
-        }
-        double l[kDepth], v[kDepth][NR];
-#pragma unroll
-        for (int u = 0; u < kDepth; ++u) {
-            l[u] = 0.0;
-            if (ci[u] >= 0) {
-                l[u] = double(Lcsc[e + int64_t(u) * STRIDE]);
-                const double* xk = y + int64_t(ci[u]) * ld + r0;
-#pragma unroll
-                for (int r = 0; r < NR; ++r) v[u][r] = xk[r];
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < kDepth; ++u)
-            if (ci[u] >= 0) {
-#pragma unroll
-                for (int r = 0; r < NR; ++r) s[r] = __builtin_fma(l[u], v[u][r], s[r]);
-            }
-#pragma unroll
-        for (int u = 0; u < kDepth; ++u) ci[u] = cn[u];
     }
 }
 
@@ -1295,54 +1211,6 @@ __global__ __launch_bounds__(kBlock) void bwd_partial(const kc::BwdChunk* __rest
         for (int r = 1; r < NR; ++r)
             if (lane == r) v = s[r];
         partial[int64_t(ch.slot) * NR + lane] = v;
-    }
-}
-
-// Forward levels of at least kWideRows rows: there a wavefront's 64 lanes share
-// a row's dot product (every 64th entry, four in flight) and a fixed butterfly
-// adds them, instead of 8 lanes applying staged chunks in the sequential
-// order -- more throughput on large levels and a shorter chain per row on
-// medium ones.  Deterministic, but not the sequential substitution's
-// summation order; smaller levels keep that order.
-constexpr int64_t kWideRows = 1024;
-
-template <typename VT, int NR>
-__device__ __forceinline__ double wave_dot(const int32_t* __restrict__ idx, const VT* __restrict__ val, int64_t b0,
-                                           int64_t b1, const double* __restrict__ src, int ld, int r0, int lane) {
-    double s[NR];
-#pragma unroll
-    for (int r = 0; r < NR; ++r) s[r] = 0.0;
-    dot_entries<VT, NR>(idx, val, b0 + lane, b1, src, ld, r0, s);
-#pragma unroll
-    for (int r = 0; r < NR; ++r)
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) s[r] += __shfl_xor(s[r], off, kWave);
-    double v = s[0];
-#pragma unroll
-    for (int r = 1; r < NR; ++r)
-        if (lane == r) v = s[r];
-    return v;  // lane r < NR holds right-hand side r's sum
-}
-
-template <typename VT, int NR>
-__global__ __launch_bounds__(kBlock) void fwd_wide(const int32_t* __restrict__ rows, int64_t beg, int64_t end,
-                                                   const int64_t* __restrict__ rowptr,
-                                                   const int64_t* __restrict__ rowend,
-                                                   const int32_t* __restrict__ colidx, const VT* __restrict__ Lv,
-                                                   const double* __restrict__ diag, const int32_t* __restrict__ perm,
-                                                   const double* __restrict__ b, int ld, int r0,
-                                                   double* __restrict__ y) {
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int lane = threadIdx.x % kWave;
-    const int64_t t = beg + int64_t(xcd_block()) * kWavesPerBlock + wave;
-    if (t >= end) return;
-    const int k = __builtin_amdgcn_readfirstlane(rows[t]);
-    const int64_t p0 = rowptr[k], pd = rowend[k] - 1;  // pd: the diagonal
-    const double v = wave_dot<VT, NR>(colidx, Lv, p0, pd, y, ld, r0, lane);
-    if (lane < NR) {
-        const double lkk = diag_value(Lv, diag, pd, k);
-        const double acc = b[int64_t(perm[k]) * ld + r0 + lane] - v;
-        y[int64_t(k) * ld + r0 + lane] = (lkk == 0.0) ? 0.0 : acc / lkk;
     }
 }
 
@@ -2056,20 +1924,18 @@ bool groups_on(const kc_factor* f, bool count) {
 template <typename VT, int NR>
 kc_status fwd_levels(const kc_factor* f, const double* b, int ld, int r0, double* y, size_t l0, size_t l1,
                      hipStream_t s) {
-    const VT* Lv = static_cast<const VT*>(f->L);
     for (size_t v = l0; v < l1; ++v) {
         const int64_t rb = f->fwd_off[v], re = f->fwd_off[v + 1];
         if (re <= rb) continue;
-        if (re - rb >= kWideRows)
-            fwd_wide<VT, NR><<<grid_for(re - rb, kWavesPerBlock), kBlock, 0, s>>>(
-                f->fwd_rows, rb, re, f->rowptr, f->rowend, f->colidx, Lv, f->diag, f->perm, b, ld, r0, y);
-        else
-            fwd_solve<VT, NR><<<grid_for(re - rb, kWavesPerBlock), kBlock, 0, s>>>(
-                f->fwd_rows, rb, re, f->rowptr, f->rowend, f->colidx, Lv, f->diag, f->perm, b, ld, r0, y);
-        KC_LAUNCH_CHECK();
+        KC_HIP(kc::launch_fwd<VT>(f, b, ld, r0, NR, y, rb, re, s));
     }
     return KC_OK;
 }
+
+// Backward levels of at most this many columns take a workgroup per column
+// (sweep.hip): 360,000 grid points, 8 right-hand sides 9.19 ms with none, 8.34 ms up
+// to 256, 8.12 ms up to 1024; 4096 was no better than 1024 there and at 160,000.
+constexpr int64_t kNarrowCols = 1024;
 
 // Backward sweep: x = P^T L^-T y for right-hand sides r0 .. r0+NR-1.
 template <typename VT, int NR>
@@ -2078,7 +1944,9 @@ kc_status bwd_levels(const kc_factor* f, double* x, int ld, int r0, double* y, d
     const size_t nr = f->short_off.size() - 1;
     for (size_t v = 0; v < nr; ++v) {
         const int64_t sb = f->short_off[v], se = f->short_off[v + 1];
-        if (se > sb) {
+        if (se > sb && se - sb <= kNarrowCols) {
+            KC_HIP(kc::launch_bwd_narrow<VT>(f, x, ld, r0, NR, y, sb, se, s));
+        } else if (se > sb) {
             bwd_solve<VT, NR><<<grid_for(se - sb, kWavesPerBlock), kBlock, 0, s>>>(
                 f->bwd_short, sb, se, f->colptr, f->rowidx, Lc, f->diag, f->perm, ld, r0, y, x);
             KC_LAUNCH_CHECK();

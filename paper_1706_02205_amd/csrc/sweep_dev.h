@@ -1,0 +1,205 @@
+// Device code of the triangular sweeps, shared by the kernels that run rows of
+// them (gfx950).
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include "chain.h"
+#include "factor.h"
+
+namespace kcdev {
+
+// Workgroups are dealt to the 8 XCDs round-robin (block b runs on XCD b % 8).
+// Renumber them so that each XCD receives one contiguous range of blocks: the
+// rows and columns of a solve level are laid out in spatial order, so each
+// XCD's L2 then serves one region of the point cloud.  (The factorization's
+// units are ordered by length instead, and keep the plain block order.)
+constexpr int kNumXcd = 8;
+__device__ __forceinline__ int xcd_block() {
+    const int b = blockIdx.x, nb = gridDim.x;
+    const int q = nb / kNumXcd, r = nb % kNumXcd;
+    const int x = b % kNumXcd, i = b / kNumXcd;
+    return x * q + (x < r ? x : r) + i;
+}
+
+template <typename VT>
+__device__ __forceinline__ double diag_value(const VT* Lv, const double* diag, int64_t pos, int k) {
+    if constexpr (sizeof(VT) == 8) return Lv[pos];
+    else return diag[k];
+}
+
+// s[r] += sum of L_e * y[row_e][r] over this lane's entries e = e, e + STRIDE,
+// ... below e1, in ascending order: four entries in flight at once, and the row
+// indices of the next four requested before this four's values and gathers,
+// so each step waits for one round trip instead of two.
+template <typename VT, int NR, int STRIDE = 64>
+__device__ __forceinline__ void dot_entries(const int32_t* __restrict__ rowidx, const VT* __restrict__ Lcsc, int64_t e,
+                                            int64_t e1, const double* __restrict__ y, int ld, int r0,
+                                            double (&s)[NR], int nr = NR) {
+    constexpr int kDepth = 4;
+    int ci[kDepth];
+#pragma unroll
+    for (int u = 0; u < kDepth; ++u) {
+        const int64_t eu = e + int64_t(u) * STRIDE;
+        ci[u] = eu < e1 ? rowidx[eu] : -1;
+    }
+    for (; e < e1; e += kDepth * STRIDE) {
+        int cn[kDepth];
+#pragma unroll
+        for (int u = 0; u < kDepth; ++u) {
+            const int64_t en = e + int64_t(kDepth + u) * STRIDE;
+            cn[u] = en < e1 ? rowidx[en] : -1;
+        }
+        double l[kDepth], v[kDepth][NR];
+#pragma unroll
+        for (int u = 0; u < kDepth; ++u) {
+            l[u] = 0.0;
+            if (ci[u] >= 0) {
+                l[u] = double(Lcsc[e + int64_t(u) * STRIDE]);
+                const double* xk = y + int64_t(ci[u]) * ld + r0;
+#pragma unroll
+                for (int r = 0; r < NR; ++r) v[u][r] = r < nr ? xk[r] : 0.0;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kDepth; ++u)
+            if (ci[u] >= 0) {
+#pragma unroll
+                for (int r = 0; r < NR; ++r) s[r] = __builtin_fma(l[u], v[u][r], s[r]);
+            }
+#pragma unroll
+        for (int u = 0; u < kDepth; ++u) ci[u] = cn[u];
+    }
+}
+
+// Forward levels of at least kWideRows rows: there a wavefront's 64 lanes share
+// a row's dot product (every 64th entry, four in flight) and a fixed butterfly
+// adds them, instead of 8 lanes applying staged chunks in the sequential
+// order -- more throughput on large levels and a shorter chain per row on
+// medium ones.  Deterministic, but not the sequential substitution's
+// summation order; smaller levels keep that order.
+constexpr int64_t kWideRows = 1024;
+
+template <typename VT, int NR>
+__device__ __forceinline__ double wave_dot(const int32_t* __restrict__ idx, const VT* __restrict__ val, int64_t b0,
+                                           int64_t b1, const double* __restrict__ src, int ld, int r0, int nr, int lane) {
+    double s[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) s[r] = 0.0;
+    dot_entries<VT, NR>(idx, val, b0 + lane, b1, src, ld, r0, s, nr);
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) s[r] += __shfl_xor(s[r], off, 64);
+    double v = s[0];
+#pragma unroll
+    for (int r = 1; r < NR; ++r)
+        if (lane == r) v = s[r];
+    return v;  // lane r < NR holds right-hand side r's sum
+}
+
+// What the two sweeps differ in: the row's entries [p0, p1) of idx and val, its
+// diagonal entry, where the right-hand side comes from and where x goes.
+template <typename VT>
+struct SweepArgs {
+    const int32_t* rows;
+    const int64_t *ptr, *end;  // forward: rowptr, rowend; backward: colptr
+    const int32_t* idx;
+    const VT* val;
+    const double* diag;
+    const int32_t* perm;
+    const double* b;  // forward: right-hand side, original order
+    double* x;        // backward: solution, original order
+    double* y;
+    int ld, r0;
+};
+
+template <typename VT>
+SweepArgs<VT> fwd_args(const kc_factor* f, const double* b, int ld, int r0, double* y) {
+    return {f->fwd_rows, f->rowptr, f->rowend, f->colidx, static_cast<const VT*>(f->L), f->diag, f->perm, b, nullptr,
+            y, ld, r0};
+}
+
+// One row of a wide forward level by a wavefront.
+template <typename VT, int NR>
+__device__ __forceinline__ void wide_row(const SweepArgs<VT>& a, int k, int nr, int lane) {
+    const int64_t p0 = a.ptr[k], pd = a.end[k] - 1;  // pd: the diagonal
+    const double v = wave_dot<VT, NR>(a.idx, a.val, p0, pd, a.y, a.ld, a.r0, nr, lane);
+    if (lane < nr) {
+        const double lkk = diag_value(a.val, a.diag, pd, k);
+        const double acc = a.b[int64_t(a.perm[k]) * a.ld + a.r0 + lane] - v;
+        a.y[int64_t(k) * a.ld + a.r0 + lane] = (lkk == 0.0) ? 0.0 : acc / lkk;
+    }
+}
+
+// One row by a workgroup of THREADS (a multiple of 16), right-hand sides r0 ..
+// r0 + nr - 1 (nr <= NR).  Entries past the row's end are staged as L = y = +0:
+// fma(-0, +0, acc) changes no acc, so the result is the sequential substitution's
+// bit for bit.
+template <typename VT, int NR, int THREADS, bool FWD>
+__device__ __forceinline__ void sweep_row(const SweepArgs<VT>& a, int k, int nr, double* __restrict__ lds) {
+    constexpr int kStride = THREADS + 2;  // rows of consecutive right-hand sides 4 banks apart
+    const int tid = threadIdx.x;
+    auto sL = [&](int buf) { return lds + buf * THREADS; };
+    auto sY = [&](int buf) { return lds + 2 * THREADS + buf * NR * kStride; };
+    const int64_t q0 = a.ptr[k];
+    const int64_t p0 = FWD ? q0 : q0 + 1;
+    const int64_t p1 = FWD ? a.end[k] - 1 : a.ptr[k + 1];
+    const int64_t pd = FWD ? p1 : q0;  // the diagonal
+    const int n = int(p1 - p0);
+    int ci, cn;
+    double lv, ln, v[NR];
+    auto entries = [&](int at, int& c, double& l) {
+        const int q = at + tid;
+        c = q < n ? a.idx[p0 + q] : -1;
+        l = q < n ? double(a.val[p0 + q]) : 0.0;
+    };
+    auto gather = [&]() {
+        const double* src = a.y + int64_t(ci < 0 ? 0 : ci) * a.ld + a.r0;
+#pragma unroll
+        for (int r = 0; r < NR; ++r) v[r] = ci < 0 || r >= nr ? 0.0 : src[r];
+    };
+    auto stage = [&](int buf) {
+        sL(buf)[tid] = lv;
+#pragma unroll
+        for (int r = 0; r < NR; ++r) sY(buf)[r * kStride + tid] = v[r];
+    };
+    entries(0, ci, lv);
+    entries(THREADS, cn, ln);
+    double acc = 0.0, lkk = 1.0;
+    if (tid < nr) {
+        acc = FWD ? a.b[int64_t(a.perm[k]) * a.ld + a.r0 + tid] : a.y[int64_t(k) * a.ld + a.r0 + tid];
+        lkk = diag_value(a.val, a.diag, pd, k);
+    }
+    if (n > 0) {
+        gather();
+        stage(0);
+        __syncthreads();
+        for (int at = 0; at < n; at += THREADS) {
+            const int buf = (at / THREADS) & 1;
+            const bool more = at + THREADS < n;
+            if (more) {  // the next block's rows and the indices after it, in flight while the chain runs
+                ci = cn;
+                lv = ln;
+                gather();
+                entries(at + 2 * THREADS, cn, ln);
+            }
+            const int m = n - at < THREADS ? chain_padded(n - at) : THREADS;
+            if (tid < nr) acc = chain_dot(sL(buf), sY(buf) + tid * kStride, m, acc);
+            if (more) {
+                stage(buf ^ 1);
+                __syncthreads();
+            }
+        }
+    }
+    if (tid < nr) {
+        const double x = lkk == 0.0 ? 0.0 : acc / lkk;
+        a.y[int64_t(k) * a.ld + a.r0 + tid] = x;
+        if constexpr (!FWD) a.x[int64_t(a.perm[k]) * a.ld + a.r0 + tid] = x;
+    }
+}
+
+// Doubles of LDS that sweep_row takes.
+constexpr size_t sweep_lds(int nr, int threads) { return 2 * size_t(threads) + 2 * size_t(nr) * size_t(threads + 2); }
+
+}  // namespace kcdev

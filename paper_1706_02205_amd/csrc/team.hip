@@ -18,7 +18,7 @@
 
 #include <algorithm>
 
-#include "pivot.h"
+#include "chain.h"
 #include "team.h"
 
 using namespace kc::counter;
