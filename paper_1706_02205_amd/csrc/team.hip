@@ -9,14 +9,15 @@
 // lookups in flight together; a hash table measured slower, since one probe in
 // some lane or other nearly always failed and each further probe cost the whole
 // wavefront an LDS round trip).  What is left in sequence is the fma chain.
-// Measured, a whole factorization: 2,000 points 1.71 -> 0.57 ms, 20,011 in 3-D
-// 29.9 -> 5.35 ms, 50,003 on the sphere (mixed) 8.65 -> 3.6 ms, 90,601 grid points
+// Measured, a whole factorization: 2,000 points 1.71 -> 0.52 ms, 20,011 in 3-D
+// 29.9 -> 5.2 ms, 50,003 on the sphere (mixed) 8.65 -> 3.6 ms, 90,601 grid points
 // (mixed) 12.1 with match masks -> 6.8 ms without using them, 160,000 (FP64)
-// 22.5 -> 17.9 ms.  Bound now by each level's chain of dependent loads (schedule,
-// row j, row k's place, row k) and the launch.
+// 22.5 -> 16.7 ms.  Bound now by each level's chain of dependent loads (schedule,
+// row j, row k's place, row k: 4 us with the launch) and 0.03 us per row entry.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "chain.h"
 #include "team.h"
@@ -26,17 +27,12 @@ using namespace kc::counter;
 namespace {
 
 constexpr int kWave = 64;
-constexpr int kUnit = 64;   // entries of a column per workgroup
+constexpr int kUnit = 64;   // entries of a column per unit of the schedule
 // Row entries an entry's lanes take at once.  A load instruction then serves four
-// entries, and the pairs of a workgroup fit in 17 KB (FP64): with 64 a workgroup
+// entries, and the pairs of 64 entries fit in 17 KB (FP64): with 64 a workgroup
 // took 67 KB and few fitted on a CU (160,000 grid points, FP64: 26.6 ms against
 // 20.9 ms; 32: 25.1 ms; 8: 25.7 ms).
 constexpr int kChunk = 16;
-// Entries per walking wavefront: 8 in levels of at most kNarrow workgroups per CU,
-// where latency is all that counts (20,011 points in 3-D: 5.35 ms against 6.00 ms
-// with 16), 16 in wider ones, where half as many chain instructions are issued per
-// update (160,000 grid points: 17.9 ms against 20.3 ms; 32 entries: 19.5 ms).
-constexpr int64_t kNarrow = 2;
 
 // One update: L_ki and L_ji, (+0, +0) where row k's entry is no parent of j.
 template <typename VT>
@@ -77,39 +73,34 @@ struct TeamArgs {
     unsigned long long *nonpos, *shifted, *updates, *nonfinite;
 };
 
-// acc <- fma(-a, b, acc) over n pairs (a multiple of 8) in ascending order, the
-// next eight pairs requested from LDS before the current eight's dependent fmas.
+// acc <- fma(-a, b, acc) over n pairs (a multiple of 8) in ascending order, eight
+// pairs read from LDS at once.  (All 16 pairs of a chunk at once took 64 registers
+// in FP64 and with them a workgroup per CU: 160,000 grid points 17.9 -> 22.1 ms.)
 template <typename VT>
 __device__ __forceinline__ VT chain(const Pair<VT>* __restrict__ p, int n, VT acc) {
-    typedef VT vec4 __attribute__((ext_vector_type(16 / sizeof(VT))));
+    typedef VT vec __attribute__((ext_vector_type(16 / sizeof(VT))));
     constexpr int kRead = sizeof(VT) == 8 ? 1 : 2;  // pairs per 128-bit read
     constexpr int kVec = 8 / kRead;
-    const vec4* v = reinterpret_cast<const vec4*>(p);
-    vec4 cur[kVec];
-#pragma unroll
-    for (int u = 0; u < kVec; ++u) cur[u] = v[u];
+    const vec* s = reinterpret_cast<const vec*>(p);
     for (int t = 0; t < n; t += 8) {
-        vec4 nxt[kVec];
-        const int at = t + 8 < n ? (t + 8) / kRead : 0;
+        vec v[kVec];
 #pragma unroll
-        for (int u = 0; u < kVec; ++u) nxt[u] = v[at + u];
+        for (int u = 0; u < kVec; ++u) v[u] = s[t / kRead + u];
 #pragma unroll
         for (int u = 0; u < kVec; ++u) {
             if constexpr (sizeof(VT) == 8) {
-                acc = __builtin_fma(-cur[u][0], cur[u][1], acc);
+                acc = __builtin_fma(-v[u][0], v[u][1], acc);
             } else {
-                acc = __builtin_fmaf(-cur[u][0], cur[u][1], acc);
-                acc = __builtin_fmaf(-cur[u][2], cur[u][3], acc);
+                acc = __builtin_fmaf(-v[u][0], v[u][1], acc);
+                acc = __builtin_fmaf(-v[u][2], v[u][3], acc);
             }
         }
-#pragma unroll
-        for (int u = 0; u < kVec; ++u) cur[u] = nxt[u];
     }
     return acc;
 }
 
-// A workgroup owns 64 entries of column j: 64 / EPW walking wavefronts with EPW
-// entries each and one more for the pivot.  Row j goes into LDS: its parents'
+// A workgroup owns ENT of the 64 entries of a unit, in column j: ENT / EPW walking
+// wavefronts with EPW entries each and one more for the pivot.  Row j goes into LDS: its parents'
 // values in order, and their indices as a bitmap.  A walking wavefront takes its
 // entries' rows in chunks: each lane looks one index up and writes the pair
 // (L_ki, L_ji) to LDS; then lanes 0 .. EPW-1 run their entries' chains over those
@@ -117,28 +108,30 @@ __device__ __forceinline__ VT chain(const Pair<VT>* __restrict__ p, int n, VT ac
 // fma(-0, +0, acc) adds -0, which leaves every acc as it is, so the updates and
 // their order are those of ichol_level and L is bitwise the same.  The next
 // chunk's indices and values are on their way while the chains run.
-template <bool COUNT, typename VT, int EPW>
-__global__ __launch_bounds__((kUnit / EPW + 1) * kWave) void ichol_team(TeamArgs<VT> a,
+template <bool COUNT, typename VT, int EPW, int ENT>
+__global__ __launch_bounds__((ENT / EPW + 1) * kWave) void ichol_team(TeamArgs<VT> a,
                                                                          const kc::Unit* __restrict__ bunits,
                                                                          int64_t ubeg, int64_t uend, int cap) {
-    constexpr int kWalkers = kUnit / EPW;
+    constexpr int kWalkers = ENT / EPW;
+    constexpr int kParts = kUnit / ENT;  // workgroups per unit
     constexpr int kAtOnce = kWave / kChunk;  // entries whose chunks one load takes
     constexpr int kLoads = EPW / kAtOnce;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ double piv;
     __shared__ int piv_zero;
-    const int64_t bu = ubeg + int64_t(blockIdx.x);
+    const int64_t bu = ubeg + int64_t(blockIdx.x / kParts);
     if (bu >= uend) return;  // the whole workgroup
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int lane = threadIdx.x % kWave;
     const int j = __builtin_amdgcn_readfirstlane(bunits[bu].col);
-    const int first = __builtin_amdgcn_readfirstlane(bunits[bu].first);
+    const int first = __builtin_amdgcn_readfirstlane(bunits[bu].first) + int(blockIdx.x % kParts) * ENT;
+    if (a.colptr[j] + first >= a.colptr[j + 1]) return;  // the whole workgroup: past the column's end
     const int64_t t0 = a.rowptr[j];
     const int np = int(a.rowend[j] - 1 - t0);
     VT* sval = reinterpret_cast<VT*>(smem);
     Pair<VT>* pairs = reinterpret_cast<Pair<VT>*>(smem + size_t(cap) * sizeof(VT));
     MapWord* map = reinterpret_cast<MapWord*>(smem + size_t(cap) * sizeof(VT) +
-                                              sizeof(Pair<VT>) * size_t(kUnit) * kPairStride<VT>);
+                                              sizeof(Pair<VT>) * size_t(ENT) * kPairStride<VT>);
 
     // this wavefront's entries, one per lane: entry e = (k, j), row k from rp, pos entries before (k, j)
     const int64_t e = a.colptr[j] + first + wave * EPW + lane;
@@ -265,11 +258,14 @@ __global__ __launch_bounds__((kUnit / EPW + 1) * kWave) void ichol_team(TeamArgs
 
 int32_t team_cap(int32_t max_row) { return (max_row + 16) / 16 * 16; }
 
-template <bool COUNT, typename VT, int EPW>
-hipError_t launch_epw(const kc_factor* f, const TeamArgs<VT>& a, int64_t ub, int64_t ue, int32_t max_col,
+template <int V>
+using Int = std::integral_constant<int, V>;
+
+template <bool COUNT, typename VT, int EPW, int ENT>
+hipError_t launch_shape(const kc_factor* f, const TeamArgs<VT>& a, int64_t ub, int64_t ue, int32_t max_col,
                       hipStream_t s) {
     const size_t lds = kc::team_lds(f->max_row, max_col, sizeof(VT));
-    ichol_team<COUNT, VT, EPW><<<unsigned(ue - ub), (kUnit / EPW + 1) * kWave, lds, s>>>(
+    ichol_team<COUNT, VT, EPW, ENT><<<unsigned(ue - ub) * (kUnit / ENT), (ENT / EPW + 1) * kWave, lds, s>>>(
         a, f->bunits[f->order][0], ub, ue, team_cap(f->max_row));
     return hipGetLastError();
 }
@@ -284,6 +280,14 @@ size_t team_lds(int32_t max_row, int32_t max_col, size_t vt) {
            size_t(map_words(max_col)) * sizeof(MapWord);
 }
 
+// The split of a level.  At most a quarter of a unit per CU: 16 entries to a
+// workgroup, 4 to a wavefront, so that the chains' LDS reads (a whole instruction
+// for a wavefront's few entries) spread over more CUs.  Up to 2 units per CU: 32
+// and 8; whole units of 9 wavefronts ran one to a CU there, and a level of 257
+// units took twice as long as one of 256 (20,011 points in 3-D: 5.82 -> 5.42 ms,
+// 2,000 points 0.565 -> 0.515 ms with both).  Beyond, 64 and 16: half as many
+// chain reads per update (160,000 grid points: 17.9 ms against 20.3 ms with 8
+// entries to a wavefront; 32: 19.5 ms).
 template <typename VT>
 hipError_t launch_team(const kc_factor* f, bool count, int policy, double tau, int64_t ub, int64_t ue,
                        int32_t max_col, hipStream_t s) {
@@ -292,9 +296,16 @@ hipError_t launch_team(const kc_factor* f, bool count, int policy, double tau, i
                          static_cast<VT*>(f->L), static_cast<VT*>(f->Lcsc), f->diag, policy, tau,
                          f->counters + kNonpos, f->counters + kShifted, f->counters + kUpdates,
                          f->counters + kNonfinite};
-    if (ue - ub <= kNarrow * std::max(1, f->num_cu))
-        return count ? launch_epw<true, VT, 8>(f, a, ub, ue, max_col, s) : launch_epw<false, VT, 8>(f, a, ub, ue, max_col, s);
-    return count ? launch_epw<true, VT, 16>(f, a, ub, ue, max_col, s) : launch_epw<false, VT, 16>(f, a, ub, ue, max_col, s);
+    const int64_t units = ue - ub, cus = std::max(1, f->num_cu);
+    auto go = [&](auto c, auto epw, auto ent) {
+        return launch_shape<decltype(c)::value, VT, decltype(epw)::value, decltype(ent)::value>(f, a, ub, ue, max_col, s);
+    };
+    auto shape = [&](auto c) {
+        if (4 * units <= cus) return go(c, Int<4>(), Int<16>());
+        if (units <= 2 * cus) return go(c, Int<8>(), Int<32>());
+        return go(c, Int<16>(), Int<64>());
+    };
+    return count ? shape(std::true_type()) : shape(std::false_type());
 }
 
 template hipError_t launch_team<double>(const kc_factor*, bool, int, double, int64_t, int64_t, int32_t,
