@@ -219,12 +219,13 @@ kc_status kc_solve(const kc_factor *f, const double *b_dev, double *x_dev, int32
 kc_status kc_solve_noalloc(const kc_factor *f, const double *b_dev, double *x_dev, int32_t nrhs, void *stream);
 
 /* kc_factorize followed by kc_solve (Section 2.2 and Section 1, task (2)) in one
- * call, with the forward sweep overlapped with the factorization: after the
- * launch covering factor levels [l0, l1) is enqueued on `stream`, a second
- * stream owned by the factor (created on first use, default priority; it waits
- * on an event recorded on `stream`) runs the forward sweep of those levels,
- * while `stream` goes on with the next levels; the backward sweep runs on
- * `stream` after both.  Results are bitwise those of kc_factorize (or
+ * call, with the forward sweep overlapped with the factorization.  Where every
+ * factor level is small, both run on `stream` and a forward level shares the
+ * launch of the next factor level.  Otherwise, after the launch covering factor
+ * levels [l0, l1) is enqueued on `stream`, a second stream owned by the factor
+ * (created on first use, default priority; it waits on an event recorded on
+ * `stream`) runs the forward sweep of those levels, while `stream` goes on with
+ * the next levels.  The backward sweep runs on `stream` after both.  Results are bitwise those of kc_factorize (or
  * kc_factorize_batched) + kc_solve.  Arguments as for those calls (update
  * counting is not offered): for a batch plan pass ell_dev, one lengthscale per
  * instance (kernel.lengthscale is then ignored), else NULL.  All work is

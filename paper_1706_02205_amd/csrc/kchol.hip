@@ -51,7 +51,6 @@ constexpr int64_t kLongColumn = 2048;          // backward solve: longer columns
 constexpr int64_t kChunk = 512;                // entries per partial dot product of a long top part
 constexpr int64_t kFinePiece = 2048;           // entries per piece of a top column's rows below the top block
 constexpr int64_t kBandRows = 32768;           // rows per band of those pieces (8 RHS: 2 MB of x per band)
-constexpr int kMaxRhsPerPass = 8;
 
 // ---------------------------------------------------------------------------
 // small kernels
@@ -1977,11 +1976,11 @@ kc_status bwd_levels(const kc_factor* f, double* x, int ld, int r0, double* y, d
 }
 
 // Calls fn(std::integral_constant<int, NR>(), r0) for each pass of at most
-// kMaxRhsPerPass right-hand sides, NR being the pass's width.
+// kMaxRhs right-hand sides, NR being the pass's width.
 template <typename Fn>
 kc_status for_passes(int nrhs, Fn fn) {
-    for (int r0 = 0; r0 < nrhs; r0 += kMaxRhsPerPass) {
-        const int nr = std::min(kMaxRhsPerPass, nrhs - r0);
+    for (int r0 = 0; r0 < nrhs; r0 += kMaxRhs) {
+        const int nr = std::min(kMaxRhs, nrhs - r0);
         kc_status st;
         switch (nr) {
             case 1: st = fn(std::integral_constant<int, 1>(), r0); break;
@@ -2009,7 +2008,67 @@ kc_status solve_typed(const kc_factor* f, const double* b, double* x, int nrhs, 
     });
 }
 
-// Factorization and solve with the forward sweep overlapped: once the launch
+// Whether every level of the factorization runs by teams.
+bool all_teams(const kc_factor* f) {
+    const size_t nl = f->unit_off.size() - 1;
+    for (size_t v = 0; v < nl; ++v) {
+        const int64_t units = f->unit_off[v + 1] - f->unit_off[v];
+        if (units <= f->persist_max) return false;
+        if (!(f->prec == KC_FP64 ? team_level<double>(f, int(v), units) : team_level<float>(f, int(v), units)))
+            return false;
+    }
+    return true;
+}
+
+// Factorization and forward sweep in the same launches: the sweep's level v - 1
+// needs columns up to level v - 1 and rows up to level v - 2, so it shares the
+// launch of factor level v, whose few workgroups leave it room.  No second stream
+// and no event per level (some 8 us each: 2,000 points 1.85 - 2.5 ms with them, 1.55
+// with separate launches on one stream, 1.30 with shared ones; 20,011 in 3-D 10.4,
+// 9.4, 7.8 ms).  A larger level's workgroups fill the chip, and the sweep's LDS
+// (46 KB for 8 right-hand sides, 26 KB for 4) would keep some of them out: 90,601
+// grid points with 8 right-hand sides 11.55 ms shared up to 2 units per CU, 12.7 up
+// to 4; 50,003 on the sphere with 4 5.96 and 5.56 ms.  Those levels and the wide
+// rows take two launches.
+template <typename VT>
+kc_status factorize_forward(const kc_factor* f, int pol, double tau, const double* b, int nrhs, double* y,
+                            hipStream_t s) {
+    const size_t nl = f->unit_off.size() - 1;
+    const int64_t share = int64_t(std::max(1, f->num_cu)) * (nrhs <= 4 ? 4 : 2);
+    for (size_t v = 0; v <= nl; ++v) {
+        const int64_t ub = v < nl ? f->boff[0][v] : 0, ue = v < nl ? f->boff[0][v + 1] : 0;
+        const int64_t rb = v > 0 ? f->fwd_off[v - 1] : 0, re = v > 0 ? f->fwd_off[v] : 0;
+        const int32_t last = v < nl ? f->level_last[v] : 0;
+        if (re - rb < kWideRows && ue - ub <= share) {
+            KC_HIP(kc::launch_team_fwd<VT>(f, pol, tau, ub, ue, last, b, y, nrhs, rb, re, s));
+            continue;
+        }
+        KC_HIP(kc::launch_team<VT>(f, false, pol, tau, ub, ue, last, s));
+        const kc_status st = for_passes(nrhs, [&](auto w, int r0) -> kc_status {
+            KC_HIP(kc::launch_fwd<VT>(f, b, nrhs, r0, decltype(w)::value, y, rb, re, s));
+            return KC_OK;
+        });
+        if (st != KC_OK) return st;
+    }
+    return KC_OK;
+}
+
+// The second stream of kc_factorize_solve and its event, created when first needed.
+kc_status make_aux(kc_factor* f) {
+    if (f->aux) return KC_OK;
+    // default priority, on the current device
+    KC_HIP(hipStreamCreateWithFlags(&f->aux, hipStreamNonBlocking));
+    if (hipEventCreateWithFlags(&f->aux_ev, hipEventDisableTiming) != hipSuccess) {
+        (void)hipStreamDestroy(f->aux);
+        f->aux = nullptr;
+        kc::set_error("kc_factorize_solve: hipEventCreateWithFlags failed");
+        return KC_EHIP;
+    }
+    return KC_OK;
+}
+
+// Factorization and solve with the forward sweep overlapped: by shared launches
+// where every level is small, else on a second stream.  There, once the launch
 // covering factor levels [l0, l1) is enqueued on s, an event recorded after it
 // lets the second stream `aux` run the forward sweep of the same levels while s
 // goes on with the next factor levels.  A row of level v reads only L entries of
@@ -2019,6 +2078,18 @@ kc_status solve_typed(const kc_factor* f, const double* b, double* x, int nrhs, 
 template <typename VT>
 kc_status factorize_solve_typed(kc_factor* f, int pol, double tau, const double* b, double* x, int nrhs, double* y,
                                 double* partial, hipStream_t s) {
+    auto backward = [&]() {
+        return for_passes(nrhs, [&](auto w, int r0) {
+            constexpr int NR = decltype(w)::value;
+            return bwd_levels<VT, NR>(f, x, nrhs, r0, y, partial, s);
+        });
+    };
+    if (all_teams(f)) {
+        const kc_status st = factorize_forward<VT>(f, pol, tau, b, nrhs, y, s);
+        return st != KC_OK ? st : backward();
+    }
+    const kc_status made = make_aux(f);
+    if (made != KC_OK) return made;
     hipStream_t aux = f->aux;
     hipEvent_t ev = f->aux_ev;
     auto after = [&](int l0, int l1) -> kc_status {
@@ -2033,16 +2104,12 @@ kc_status factorize_solve_typed(kc_factor* f, int pol, double tau, const double*
     // whatever was enqueued on aux must finish before s goes on, also after an error
     KC_HIP(hipEventRecord(ev, aux));
     KC_HIP(hipStreamWaitEvent(s, ev, 0));
-    if (st != KC_OK) return st;
-    return for_passes(nrhs, [&](auto w, int r0) {
-        constexpr int NR = decltype(w)::value;
-        return bwd_levels<VT, NR>(f, x, nrhs, r0, y, partial, s);
-    });
+    return st != KC_OK ? st : backward();
 }
 
 size_t solve_scratch_bytes(const kc_factor* f, int32_t nrhs) {
     return align256(size_t(f->n) * size_t(nrhs) * sizeof(double)) +
-           size_t(std::max<int64_t>(f->max_slots, 1)) * kMaxRhsPerPass * sizeof(double);
+           size_t(std::max<int64_t>(f->max_slots, 1)) * kMaxRhs * sizeof(double);
 }
 
 }  // namespace
@@ -2456,10 +2523,9 @@ kc_status kc_factor_create(const kc_plan* plan, kc_prec prec, void* ws_dev, size
     return KC_OK;
 }
 
-static kc_status factorize_impl(kc_factor* f, const double* x_dev, double nu, double ell, const double* ells,
-                                kc_pivot pivot, double tau, int32_t count_updates, void* stream) {
-    const int tn = twonu_of(nu);
-    if (!tn) {
+static kc_status check_kernel(double nu, kc_pivot pivot, double tau, int* tn) {
+    *tn = twonu_of(nu);
+    if (!*tn) {
         kc::set_error("kc_factorize: nu must be 0.5, 1.5 or 2.5");
         return KC_EINVAL;
     }
@@ -2468,6 +2534,14 @@ static kc_status factorize_impl(kc_factor* f, const double* x_dev, double nu, do
         kc::set_error("kc_factorize: KC_PIVOT_SHIFT needs a finite tau > 0");
         return KC_EINVAL;
     }
+    return KC_OK;
+}
+
+static kc_status factorize_impl(kc_factor* f, const double* x_dev, double nu, double ell, const double* ells,
+                                kc_pivot pivot, double tau, int32_t count_updates, void* stream) {
+    int tn = 0;
+    const kc_status ok = check_kernel(nu, pivot, tau, &tn);
+    if (ok != KC_OK) return ok;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const bool cnt = count_updates != 0;
     kc_status st = launch_start(f, x_dev, tn, ell, ells, s);
@@ -2651,15 +2725,6 @@ kc_status kc_factorize_solve(kc_factor* f, const double* x_dev, kc_kernel kernel
     if (scratch_bytes < solve_scratch_bytes(f, nrhs) || reinterpret_cast<uintptr_t>(scratch_dev) % 256) {
         kc::set_error("kc_factorize_solve: scratch must be 256-byte aligned and hold kc_solve_bytes bytes");
         return KC_EWORKSPACE;
-    }
-    if (!f->aux) {  // the second stream, default priority, on the current device
-        KC_HIP(hipStreamCreateWithFlags(&f->aux, hipStreamNonBlocking));
-        if (hipEventCreateWithFlags(&f->aux_ev, hipEventDisableTiming) != hipSuccess) {
-            (void)hipStreamDestroy(f->aux);
-            f->aux = nullptr;
-            kc::set_error("kc_factorize_solve: hipEventCreateWithFlags failed");
-            return KC_EHIP;
-        }
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
     double* y = static_cast<double*>(scratch_dev);
@@ -2995,13 +3060,23 @@ kc_status kc_graph_create(kc_factor* f, const double* x_dev, double nu, double e
         e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
         kc_status st = KC_OK;
         if (e == hipSuccess) {
-            st = factorize_impl(f, x_dev, nu, ell, ell_dev, pivot, tau, 0, cs);
-            if (st == KC_OK) {
-                double* y = static_cast<double*>(scratch_dev);
-                double* partial = reinterpret_cast<double*>(static_cast<char*>(scratch_dev) +
-                                                            align256(size_t(f->n) * size_t(nrhs) * sizeof(double)));
-                st = f->prec == KC_FP64 ? solve_typed<double>(f, b_dev, sol_dev, nrhs, y, partial, cs)
-                                        : solve_typed<float>(f, b_dev, sol_dev, nrhs, y, partial, cs);
+            double* y = static_cast<double*>(scratch_dev);
+            double* partial = reinterpret_cast<double*>(static_cast<char*>(scratch_dev) +
+                                                        align256(size_t(f->n) * size_t(nrhs) * sizeof(double)));
+            if (!groups_on(f, false) && all_teams(f)) {  // one stream: the fused call's launches
+                int tn = 0;
+                st = check_kernel(nu, pivot, tau, &tn);
+                if (st == KC_OK) st = launch_start(f, x_dev, tn, ell, ell_dev, cs);
+                if (st == KC_OK)
+                    st = f->prec == KC_FP64 ? factorize_solve_typed<double>(f, int(pivot), tau, b_dev, sol_dev, nrhs, y,
+                                                                            partial, cs)
+                                            : factorize_solve_typed<float>(f, int(pivot), tau, b_dev, sol_dev, nrhs, y,
+                                                                           partial, cs);
+            } else {
+                st = factorize_impl(f, x_dev, nu, ell, ell_dev, pivot, tau, 0, cs);
+                if (st == KC_OK)
+                    st = f->prec == KC_FP64 ? solve_typed<double>(f, b_dev, sol_dev, nrhs, y, partial, cs)
+                                            : solve_typed<float>(f, b_dev, sol_dev, nrhs, y, partial, cs);
             }
             hipGraph_t graph = nullptr;
             hipError_t e2 = hipStreamEndCapture(cs, &graph);

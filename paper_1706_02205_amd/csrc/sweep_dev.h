@@ -98,6 +98,8 @@ __device__ __forceinline__ double wave_dot(const int32_t* __restrict__ idx, cons
     return v;  // lane r < NR holds right-hand side r's sum
 }
 
+constexpr int kMaxRhs = 8;  // right-hand sides of one pass over L
+
 // What the two sweeps differ in: the row's entries [p0, p1) of idx and val, its
 // diagonal entry, where the right-hand side comes from and where x goes.
 template <typename VT>

@@ -15,4 +15,10 @@ template <typename VT>
 hipError_t launch_team(const kc_factor* f, bool count, int policy, double tau, int64_t ub, int64_t ue,
                        int32_t max_col, hipStream_t s);
 
+// The same, and in the same launch the forward sweep (all nrhs right-hand sides) of
+// rows [rb, re) of fwd_rows, a level before it; either may be empty.
+template <typename VT>
+hipError_t launch_team_fwd(const kc_factor* f, int policy, double tau, int64_t ub, int64_t ue, int32_t max_col,
+                           const double* b, double* y, int nrhs, int64_t rb, int64_t re, hipStream_t s);
+
 }  // namespace kc

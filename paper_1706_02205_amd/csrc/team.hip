@@ -19,10 +19,11 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "chain.h"
+#include "sweep_dev.h"
 #include "team.h"
 
 using namespace kc::counter;
+using namespace kcdev;
 
 namespace {
 
@@ -33,6 +34,7 @@ constexpr int kUnit = 64;   // entries of a column per unit of the schedule
 // took 67 KB and few fitted on a CU (160,000 grid points, FP64: 26.6 ms against
 // 20.9 ms; 32: 25.1 ms; 8: 25.7 ms).
 constexpr int kChunk = 16;
+constexpr int kTeamThreads = 5 * kWave;  // four walking wavefronts and the pivot's
 
 // One update: L_ki and L_ji, (+0, +0) where row k's entry is no parent of j.
 template <typename VT>
@@ -100,31 +102,30 @@ __device__ __forceinline__ VT chain(const Pair<VT>* __restrict__ p, int n, VT ac
 }
 
 // A workgroup owns ENT of the 64 entries of a unit, in column j: ENT / EPW walking
-// wavefronts with EPW entries each and one more for the pivot.  Row j goes into LDS: its parents'
-// values in order, and their indices as a bitmap.  A walking wavefront takes its
-// entries' rows in chunks: each lane looks one index up and writes the pair
-// (L_ki, L_ji) to LDS; then lanes 0 .. EPW-1 run their entries' chains over those
-// pairs.  Indices that are no parents of j leave (+0, +0):
+// wavefronts with EPW entries each and one more for the pivot.  Row j goes into
+// LDS: its parents' values in order, and their indices as a bitmap.  A walking
+// wavefront takes its entries' rows in chunks: each lane looks one index up and
+// writes the pair (L_ki, L_ji) to LDS; then lanes 0 .. EPW-1 run their entries'
+// chains over those pairs.  Indices that are no parents of j leave (+0, +0):
 // fma(-0, +0, acc) adds -0, which leaves every acc as it is, so the updates and
 // their order are those of ichol_level and L is bitwise the same.  The next
 // chunk's indices and values are on their way while the chains run.
 template <bool COUNT, typename VT, int EPW, int ENT>
-__global__ __launch_bounds__((ENT / EPW + 1) * kWave) void ichol_team(TeamArgs<VT> a,
-                                                                         const kc::Unit* __restrict__ bunits,
-                                                                         int64_t ubeg, int64_t uend, int cap) {
+__device__ __forceinline__ void team_unit(const TeamArgs<VT>& a, const kc::Unit* __restrict__ bunits, int64_t ubeg,
+                                          int64_t uend, int cap, int block, unsigned char* smem) {
     constexpr int kWalkers = ENT / EPW;
+    static_assert(kWalkers + 1 == kTeamThreads / kWave);
     constexpr int kParts = kUnit / ENT;  // workgroups per unit
     constexpr int kAtOnce = kWave / kChunk;  // entries whose chunks one load takes
     constexpr int kLoads = EPW / kAtOnce;
-    extern __shared__ __align__(16) unsigned char smem[];
     __shared__ double piv;
     __shared__ int piv_zero;
-    const int64_t bu = ubeg + int64_t(blockIdx.x / kParts);
+    const int64_t bu = ubeg + int64_t(block / kParts);
     if (bu >= uend) return;  // the whole workgroup
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int lane = threadIdx.x % kWave;
     const int j = __builtin_amdgcn_readfirstlane(bunits[bu].col);
-    const int first = __builtin_amdgcn_readfirstlane(bunits[bu].first) + int(blockIdx.x % kParts) * ENT;
+    const int first = __builtin_amdgcn_readfirstlane(bunits[bu].first) + int(block % kParts) * ENT;
     if (a.colptr[j] + first >= a.colptr[j + 1]) return;  // the whole workgroup: past the column's end
     const int64_t t0 = a.rowptr[j];
     const int np = int(a.rowend[j] - 1 - t0);
@@ -155,7 +156,7 @@ __global__ __launch_bounds__((ENT / EPW + 1) * kWave) void ichol_team(TeamArgs<V
         atomicOr(&map[i >> 5].bits, 1u << (i & 31));
         if (t == 0 || (a.colidx[t0 + t - 1] >> 5) != (i >> 5)) map[i >> 5].rank = uint32_t(t);
     }
-    kcdev::pad_row(sval, np, int(threadIdx.x));
+    pad_row(sval, np, int(threadIdx.x));
     __syncthreads();
 
     unsigned long long hits = 0;
@@ -215,7 +216,7 @@ __global__ __launch_bounds__((ENT / EPW + 1) * kWave) void ichol_team(TeamArgs<V
             wave_lds_sync();
         }
     } else {
-        double dacc = kcdev::pivot_sum(sval, np, 1.0);  // from Theta_jj = 1
+        double dacc = pivot_sum(sval, np, 1.0);  // from Theta_jj = 1
         bool zero = false, shift = false;
         if (a.policy == KC_PIVOT_ZERO) {
             zero = !(dacc > 0.0);
@@ -256,18 +257,61 @@ __global__ __launch_bounds__((ENT / EPW + 1) * kWave) void ichol_team(TeamArgs<V
     }
 }
 
+template <bool COUNT, typename VT, int EPW, int ENT>
+__global__ __launch_bounds__(kTeamThreads) void ichol_team(TeamArgs<VT> a, const kc::Unit* __restrict__ bunits,
+                                                           int64_t ubeg, int64_t uend, int cap) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    team_unit<COUNT, VT, EPW, ENT>(a, bunits, ubeg, uend, cap, blockIdx.x, smem);
+}
+
+// A level of the factorization and, in the workgroups from nteam on, a level of
+// the forward sweep: rows [rbeg, rend), `passes` times over for more than 8
+// right-hand sides.  The sweep's level is an earlier one than the factorization's,
+// so neither reads what the other writes.
+template <typename VT, int EPW, int ENT, int NR>
+__global__ __launch_bounds__(kTeamThreads) void ichol_team_fwd(TeamArgs<VT> a, const kc::Unit* __restrict__ bunits,
+                                                               int64_t ubeg, int64_t uend, int cap, int nteam,
+                                                               SweepArgs<VT> sw, int nrhs, int64_t rbeg, int rows) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    if (int(blockIdx.x) < nteam) {
+        team_unit<false, VT, EPW, ENT>(a, bunits, ubeg, uend, cap, blockIdx.x, smem);
+        return;
+    }
+    const int block = int(blockIdx.x) - nteam;
+    sw.r0 = block / rows * kMaxRhs;
+    sweep_row<VT, NR, kTeamThreads, true>(sw, sw.rows[rbeg + block % rows], min(kMaxRhs, nrhs - sw.r0),
+                                          reinterpret_cast<double*>(smem));
+}
+
 int32_t team_cap(int32_t max_row) { return (max_row + 16) / 16 * 16; }
 
 template <int V>
 using Int = std::integral_constant<int, V>;
 
-template <bool COUNT, typename VT, int EPW, int ENT>
-hipError_t launch_shape(const kc_factor* f, const TeamArgs<VT>& a, int64_t ub, int64_t ue, int32_t max_col,
-                      hipStream_t s) {
-    const size_t lds = kc::team_lds(f->max_row, max_col, sizeof(VT));
-    ichol_team<COUNT, VT, EPW, ENT><<<unsigned(ue - ub) * (kUnit / ENT), (ENT / EPW + 1) * kWave, lds, s>>>(
-        a, f->bunits[f->order][0], ub, ue, team_cap(f->max_row));
-    return hipGetLastError();
+template <typename VT>
+TeamArgs<VT> team_args(const kc_factor* f, int policy, double tau) {
+    return {f->colptr, f->rowidx, f->csc2csr, f->rowptr, f->rowend, f->colidx,
+            static_cast<VT*>(f->L), static_cast<VT*>(f->Lcsc), f->diag, policy, tau,
+            f->counters + kNonpos, f->counters + kShifted, f->counters + kUpdates, f->counters + kNonfinite};
+}
+
+template <int V>
+using Int = std::integral_constant<int, V>;
+
+// The split of a level.  At most a quarter of a unit per CU: 16 entries to a
+// workgroup, 4 to a wavefront, so that the chains' LDS reads (a whole instruction
+// for a wavefront's few entries) spread over more CUs.  Up to 2 units per CU: 32
+// and 8; whole units of 9 wavefronts ran one to a CU there, and a level of 257
+// units took twice as long as one of 256 (2,000 points 0.565 -> 0.516 ms, 20,011
+// in 3-D 5.35 -> 5.19 ms with both).  Beyond, 64 and 16: half as many chain reads
+// per update (160,000 grid points: 17.9 ms against 20.3 ms with 8 entries to a
+// wavefront; 32: 19.5 ms).
+template <typename Fn>
+void team_shape(const kc_factor* f, int64_t units, Fn fn) {
+    const int64_t cus = std::max(1, f->num_cu);
+    if (4 * units <= cus) fn(Int<4>(), Int<16>());
+    else if (units <= 2 * cus) fn(Int<8>(), Int<32>());
+    else fn(Int<16>(), Int<64>());
 }
 
 }  // namespace
@@ -280,34 +324,53 @@ size_t team_lds(int32_t max_row, int32_t max_col, size_t vt) {
            size_t(map_words(max_col)) * sizeof(MapWord);
 }
 
-// The split of a level.  At most a quarter of a unit per CU: 16 entries to a
-// workgroup, 4 to a wavefront, so that the chains' LDS reads (a whole instruction
-// for a wavefront's few entries) spread over more CUs.  Up to 2 units per CU: 32
-// and 8; whole units of 9 wavefronts ran one to a CU there, and a level of 257
-// units took twice as long as one of 256 (20,011 points in 3-D: 5.82 -> 5.42 ms,
-// 2,000 points 0.565 -> 0.515 ms with both).  Beyond, 64 and 16: half as many
-// chain reads per update (160,000 grid points: 17.9 ms against 20.3 ms with 8
-// entries to a wavefront; 32: 19.5 ms).
 template <typename VT>
 hipError_t launch_team(const kc_factor* f, bool count, int policy, double tau, int64_t ub, int64_t ue,
                        int32_t max_col, hipStream_t s) {
     if (ue <= ub) return hipSuccess;
-    const TeamArgs<VT> a{f->colptr, f->rowidx, f->csc2csr, f->rowptr, f->rowend, f->colidx,
-                         static_cast<VT*>(f->L), static_cast<VT*>(f->Lcsc), f->diag, policy, tau,
-                         f->counters + kNonpos, f->counters + kShifted, f->counters + kUpdates,
-                         f->counters + kNonfinite};
-    const int64_t units = ue - ub, cus = std::max(1, f->num_cu);
-    auto go = [&](auto c, auto epw, auto ent) {
-        return launch_shape<decltype(c)::value, VT, decltype(epw)::value, decltype(ent)::value>(f, a, ub, ue, max_col, s);
-    };
-    auto shape = [&](auto c) {
-        if (4 * units <= cus) return go(c, Int<4>(), Int<16>());
-        if (units <= 2 * cus) return go(c, Int<8>(), Int<32>());
-        return go(c, Int<16>(), Int<64>());
-    };
-    return count ? shape(std::true_type()) : shape(std::false_type());
+    const TeamArgs<VT> a = team_args<VT>(f, policy, tau);
+    const size_t lds = team_lds(f->max_row, max_col, sizeof(VT));
+    const int32_t cap = team_cap(f->max_row);
+    team_shape(f, ue - ub, [&](auto epw, auto ent) {
+        constexpr int EPW = decltype(epw)::value, ENT = decltype(ent)::value;
+        const unsigned grid = unsigned(ue - ub) * (kUnit / ENT);
+        if (count) ichol_team<true, VT, EPW, ENT><<<grid, kTeamThreads, lds, s>>>(a, f->bunits[f->order][0], ub, ue, cap);
+        else ichol_team<false, VT, EPW, ENT><<<grid, kTeamThreads, lds, s>>>(a, f->bunits[f->order][0], ub, ue, cap);
+    });
+    return hipGetLastError();
 }
 
+template <typename VT>
+hipError_t launch_team_fwd(const kc_factor* f, int policy, double tau, int64_t ub, int64_t ue, int32_t max_col,
+                           const double* b, double* y, int nrhs, int64_t rb, int64_t re, hipStream_t s) {
+    const int64_t rows = re - rb;
+    if (ue <= ub && rows <= 0) return hipSuccess;
+    const TeamArgs<VT> a = team_args<VT>(f, policy, tau);
+    const SweepArgs<VT> sw = fwd_args<VT>(f, b, nrhs, 0, y);
+    const int32_t cap = team_cap(f->max_row);
+    const int64_t passes = (nrhs + kMaxRhs - 1) / kMaxRhs;
+    team_shape(f, ue - ub, [&](auto epw, auto ent) {
+        constexpr int EPW = decltype(epw)::value, ENT = decltype(ent)::value;
+        const int nteam = int(ue - ub) * (kUnit / ENT);
+        auto go = [&](auto w) {
+            constexpr int NR = decltype(w)::value;
+            size_t lds = ue > ub ? team_lds(f->max_row, max_col, sizeof(VT)) : 0;
+            if (rows > 0) lds = std::max(lds, sweep_lds(NR, kTeamThreads) * sizeof(double));
+            ichol_team_fwd<VT, EPW, ENT, NR><<<unsigned(nteam) + unsigned(rows * passes), kTeamThreads, lds, s>>>(
+                a, f->bunits[f->order][0], ub, ue, cap, nteam, sw, nrhs, rb, int(std::max<int64_t>(rows, 1)));
+        };
+        if (nrhs == 1) go(Int<1>());
+        else if (nrhs == 2) go(Int<2>());
+        else if (nrhs <= 4) go(Int<4>());
+        else go(Int<8>());
+    });
+    return hipGetLastError();
+}
+
+template hipError_t launch_team_fwd<double>(const kc_factor*, int, double, int64_t, int64_t, int32_t, const double*,
+                                            double*, int, int64_t, int64_t, hipStream_t);
+template hipError_t launch_team_fwd<float>(const kc_factor*, int, double, int64_t, int64_t, int32_t, const double*,
+                                           double*, int, int64_t, int64_t, hipStream_t);
 template hipError_t launch_team<double>(const kc_factor*, bool, int, double, int64_t, int64_t, int32_t,
                                          hipStream_t);
 template hipError_t launch_team<float>(const kc_factor*, bool, int, double, int64_t, int64_t, int32_t,

@@ -24,7 +24,7 @@ def test_every_row_length_bitwise(K, n, nrhs):
     import oracle as O
     from paper_1706_02205_amd import workloads as W
     x = W.uniform_points(n, 2, 400 + n)
-    rho = 200.0
+    rho = 1e6
     P = O.pattern(x, rho)
     assert P.nnz == n * (n + 1) // 2
     R = O.ichol(P, O.theta_on_pattern(P, 0.5, 0.3))
