@@ -44,7 +44,7 @@ def build(verbose: bool = False) -> str:
         obj = os.path.join(BUILD, src + ".o")
         _run(["g++", *HOST_FLAGS, *inc, "-c", os.path.join(CSRC, src), "-o", obj], verbose)
         objs.append(obj)
-    hips = ("kchol.hip", "team.hip", "sweep.hip", "pcg.hip")
+    hips = ("kchol.hip", "group.hip", "team.hip", "sweep.hip", "pcg.hip")
     cmds = [[HIPCC, *HIP_FLAGS, *inc, "-c", os.path.join(CSRC, src), "-o", os.path.join(BUILD, src + ".o")]
             for src in hips]
     with ThreadPoolExecutor(max_workers=len(cmds)) as pool:  # one compiler process per source

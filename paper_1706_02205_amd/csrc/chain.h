@@ -12,6 +12,14 @@
 
 namespace kcdev {
 
+// Wave-local LDS ordering: every lane's LDS writes are visible to the other
+// lanes of the same wavefront after this point.
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 __device__ __forceinline__ void keep_loads_above() { asm volatile("" ::: "memory"); }
 
 // Row entries are padded to a multiple of this.

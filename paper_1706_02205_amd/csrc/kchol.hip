@@ -33,6 +33,7 @@
 #include "crmath.h"
 #include "chain.h"
 #include "factor.h"
+#include "group.h"
 #include "plan.h"
 #include "sweep.h"
 #include "sweep_dev.h"
@@ -40,6 +41,8 @@
 
 using kc::Unit;
 using namespace kcdev;
+using kc::kGroupCols;
+using kc::kGroupRows;
 using namespace kc::counter;
 
 namespace {
@@ -134,14 +137,6 @@ __global__ __launch_bounds__(kBlock) void unit_walk_kernel(const Unit* __restric
 }
 
 // ---------------------------------------------------------------------------
-// Wave-local LDS ordering: every lane's LDS writes are visible to the other
-// lanes of the same wavefront after this point.
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Row windows.  L2 lines are 128 bytes, and with thousands of rows walked at
 // once a line is evicted before a lane comes back for its other half, so every
 // load below reads whole lines: 64 column-index gaps (16 bits each, 128 B) per
@@ -838,216 +833,6 @@ __global__ __launch_bounds__(WPB * kWave) void ichol_persistent(IcholArgs<VT> a,
         }
         grid.sync();
     }
-}
-
-// ---------------------------------------------------------------------------
-// Supernodal groups on the matrix cores (mixed precision, supernodal plans).
-//
-// The block-closed pattern makes every member of a supernode J = [s0, s1) share
-// one row structure: row g of a member is P(J) (the parents of s0), then s0..g-1;
-// column g is g..s1-1, then the rows O_J of the other supernodes below J.  A
-// group G = [g0, g1) of at most 16 consecutive members therefore shares its
-// parents P_G = row g0 before its diagonal, and for a row k of column g0 the
-// Schur updates of all 16 entries (k, g), g in G, run over the same parents
-// i in P_G that row k holds:
-//     a_kg = Theta_kg - sum_{i in P_G, i in row k} L_ki L_gi - sum_{g0 <= h < g} L_kh L_gh.
-// The first sum, for 64 rows at once, is a dense product (64 x |P_G|) . (|P_G| x 16)
-// on v_mfma_f32_16x16x4f32: row k's values are scattered into an LDS tile over
-// P_G (row k is walked once for the whole group, instead of once per column as
-// in the element-wise kernel) and the group's rows L_{G,P_G} form the other
-// operand.  The second sum and the divisions follow in registers, column by
-// column: the dense Cholesky of the group's diagonal block with FP64 pivots
-// (accumulated as in the element-wise kernel, FP32 x FP32 products exact in
-// FP64), then the panel rows.  A unit is one group with its 16 diagonal rows
-// (recomputed by every unit of the group, written by the first) and 48 panel
-// rows; the units of a level of the group DAG run in one launch.
-constexpr int kGroupCols = 16;  // columns of a group: the width of the MFMA tile
-constexpr int kGroupRows = 48;  // panel rows of a unit, beside the group's 16 diagonal rows
-constexpr int kGroupKC = 64;    // parents per LDS chunk
-
-typedef float mfma_f4 __attribute__((ext_vector_type(4)));
-
-template <int TWONU>
-__global__ __launch_bounds__(kWave) void ichol_group(IcholArgs<float> a, const double* __restrict__ xh, int d,
-                                                     float ell, const kc::GroupDesc* __restrict__ groups,
-                                                     const int2* __restrict__ gunits, int64_t ubeg, int64_t uend) {
-    __shared__ float As[kWave][kGroupKC + 1];
-    __shared__ float Bs[kGroupCols][kGroupKC + 1];
-    __shared__ float Cs[kWave][kGroupCols + 1];
-    __shared__ float Ld[kGroupCols][kGroupCols + 1];
-    __shared__ double piv[kGroupCols];
-    __shared__ int pzero[kGroupCols];
-    extern __shared__ __align__(16) unsigned char smem[];
-    int32_t* sP = reinterpret_cast<int32_t*>(smem);  // the group's parents, then a sentinel
-    const int lane = threadIdx.x;
-    const int64_t u = ubeg + int64_t(blockIdx.x);
-    if (u >= uend) return;
-    const int2 gu = gunits[u];
-    const kc::GroupDesc G = groups[gu.x];
-    const int tile = gu.y;
-    const int g0 = G.g0, m = G.g1 - G.g0;
-    const int64_t t0 = a.rowptr[g0];
-    const int np = int(a.rowend[g0] - 1 - t0);
-    for (int t = lane; t < np; t += kWave) sP[t] = a.colidx[t0 + t];
-    if (lane == 0) sP[np] = INT_MAX;
-    // this lane's row: lanes 0..15 the group's diagonal rows g0 + lane, lanes 16..63 panel rows
-    const int64_t cg0 = a.colptr[g0];
-    int k = -1;
-    int64_t eoff = -1;  // offset of (k, g0) in column g0
-    if (lane < kGroupCols) {
-        if (lane < m) {
-            k = g0 + lane;
-            eoff = lane;
-        }
-    } else {
-        const int64_t pr = int64_t(tile) * kGroupRows + (lane - kGroupCols);
-        if (pr < G.nb) {
-            eoff = m + pr;
-            k = a.rowidx[cg0 + eoff];
-        }
-    }
-    const bool panel = lane >= kGroupCols && k >= 0;
-    int64_t p = 0, pend = 0;  // the walk of row k before (k, g0)
-    int q = 0;                // cursor over the parents
-    if (panel) {
-        p = a.rowptr[k];
-        pend = a.csc2csr[cg0 + eoff];
-    }
-    wave_lds_sync();
-
-    mfma_f4 acc[4];
-#pragma unroll
-    for (int rb = 0; rb < 4; ++rb) acc[rb] = mfma_f4{0.f, 0.f, 0.f, 0.f};
-    double dd = 1.0;  // pivot of diagonal row `lane`: Theta_jj = 1 minus the squares, ascending
-    for (int c0 = 0; c0 < np; c0 += kGroupKC) {
-        const int cn = np - c0 < kGroupKC ? np - c0 : kGroupKC;
-        for (int idx = lane; idx < kGroupCols * kGroupKC; idx += kWave) {
-            const int g = idx / kGroupKC, qq = idx % kGroupKC;
-            Bs[g][qq] = (g < m && qq < cn) ? a.Lv[a.rowptr[g0 + g] + c0 + qq] : 0.f;
-        }
-#pragma unroll
-        for (int qq = 0; qq < kGroupKC; ++qq) As[lane][qq] = 0.f;
-        wave_lds_sync();
-        if (lane < m) {  // a diagonal row's prefix is P_G itself
-            for (int qq = 0; qq < cn; ++qq) {
-                const float v = Bs[lane][qq];
-                As[lane][qq] = v;
-                dd = __builtin_fma(-double(v), double(v), dd);
-            }
-        }
-        bool more = panel && p < pend;
-        while (more) {  // eight entries of row k per load, from an 8-aligned start (rows are 64-aligned)
-            const int64_t bp = p & ~int64_t(7);
-            const int4 ia = *reinterpret_cast<const int4*>(a.colidx + bp);
-            const int4 ib = *reinterpret_cast<const int4*>(a.colidx + bp + 4);
-            const float4 va = *reinterpret_cast<const float4*>(a.Lv + bp);
-            const float4 vb = *reinterpret_cast<const float4*>(a.Lv + bp + 4);
-            const int ii[8] = {ia.x, ia.y, ia.z, ia.w, ib.x, ib.y, ib.z, ib.w};
-            const float vv[8] = {va.x, va.y, va.z, va.w, vb.x, vb.y, vb.z, vb.w};
-#pragma unroll
-            for (int h = 0; h < 8; ++h) {
-                if (more && bp + h >= p) {
-                    if (bp + h >= pend) {
-                        more = false;
-                    } else {
-                        const int i = ii[h];
-                        while (sP[q] < i) ++q;  // the sentinel stops at np
-                        if (q >= c0 + cn) {
-                            more = false;  // a later chunk: resume here
-                        } else {
-                            if (sP[q] == i) As[lane][q - c0] = vv[h];
-                            p = bp + h + 1;
-                        }
-                    }
-                }
-            }
-        }
-        wave_lds_sync();
-#pragma unroll
-        for (int ks = 0; ks < kGroupKC / 4; ++ks) {
-            const int kk = ks * 4 + lane / 16, col = lane % 16;
-            const float bv = Bs[col][kk];
-#pragma unroll
-            for (int rb = 0; rb < 4; ++rb)
-                acc[rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(As[rb * 16 + col][kk], bv, acc[rb], 0, 0, 0);
-        }
-        wave_lds_sync();
-    }
-#pragma unroll
-    for (int rb = 0; rb < 4; ++rb)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) Cs[rb * 16 + 4 * (lane / 16) + i][lane % 16] = acc[rb][i];
-    wave_lds_sync();
-
-    // External part: a_g = Theta_kg - C_kg.  A panel row's Theta is in Lcsc, which
-    // this unit alone overwrites; the diagonal rows are recomputed by every unit of
-    // the group while its first unit writes their L there, so theirs is evaluated here.
-    float av[kGroupCols], Lr[kGroupCols];
-    // CSC entry of (k, g0 + g): a row of the supernode by its distance from the diagonal, a row below by its place
-    auto entry = [&](int g) {
-        const int j = g0 + g;
-        return k < G.s1 ? a.colptr[j] + (k - j) : a.colptr[j] + (G.s1 - j) + (eoff - (G.s1 - g0));
-    };
-#pragma unroll
-    for (int g = 0; g < kGroupCols; ++g) {
-        av[g] = 0.f;
-        Lr[g] = 0.f;
-        if (k >= 0 && g < m && (panel || lane > g)) {
-            const float th = panel ? a.Lcsc[entry(g)]
-                                   : kcdev::matern_f32<TWONU>(
-                                         float(kcdev::dist(xh + int64_t(k) * d, xh + int64_t(g0 + g) * d, d)), ell);
-            av[g] = th - Cs[lane][g];
-        }
-    }
-    // the group's columns in order: pivot from diagonal lane g, then the rows below
-#pragma unroll
-    for (int g = 0; g < kGroupCols; ++g) {
-        if (g < m) {
-            if (lane == g) {
-                double pd = dd;
-#pragma unroll
-                for (int h = 0; h < g; ++h) pd = __builtin_fma(-double(Lr[h]), double(Lr[h]), pd);
-                bool zero = false;
-                if (a.policy == KC_PIVOT_ZERO) {
-                    zero = !(pd > 0.0);
-                } else if (!(pd > a.tau)) {
-                    pd = a.tau;
-                    if (tile == 0) atomicAdd(a.counters + kShifted, 1ull);
-                }
-                if (zero && tile == 0) atomicAdd(a.counters + kNonpos, 1ull);
-                piv[g] = zero ? 0.0 : __builtin_sqrt(pd);
-                pzero[g] = zero;
-            }
-            wave_lds_sync();
-            const double ljj = piv[g];
-            const bool zero = pzero[g] != 0;
-            if ((lane < m && lane > g) || panel) {
-                float x = av[g];
-#pragma unroll
-                for (int h = 0; h < g; ++h) x = __builtin_fmaf(-Lr[h], Ld[g][h], x);
-                Lr[g] = zero ? 0.f : float(double(x) / ljj);
-                if (lane < m) Ld[lane][g] = Lr[g];
-            }
-            wave_lds_sync();
-        }
-    }
-    // write: panel rows by every unit, the diagonal block by the group's first unit
-    bool bad = false;
-    if (k >= 0 && (panel || tile == 0)) {
-#pragma unroll
-        for (int g = 0; g < kGroupCols; ++g) {
-            if (g < m && (panel || lane >= g)) {
-                const int64_t e = entry(g);
-                const float out = lane == g ? float(piv[g]) : Lr[g];
-                a.Lcsc[e] = out;
-                a.Lv[a.csc2csr[e]] = out;
-                if (lane == g) a.diag[g0 + g] = piv[g];
-                bad = bad || !__builtin_isfinite(out);
-            }
-        }
-    }
-    const unsigned long long nf = __ballot(bad);
-    if (nf && lane == 0) atomicAdd(a.counters + kNonfinite, (unsigned long long)__popcll(nf));
 }
 
 // ---------------------------------------------------------------------------
@@ -1870,20 +1655,8 @@ kc_status launch_levels(const kc_factor* f, bool cnt, int pol, double tau, hipSt
 
 // The factorization by supernodal groups: one launch per level of the group DAG.
 kc_status launch_groups(const kc_factor* f, int tn, double ell, int pol, double tau, hipStream_t s) {
-    const IcholArgs<float> a = ichol_args<float>(f, pol, tau);
-    const size_t lds = (size_t(f->cap) + 1) * sizeof(int32_t);
-    const size_t nl = f->goff.size() - 1;
-    for (size_t v = 0; v < nl; ++v) {
-        const int64_t ub = f->goff[v], ue = f->goff[v + 1];
-        if (ue <= ub) continue;
-        auto go = [&](auto kernel) {
-            kernel<<<unsigned(ue - ub), kWave, lds, s>>>(a, f->xh, f->d, float(ell), f->groups, f->gunits, ub, ue);
-        };
-        if (tn == 1) go(ichol_group<1>);
-        else if (tn == 3) go(ichol_group<3>);
-        else go(ichol_group<5>);
-        KC_LAUNCH_CHECK();
-    }
+    for (size_t v = 0; v + 1 < f->goff.size(); ++v)
+        KC_HIP(kc::launch_group(f, tn, ell, pol, tau, f->goff[v], f->goff[v + 1], s));
     return KC_OK;
 }
 

@@ -53,12 +53,6 @@ struct __align__(8) MapWord {
 };
 __host__ __device__ constexpr int map_words(int j) { return j / 32 + 1; }
 
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 template <typename VT>
 struct TeamArgs {
     const int64_t* colptr;
