@@ -22,44 +22,9 @@ __device__ __forceinline__ void wave_lds_sync() {
 
 __device__ __forceinline__ void keep_loads_above() { asm volatile("" ::: "memory"); }
 
-// Row entries are padded to a multiple of this.
+// Entries of a chain are padded to a multiple of this.
 constexpr int kChainPad = 16;
 __host__ __device__ constexpr int chain_padded(int n) { return (n + kChainPad - 1) / kChainPad * kChainPad; }
-
-// acc <- fma(-l[q], y[q], acc), q = 0 .. m - 1 ascending; m a positive multiple of 16, l and y 16-byte aligned.
-__device__ __forceinline__ double chain_dot(const double* __restrict__ l, const double* __restrict__ y, int m,
-                                            double acc) {
-    struct Eight {
-        double2 l[4], y[4];
-    };
-    const double2* lv = reinterpret_cast<const double2*>(l);
-    const double2* yv = reinterpret_cast<const double2*>(y);
-    auto load = [&](Eight& e, int q) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            e.l[u] = lv[q / 2 + u];
-            e.y[u] = yv[q / 2 + u];
-        }
-    };
-    auto apply = [&](const Eight& e) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            acc = __builtin_fma(-e.l[u].x, e.y[u].x, acc);
-            acc = __builtin_fma(-e.l[u].y, e.y[u].y, acc);
-        }
-    };
-    Eight a, b;
-    load(a, 0);
-    for (int q = 0; q < m; q += 16) {
-        load(b, q + 8);
-        keep_loads_above();
-        apply(a);
-        load(a, q + 16 < m ? q + 16 : 0);
-        keep_loads_above();
-        apply(b);
-    }
-    return acc;
-}
 
 // acc <- fma(-v, v, acc) over the staged row of np values in ascending order, in FP64 (padded, see pad_row).
 template <typename VT>

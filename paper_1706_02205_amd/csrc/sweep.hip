@@ -6,12 +6,11 @@
 // right-hand-side row).  In a level of few rows nothing hides those: a wavefront
 // per row took 384 entries at a time (bwd_solve still does, in large levels), and
 // each such step waited for both loads and then for an LDS round trip per eight
-// fmas.  Here the four wavefronts
-// of a workgroup gather a block of the row while the first of them runs the
-// previous block's chain, and the chain requests its next eight entries from LDS
-// before it uses the current eight.  Measured, a whole solve: 2,000 points 1.33 ->
-// 1.02 ms, 20,011 in 3-D 5.6 -> 4.2 ms, 90,601 grid points with 8 right-hand sides
-// 6.8 -> 5.0 ms, 160,000 with one 5.9 -> 4.7 ms.
+// fmas.  Here the four wavefronts of a workgroup gather a block of the row while
+// the first (and, past four right-hand sides, the second) runs the previous
+// block's chains, 16 lanes to a right-hand side (row_chain.h).  Measured, a whole
+// solve: 2,000 points 1.33 -> 0.94 ms, 20,011 in 3-D 5.6 -> 3.9 ms, 90,601 grid
+// points with 8 right-hand sides 6.8 -> 4.8 ms, 160,000 with one 5.9 -> 4.3 ms.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>

@@ -4,8 +4,8 @@
 
 #include <hip/hip_runtime.h>
 
-#include "chain.h"
 #include "factor.h"
+#include "row_chain.h"
 
 namespace kcdev {
 
@@ -135,9 +135,9 @@ __device__ __forceinline__ void wide_row(const SweepArgs<VT>& a, int k, int nr, 
 }
 
 // One row by a workgroup of THREADS (a multiple of 16), right-hand sides r0 ..
-// r0 + nr - 1 (nr <= NR).  Entries past the row's end are staged as L = y = +0:
-// fma(-0, +0, acc) changes no acc, so the result is the sequential substitution's
-// bit for bit.
+// r0 + nr - 1 (nr <= NR).  The chain is a row chain per right-hand side (L staged
+// negated).  Entries past the row's end are staged as -0 and +0: fma(-0, +0, acc)
+// changes no acc, so the result is the sequential substitution's bit for bit.
 template <typename VT, int NR, int THREADS, bool FWD>
 __device__ __forceinline__ void sweep_row(const SweepArgs<VT>& a, int k, int nr, double* __restrict__ lds) {
     constexpr int kStride = THREADS + 2;  // rows of consecutive right-hand sides 4 banks apart
@@ -162,15 +162,18 @@ __device__ __forceinline__ void sweep_row(const SweepArgs<VT>& a, int k, int nr,
         for (int r = 0; r < NR; ++r) v[r] = ci < 0 || r >= nr ? 0.0 : src[r];
     };
     auto stage = [&](int buf) {
-        sL(buf)[tid] = lv;
+        sL(buf)[tid] = -lv;
 #pragma unroll
         for (int r = 0; r < NR; ++r) sY(buf)[r * kStride + tid] = v[r];
     };
     entries(0, ci, lv);
     entries(THREADS, cn, ln);
+    // right-hand side r is the business of 16 lanes: rows 0 .. 3 of wavefront 0, then of wavefront 1
+    const int r = tid / kRowLanes;
+    const bool chains = tid < 64 * ((NR + 3) / 4);  // whole wavefronts
     double acc = 0.0, lkk = 1.0;
-    if (tid < nr) {
-        acc = FWD ? a.b[int64_t(a.perm[k]) * a.ld + a.r0 + tid] : a.y[int64_t(k) * a.ld + a.r0 + tid];
+    if (r < nr) {
+        acc = FWD ? a.b[int64_t(a.perm[k]) * a.ld + a.r0 + r] : a.y[int64_t(k) * a.ld + a.r0 + r];
         lkk = diag_value(a.val, a.diag, pd, k);
     }
     if (n > 0) {
@@ -187,17 +190,17 @@ __device__ __forceinline__ void sweep_row(const SweepArgs<VT>& a, int k, int nr,
                 entries(at + 2 * THREADS, cn, ln);
             }
             const int m = n - at < THREADS ? chain_padded(n - at) : THREADS;
-            if (tid < nr) acc = chain_dot(sL(buf), sY(buf) + tid * kStride, m, acc);
+            if (chains) acc = row_chain(sL(buf), sY(buf) + (r < NR ? r : 0) * kStride, m, acc);
             if (more) {
                 stage(buf ^ 1);
                 __syncthreads();
             }
         }
     }
-    if (tid < nr) {
+    if (r < nr && tid % kRowLanes == 0) {
         const double x = lkk == 0.0 ? 0.0 : acc / lkk;
-        a.y[int64_t(k) * a.ld + a.r0 + tid] = x;
-        if constexpr (!FWD) a.x[int64_t(a.perm[k]) * a.ld + a.r0 + tid] = x;
+        a.y[int64_t(k) * a.ld + a.r0 + r] = x;
+        if constexpr (!FWD) a.x[int64_t(a.perm[k]) * a.ld + a.r0 + r] = x;
     }
 }
 
