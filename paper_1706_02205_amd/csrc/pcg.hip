@@ -16,6 +16,7 @@
 #include <algorithm>
 #include <cmath>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "factor.h"
@@ -105,95 +106,117 @@ __device__ __forceinline__ double matern_fast(double a, const double* __restrict
 }
 
 // Y[i, r0+r] = sum_j Theta(x_i, x_j) X[j, r0+r].  x: n x d (any order, X and Y
-// in the same order).  D = d for d <= 3 (coordinates in registers), D = 0 for
-// any d <= 32 (own coordinates re-read through the cache).  Columns stream
-// through LDS in tiles shared by the 256 rows of a block.
+// in the same order).  D >= d coordinates of each row are held in registers, the
+// ones past d as zeros on both sides.  Columns stream through LDS in tiles shared
+// by the workgroup.
 //
 // The kernel values are generated on the vector ALUs; their contraction with
 // the right-hand sides runs on the matrix cores, by v_mfma_f64_4x4x4f64: four independent 4 x 4 x 4 blocks per wave, lane
 // l = 16 s + 4 q + t supplying A[q][t][s], B[q][s][t] and receiving D[q][s][t].
-// A wave owns kGroups groups of 16 rows; in a group, block q covers rows
-// 4q..4q+3.  For each quad of staged columns (column s of the quad), lane l
+// A wave owns G groups of 16 rows; in a group, block q covers rows 4q..4q+3.  For each quad of staged columns (column s of the quad), lane l
 // evaluates Theta(row 4q + t, column s) on the vector ALUs; B[s][t] is
 // X[column s][right-hand side t] (two instructions cover 8 right-hand sides,
 // with no padding), and lane l ends with Y[row 4q + s][t].  The order of
 // summation over j is fixed (by quads, ascending), so results are
 // reproducible run to run.
-constexpr int kGroups = 2;                    // 16-row groups per wave
+//
+// A workgroup's wavefronts take SETS sets of 16 G rows; the SPLIT wavefronts of a
+// set share its columns, every SPLIT-th quad of a tile each, and their sums are
+// added at the end in wavefront order.  128 rows to a workgroup (G = 2, SETS = 4,
+// SPLIT = 1) read the columns least often, but leave most of the chip idle below
+// some 100,000 rows: 16 rows and 16 wavefronts up to 28,000 points (3,001 points
+// 134 -> 23 us, 9,001 398 -> 150 us), 32 rows and 4 wavefronts up to 150,000 (70,000
+// points, 8 right-hand sides 7.9 -> 5.8 ms, 100,000 in 3-D 16.4 -> 13.2 ms; at
+// 150,000 the two are equal, at 10^6 128 rows take 1.02 s, 32 rows 1.08 s).  With
+// 20 or more coordinates in registers the lines lie at 6,000 and 30,000 (20-D:
+// 9,001 points 500 us by 16 rows, 510 by 32, 981 by 128; 40,000 8.8, 7.0, 6.4 ms).
+// Reading a row's coordinates through the cache for every quad, as any d above 3
+// once did, took 7.1 ms and 42 ms there.  The split sums are the more accurate ones
+// (against 80-bit sums, 100,000 points in 3-D: 1.2e-14 of the norm by 128 rows,
+// 6.2e-15 by 32, 3.2e-15 by 16).
 constexpr int kMfmaRhs = 8;                   // right-hand sides per pass (two 4-wide blocks)
-constexpr int kMfmaRows = 4 * 16 * kGroups;   // rows per block (4 waves)
 constexpr int kMfmaLds = 65536;               // LDS bytes per block at most
 
-template <int TWONU, int D, int NB>
-__global__ __launch_bounds__(256) void dense_matvec_mfma(const double* __restrict__ x, int64_t n, int d,
+template <int TWONU, int D, int NB, int G, int SETS, int SPLIT>
+__global__ __launch_bounds__(SETS* SPLIT * 64) void dense_matvec_mfma(const double* __restrict__ x, int64_t n, int d,
                                                          double scale, const double* __restrict__ X, int ld,
                                                          int r0, int nr, double* __restrict__ Y, ExpTable et,
                                                          int tj) {
     extern __shared__ double tile[];  // kExpSize table entries, tj * d coordinates, tj * 8 values
     double* tab = tile;
     double* sx = tile + kExpSize;
-    double* sv = sx + size_t(tj) * d;
+    double* sv = sx + size_t(tj) * D;
     for (int q = threadIdx.x; q < kExpSize; q += blockDim.x) tab[q] = et.t[q];
-    // With coordinates in registers (D > 0) both sides are multiplied by `scale`
-    // as they are loaded, so the distance comes out as a = c r / l directly.
-    const double cs = D > 0 ? scale : 1.0;
+    // Coordinates are multiplied by `scale` as they are loaded, so the distance
+    // comes out as a = c r / l directly.
     double c6 = 1.0 / 6.0;
     asm volatile("" : "+v"(c6));  // kept in a vector register for the whole loop
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int t4 = lane & 3, q4 = (lane >> 2) & 3, s4 = lane >> 4;
-    const int64_t row_base = int64_t(blockIdx.x) * kMfmaRows + int64_t(wave) * 16 * kGroups;
-    int64_t ic[kGroups];
-    double xi[kGroups][D > 0 ? D : 1];
-    double acc[kGroups][NB];
+    constexpr int kThreads = SETS * SPLIT * 64;
+    const int set = wave / SPLIT, part = __builtin_amdgcn_readfirstlane(wave % SPLIT);
+    const int64_t row_base = (int64_t(blockIdx.x) * SETS + set) * 16 * G;
+    double xi[G][D];
+    double acc[G][NB];
 #pragma unroll
-    for (int g = 0; g < kGroups; ++g) {
+    for (int g = 0; g < G; ++g) {
         const int64_t i = row_base + g * 16 + 4 * q4 + t4;
-        ic[g] = i < n ? i : n - 1;
+        const int64_t ic = i < n ? i : n - 1;
 #pragma unroll
-        for (int t = 0; t < (D > 0 ? D : 1); ++t) xi[g][t] = D > 0 ? x[ic[g] * D + t] * cs : 0.0;
+        for (int t = 0; t < D; ++t) xi[g][t] = t < d ? x[ic * d + t] * scale : 0.0;
 #pragma unroll
         for (int b = 0; b < NB; ++b) acc[g][b] = 0.0;
     }
     for (int64_t j0 = 0; j0 < n; j0 += tj) {
         const int m = int(n - j0 < tj ? n - j0 : tj);
         const int mq = (m + 3) & ~3;  // whole quads; the padding columns carry zero weights
-        for (int q = threadIdx.x; q < mq * d; q += 256) sx[q] = q < m * d ? x[j0 * d + q] * cs : 0.0;
-        for (int q = threadIdx.x; q < mq * kMfmaRhs; q += 256) {
+        for (int q = threadIdx.x; q < mq * D; q += kThreads) {
+            const int jj = q / D, t = q % D;
+            sx[q] = jj < m && t < d ? x[(j0 + jj) * d + t] * scale : 0.0;
+        }
+        for (int q = threadIdx.x; q < mq * kMfmaRhs; q += kThreads) {
             const int jj = q >> 3, r = q & 7;
             sv[q] = (jj < m && r < nr) ? X[(j0 + jj) * ld + r0 + r] : 0.0;
         }
         __syncthreads();
-        for (int jq = 0; jq < mq; jq += 4) {
+        for (int jq = 4 * part; jq < mq; jq += 4 * SPLIT) {
             const int jj = jq + s4;
             double bv[NB];
 #pragma unroll
             for (int b = 0; b < NB; ++b) bv[b] = sv[jj * kMfmaRhs + 4 * b + t4];
 #pragma unroll
-            for (int g = 0; g < kGroups; ++g) {
+            for (int g = 0; g < G; ++g) {
                 // s starts at 1e-300 so that s = 0 (a point with itself) gives
                 // a = 1e-150 (the kernel is 1 to the last bit) instead of 0 * inf
                 double s = 1e-300;
-                if constexpr (D > 0) {
 #pragma unroll
-                    for (int t = 0; t < D; ++t) {
-                        const double df = xi[g][t] - sx[jj * D + t];
-                        s = __builtin_fma(df, df, s);
-                    }
-                } else {
-                    for (int t = 0; t < d; ++t) {
-                        const double df = x[ic[g] * d + t] - sx[jj * d + t];
-                        s = __builtin_fma(df, df, s);
-                    }
+                for (int t = 0; t < D; ++t) {
+                    const double df = xi[g][t] - sx[jj * D + t];
+                    s = __builtin_fma(df, df, s);
                 }
-                const double th = matern_fast<TWONU>(D > 0 ? sqrt_pos(s) : sqrt_pos(s) * scale, tab, c6);
+                const double th = matern_fast<TWONU>(sqrt_pos(s), tab, c6);
 #pragma unroll
                 for (int b = 0; b < NB; ++b) acc[g][b] = __builtin_amdgcn_mfma_f64_4x4x4f64(th, bv[b], acc[g][b], 0, 0, 0);
             }
         }
         __syncthreads();
     }
+    if constexpr (SPLIT > 1) {
+        double* sums = tile;  // [part][set][g][b][lane]; the last tile is done with
 #pragma unroll
-    for (int g = 0; g < kGroups; ++g) {
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) sums[(((part * SETS + set) * G + g) * NB + b) * 64 + lane] = acc[g][b];
+        __syncthreads();
+        if (part > 0) return;
+        for (int p = 1; p < SPLIT; ++p)
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+#pragma unroll
+                for (int b = 0; b < NB; ++b) acc[g][b] += sums[(((p * SETS + set) * G + g) * NB + b) * 64 + lane];
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
         const int64_t i = row_base + g * 16 + 4 * q4 + s4;
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
@@ -223,12 +246,19 @@ __global__ __launch_bounds__(kRows) void dot_partial(const double* __restrict__ 
     }
 }
 
-// out[r] = sum_b partial[b * nrhs + r], b ascending
-__global__ void dot_final(const double* __restrict__ partial, int nblocks, int nrhs, double* __restrict__ out) {
-    const int r = threadIdx.x;
-    if (r >= nrhs) return;
+// out[r] = sum_b partial[b * nrhs + r], b ascending, for the right-hand side of each
+// block.  The partial sums go through LDS: one load after another, each waited for
+// by the next addition, took 56 us.
+__global__ __launch_bounds__(kRows) void dot_final(const double* __restrict__ partial, int nrhs,
+                                                   double* __restrict__ out) {
+    __shared__ double p[kDotBlocks];
+    const int r = blockIdx.x;
+    for (int b = threadIdx.x; b < kDotBlocks; b += kRows) p[b] = partial[b * nrhs + r];
+    __syncthreads();
+    if (threadIdx.x > 0) return;
     double s = 0.0;
-    for (int b = 0; b < nblocks; ++b) s += partial[b * nrhs + r];
+#pragma unroll 16
+    for (int b = 0; b < kDotBlocks; ++b) s += p[b];
     out[r] = s;
 }
 
@@ -285,20 +315,34 @@ int twonu_of(double nu) {
     return 0;
 }
 
+template <int V>
+using Int = std::integral_constant<int, V>;
+
 template <int TWONU, int D>
 hipError_t launch_matvec_d(const double* x, int64_t n, int d, double scale, const double* X, int nrhs, double* Y,
                            hipStream_t s) {
     static const ExpTable et = make_exp_table();
     for (int r0 = 0; r0 < nrhs; r0 += kMfmaRhs) {
         const int nr = std::min(kMfmaRhs, nrhs - r0);
-        // column tile: a multiple of 4, at most kTileJ, with the LDS footprint within 64 KiB
-        const int tj = std::min(kTileJ, ((kMfmaLds / int(sizeof(double)) - kExpSize) / (d + kMfmaRhs)) & ~3);
-        const size_t lds = (kExpSize + size_t(tj) * (d + kMfmaRhs)) * sizeof(double);
-        const dim3 g(blocks_for(n, kMfmaRows));
-        if (nr <= 4)
-            dense_matvec_mfma<TWONU, D, 1><<<g, 256, lds, s>>>(x, n, d, scale, X, nrhs, r0, nr, Y, et, tj);
-        else
-            dense_matvec_mfma<TWONU, D, 2><<<g, 256, lds, s>>>(x, n, d, scale, X, nrhs, r0, nr, Y, et, tj);
+        auto go = [&](auto nb, auto gr, auto se, auto sp) {
+            constexpr int NB = decltype(nb)::value, G = decltype(gr)::value, SETS = decltype(se)::value,
+                          SPLIT = decltype(sp)::value;
+            // column tile: a multiple of 4, at most kTileJ (64 per wavefront of a split), with the LDS footprint
+            // within 64 KiB and at least the wavefronts' sums
+            const int most = ((kMfmaLds / int(sizeof(double)) - kExpSize) / (D + kMfmaRhs)) & ~3;
+            const int tj = std::min(std::max(kTileJ, 32 * SPLIT), most);
+            const size_t lds = std::max<size_t>(kExpSize + size_t(tj) * (D + kMfmaRhs),
+                                                SPLIT > 1 ? size_t(SPLIT) * SETS * G * NB * 64 : 0) * sizeof(double);
+            dense_matvec_mfma<TWONU, D, NB, G, SETS, SPLIT>
+                <<<blocks_for(n, SETS * G * 16), SETS * SPLIT * 64, lds, s>>>(x, n, d, scale, X, nrhs, r0, nr, Y, et, tj);
+        };
+        auto shape = [&](auto nb) {
+            if (n <= (D <= 8 ? 28000 : 6000)) go(nb, Int<1>(), Int<1>(), Int<16>());
+            else if (n <= (D <= 8 ? 150000 : 30000)) go(nb, Int<2>(), Int<1>(), Int<4>());
+            else go(nb, Int<2>(), Int<4>(), Int<1>());
+        };
+        if (nr <= 4) shape(Int<1>());
+        else shape(Int<2>());
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -312,8 +356,12 @@ hipError_t launch_matvec_t(const double* x, int64_t n, int d, double scale, cons
         case 1: return launch_matvec_d<TWONU, 1>(x, n, d, scale, X, nrhs, Y, s);
         case 2: return launch_matvec_d<TWONU, 2>(x, n, d, scale, X, nrhs, Y, s);
         case 3: return launch_matvec_d<TWONU, 3>(x, n, d, scale, X, nrhs, Y, s);
-        default: return launch_matvec_d<TWONU, 0>(x, n, d, scale, X, nrhs, Y, s);
+        default: break;
     }
+    // more coordinates: the next of three register counts
+    if (d <= 8) return launch_matvec_d<TWONU, 8>(x, n, d, scale, X, nrhs, Y, s);
+    if (d <= 20) return launch_matvec_d<TWONU, 20>(x, n, d, scale, X, nrhs, Y, s);
+    return launch_matvec_d<TWONU, 32>(x, n, d, scale, X, nrhs, Y, s);
 }
 
 hipError_t launch_matvec(int tn, const double* x, int64_t n, int d, double ell, const double* X, int nrhs, double* Y,
@@ -326,7 +374,7 @@ hipError_t launch_matvec(int tn, const double* x, int64_t n, int d, double ell, 
 hipError_t launch_dot(const double* A, const double* B, int64_t n, int nrhs, double* partial, double* out,
                       hipStream_t s) {
     dot_partial<<<kDotBlocks, kRows, 0, s>>>(A, B, n, nrhs, partial);
-    dot_final<<<1, 64, 0, s>>>(partial, kDotBlocks, nrhs, out);
+    dot_final<<<unsigned(nrhs), kRows, 0, s>>>(partial, nrhs, out);
     return hipGetLastError();
 }
 
