@@ -270,7 +270,7 @@ void kc_factor_destroy(kc_factor *f);
 
 /* Schedule of the factorization.  Each DAG level runs as its own launch with
  * `wpb` wavefronts (1, 2 or 4) per workgroup (small levels with several
- * wavefronts to each 64 entries, whatever wpb), except that every run of
+ * wavefronts to each 64 entries, whatever wpb and order), except that every run of
  * consecutive levels with at most `persist_max` work units (64 entries of a
  * column each) runs as ONE persistent launch: a cooperative grid, resident as a
  * whole, whose wavefronts stride over each level's units with a grid-wide

@@ -58,6 +58,10 @@ struct kc_factor {
     std::vector<int64_t> boff[3];
     int32_t* fwd_rows = nullptr;
     int32_t* bwd_short = nullptr;
+    kc::SweepRow* fwd_desc = nullptr;   // fwd_rows and bwd_short with their pointers
+    kc::SweepRow* bwd_desc = nullptr;
+    kc::TeamUnit* team_units = nullptr; // units of the levels that may run by teams ...
+    std::vector<int64_t> team_off;      // ... where each level's start (nlevels + 1)
     kc::TopCol* bwd_top = nullptr;
     kc::BwdChunk* bwd_chunks = nullptr;
     int32_t* inst = nullptr;   // instance of each position (batches only)

@@ -137,6 +137,35 @@ __global__ __launch_bounds__(kBlock) void unit_walk_kernel(const Unit* __restric
 }
 
 // ---------------------------------------------------------------------------
+// The schedules with the rows' pointers (see SweepRow and TeamUnit).
+__global__ void fill_fwd_desc(const int32_t* __restrict__ rows, int64_t n, const int64_t* __restrict__ rowptr,
+                              const int64_t* __restrict__ rowend, const int32_t* __restrict__ perm,
+                              kc::SweepRow* __restrict__ out) {
+    const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (t >= n) return;
+    const int k = rows[t];
+    out[t] = kc::SweepRow{uint32_t(rowptr[k]), int32_t(rowend[k] - 1 - rowptr[k]), k, perm[k]};
+}
+
+__global__ void fill_bwd_desc(const int32_t* __restrict__ cols, int64_t n, const int64_t* __restrict__ colptr,
+                              const int32_t* __restrict__ perm, kc::SweepRow* __restrict__ out) {
+    const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (t >= n) return;
+    const int j = cols[t];
+    out[t] = kc::SweepRow{uint32_t(colptr[j] + 1), int32_t(colptr[j + 1] - colptr[j] - 1), j, perm[j]};
+}
+
+__global__ void fill_team_units(const Unit* __restrict__ units, int64_t n, const int64_t* __restrict__ colptr,
+                                const int64_t* __restrict__ rowptr, const int64_t* __restrict__ rowend,
+                                kc::TeamUnit* __restrict__ out) {
+    const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (t >= n) return;
+    const int j = units[t].col, first = units[t].first;
+    const int64_t left = colptr[j + 1] - colptr[j] - first;
+    out[t] = kc::TeamUnit{uint32_t(colptr[j] + first), int32_t(left < kWave ? left : kWave), uint32_t(rowptr[j]),
+                          int32_t(rowend[j] - 1 - rowptr[j]), j, first, 0, 0};
+}
+
 // Row windows.  L2 lines are 128 bytes, and with thousands of rows walked at
 // once a line is evicted before a lane comes back for its other half, so every
 // load below reads whole lines: 64 column-index gaps (16 bits each, 128 B) per
@@ -1266,10 +1295,31 @@ GroupSchedule group_schedule(const kc::Plan& p) {
     return gs;
 }
 
+// Which levels may run by teams (team.hip, which needs every row staged): at most 12 units per CU (360,000 grid points, FP64 with match masks: 34.3
+// ms with levels of up to 3,000 units by teams, 34.6 without any, 40.1 with up to
+// 4,000; 160,000 points without masks: 17.9 ms, 21.8 with up to 1,500, 18.4 with
+// all); and the bitmap of the level's last column small enough that two workgroups
+// share a CU (columns up to about 200,000).
+constexpr int64_t kTeamUnits = 12 * 256;
+constexpr size_t kTeamLds = 72 * 1024;
+
+// Units of each level that may, as offsets (a level that may not has none).
+std::vector<int64_t> team_offsets(const kc::Plan& p, size_t vt) {
+    std::vector<int32_t> last(size_t(p.nlevels), 0);
+    for (int64_t j = 0; j < p.n; ++j) last[size_t(p.level[size_t(j)])] = int32_t(j);
+    std::vector<int64_t> off(size_t(p.nlevels) + 1, 0);
+    for (int32_t v = 0; v < p.nlevels; ++v) {
+        const int64_t units = p.unit_off[size_t(v) + 1] - p.unit_off[size_t(v)];
+        const bool team = units <= kTeamUnits && kc::team_lds(int32_t(p.max_row), last[size_t(v)], vt) <= kTeamLds;
+        off[size_t(v) + 1] = off[size_t(v)] + (team ? units : 0);
+    }
+    return off;
+}
+
 struct Layout {
     size_t counters, xh, perm, colptr, rowidx, csc2csr, rowptr, rowend, colidx, cdelta, escptr, esc, L, Lcsc, diag,
         units, unit_off, bunits[2][3], boff[3], fwd, bshort,
-        blong, bchunks, inst, groups, gunits, total;
+        blong, bchunks, inst, groups, gunits, fdesc, bdesc, team, total;
 };
 
 Layout layout_of(const kc::Plan& p, const BwdSchedule& b, kc_prec prec, const GroupSchedule& gs = GroupSchedule()) {
@@ -1313,6 +1363,9 @@ Layout layout_of(const kc::Plan& p, const BwdSchedule& b, kc_prec prec, const Gr
     o.inst = take(p.ninst > 1 ? n * sizeof(int32_t) : 0);
     o.groups = take(prec == KC_MIXED ? gs.groups.size() * sizeof(kc::GroupDesc) : 0);
     o.gunits = take(prec == KC_MIXED ? gs.units.size() * sizeof(int2) : 0);
+    o.fdesc = take(n * sizeof(kc::SweepRow));
+    o.bdesc = take(b.shortc.size() * sizeof(kc::SweepRow));
+    o.team = take(size_t(team_offsets(p, vt).back()) * sizeof(kc::TeamUnit));
     o.total = at;
     return o;
 }
@@ -1594,19 +1647,10 @@ kc_status launch_mask(const kc_factor* f, const IcholArgs<VT>& a, int64_t ub, in
     return launch_wpb<C, VT, false>(f, a, ub, ue, l0, l1, maxu, persistent, s);
 }
 
-// Whether level v (`units` 64-entry units) runs by teams (team.hip): every row
-// staged; at most 12 units per CU (360,000 grid points, FP64 with match masks: 34.3
-// ms with levels of up to 3,000 units by teams, 34.6 without any, 40.1 with up to
-// 4,000; 160,000 points without masks: 17.9 ms, 21.8 with up to 1,500, 18.4 with
-// all); and the bitmap of the level's last column small enough that two workgroups
-// share a CU (columns up to about 200,000).
-constexpr int64_t kTeamUnitsPerCu = 12;
-constexpr size_t kTeamLds = 72 * 1024;
-
+// Whether level v (`units` 64-entry units) runs by teams.
 template <typename VT>
 bool team_level(const kc_factor* f, int v, int64_t units) {
-    return f->max_row <= f->stage_max && units <= kTeamUnitsPerCu * std::max(1, f->num_cu) &&
-           kc::team_lds(f->max_row, f->level_last[size_t(v)], sizeof(VT)) <= kTeamLds;
+    return f->max_row <= f->stage_max && units > 0 && f->team_off[size_t(v) + 1] - f->team_off[size_t(v)] == units;
 }
 
 struct NoAfter {
@@ -1631,7 +1675,7 @@ kc_status launch_levels(const kc_factor* f, bool cnt, int pol, double tau, hipSt
         if (cnt_v > f->persist_max) {
             kc_status st = KC_OK;
             if (team_level<VT>(f, v, cnt_v))
-                KC_HIP(kc::launch_team<VT>(f, cnt, pol, tau, f->boff[0][v], f->boff[0][v + 1], f->level_last[v], s));
+                KC_HIP(kc::launch_team<VT>(f, cnt, pol, tau, v, s));
             else
                 st = go(bo[v], bo[v + 1], v, v + 1, bo[v + 1] - bo[v], false);
             if (st == KC_OK) st = after(v, v + 1);
@@ -1809,14 +1853,13 @@ kc_status factorize_forward(const kc_factor* f, int pol, double tau, const doubl
     const size_t nl = f->unit_off.size() - 1;
     const int64_t share = int64_t(std::max(1, f->num_cu)) * (nrhs <= 4 ? 4 : 2);
     for (size_t v = 0; v <= nl; ++v) {
-        const int64_t ub = v < nl ? f->boff[0][v] : 0, ue = v < nl ? f->boff[0][v + 1] : 0;
+        const int64_t units = v < nl ? f->unit_off[v + 1] - f->unit_off[v] : 0;
         const int64_t rb = v > 0 ? f->fwd_off[v - 1] : 0, re = v > 0 ? f->fwd_off[v] : 0;
-        const int32_t last = v < nl ? f->level_last[v] : 0;
-        if (re - rb < kWideRows && ue - ub <= share) {
-            KC_HIP(kc::launch_team_fwd<VT>(f, pol, tau, ub, ue, last, b, y, nrhs, rb, re, s));
+        if (re - rb < kWideRows && units <= share) {
+            KC_HIP(kc::launch_team_fwd<VT>(f, pol, tau, int(v), b, y, nrhs, rb, re, s));
             continue;
         }
-        KC_HIP(kc::launch_team<VT>(f, false, pol, tau, ub, ue, last, s));
+        if (v < nl) KC_HIP(kc::launch_team<VT>(f, false, pol, tau, int(v), s));
         const kc_status st = for_passes(nrhs, [&](auto w, int r0) -> kc_status {
             KC_HIP(kc::launch_fwd<VT>(f, b, nrhs, r0, decltype(w)::value, y, rb, re, s));
             return KC_OK;
@@ -2215,6 +2258,10 @@ kc_status kc_factor_create(const kc_plan* plan, kc_prec prec, void* ws_dev, size
     f->bwd_short = reinterpret_cast<int32_t*>(base + o.bshort);
     f->bwd_top = reinterpret_cast<kc::TopCol*>(base + o.blong);
     f->bwd_chunks = reinterpret_cast<kc::BwdChunk*>(base + o.bchunks);
+    f->fwd_desc = reinterpret_cast<kc::SweepRow*>(base + o.fdesc);
+    f->bwd_desc = reinterpret_cast<kc::SweepRow*>(base + o.bdesc);
+    f->team_units = reinterpret_cast<kc::TeamUnit*>(base + o.team);
+    f->team_off = team_offsets(p, vt);
     f->inst = p.ninst > 1 ? reinterpret_cast<int32_t*>(base + o.inst) : nullptr;
     f->ninst = p.ninst;
     f->unit_off = p.unit_off;
@@ -2288,6 +2335,29 @@ kc_status kc_factor_create(const kc_plan* plan, kc_prec prec, void* ws_dev, size
         KC_HIP(hipMemcpyAsync(f->groups, gs.groups.data(), gs.groups.size() * sizeof(kc::GroupDesc),
                               hipMemcpyHostToDevice, s));
         KC_HIP(hipMemcpyAsync(f->gunits, gs.units.data(), gs.units.size() * sizeof(int2), hipMemcpyHostToDevice, s));
+    }
+    // the schedules once more with the rows' pointers beside them, from what was uploaded
+    const unsigned nb = grid_for(p.n, kBlock);
+    fill_fwd_desc<<<nb, kBlock, 0, s>>>(f->fwd_rows, p.n, f->rowptr, f->rowend, f->perm, f->fwd_desc);
+    KC_LAUNCH_CHECK();
+    if (!bs.shortc.empty()) {
+        const int64_t ns = int64_t(bs.shortc.size());
+        fill_bwd_desc<<<grid_for(ns, kBlock), kBlock, 0, s>>>(f->bwd_short, ns, f->colptr, f->perm, f->bwd_desc);
+        KC_LAUNCH_CHECK();
+    }
+    for (int32_t v = 0, w; v < p.nlevels; v = w) {  // each run of consecutive levels that may run by teams
+        const auto team = [&](int32_t l) {
+            return f->team_off[size_t(l) + 1] - f->team_off[size_t(l)] == f->unit_off[size_t(l) + 1] - f->unit_off[size_t(l)];
+        };
+        w = v + 1;
+        if (!team(v)) continue;
+        while (w < p.nlevels && team(w)) ++w;
+        const int64_t cnt = f->team_off[size_t(w)] - f->team_off[size_t(v)];
+        if (cnt <= 0) continue;
+        fill_team_units<<<grid_for(cnt, kBlock), kBlock, 0, s>>>(
+            f->bunits[KC_ORDER_SPATIAL][0] + f->boff[0][size_t(v)], cnt, f->colptr, f->rowptr, f->rowend,
+            f->team_units + f->team_off[size_t(v)]);
+        KC_LAUNCH_CHECK();
     }
     // the sources are pageable host memory owned by the plan and bs: wait for the copies
     KC_HIP(hipStreamSynchronize(s));

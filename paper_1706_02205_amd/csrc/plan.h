@@ -17,6 +17,25 @@ struct Unit {
 
 constexpr int kRowAlign = 64;
 
+// What a kernel needs to know of a sweep's row, and of a team's unit, in the order
+// of the schedule: one load instead of a chain of two or three (the schedule, then
+// the row's pointers).  Filled on the device when a factor is created.
+struct alignas(16) SweepRow {
+    uint32_t p0;    // first entry: of the row without its diagonal (forward), of the column below it (backward)
+    int32_t n;      // entries
+    int32_t k;      // position
+    int32_t perm;   // original index
+};
+struct alignas(32) TeamUnit {
+    uint32_t e0;    // the unit's first entry (CSC)
+    int32_t count;  // its entries, at most 64
+    uint32_t t0;    // row j's first entry (by rows)
+    int32_t np;     // row j's parents
+    int32_t j;
+    int32_t first;  // offset of e0 in column j
+    int32_t pad0, pad1;
+};
+
 // Backward solve: one piece of a column's dot product sum_k L_kj x_k over
 // entries [start, start + len) counted from the diagonal's successor ...
 struct BwdChunk {

@@ -33,8 +33,8 @@ __global__ __launch_bounds__(kThreads) void sweep_narrow(SweepArgs<VT> a, int64_
 // Rows of a large level, a wavefront each; every XCD takes one contiguous range.
 template <typename VT, int NR>
 __global__ __launch_bounds__(kThreads) void fwd_wide(SweepArgs<VT> a, int64_t beg, int64_t end) {
-    const int64_t t = beg + int64_t(xcd_block()) * (kThreads / 64) + threadIdx.x / 64;
-    if (t < end) wide_row<VT, NR>(a, __builtin_amdgcn_readfirstlane(a.rows[t]), NR, threadIdx.x % 64);
+    const int64_t t = beg + int64_t(xcd_block()) * (kThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    if (t < end) wide_row<VT, NR>(a, a.rows[t], NR, threadIdx.x % 64);
 }
 
 template <typename VT, bool FWD>
@@ -76,8 +76,7 @@ hipError_t launch_fwd(const kc_factor* f, const double* b, int ld, int r0, int n
 template <typename VT>
 hipError_t launch_bwd_narrow(const kc_factor* f, double* x, int ld, int r0, int nr, double* y, int64_t cb, int64_t ce,
                              hipStream_t s) {
-    const SweepArgs<VT> a{f->bwd_short, f->colptr, nullptr, f->rowidx, static_cast<const VT*>(f->Lcsc), f->diag,
-                          f->perm, nullptr, x, y, ld, r0};
+    const SweepArgs<VT> a{f->bwd_desc, f->rowidx, static_cast<const VT*>(f->Lcsc), f->diag, nullptr, x, y, ld, r0};
     return launch<VT, false>(a, nr, cb, ce, s);
 }
 

@@ -100,16 +100,14 @@ __device__ __forceinline__ double wave_dot(const int32_t* __restrict__ idx, cons
 
 constexpr int kMaxRhs = 8;  // right-hand sides of one pass over L
 
-// What the two sweeps differ in: the row's entries [p0, p1) of idx and val, its
-// diagonal entry, where the right-hand side comes from and where x goes.
+// What the two sweeps differ in: the rows' entries, where the right-hand side
+// comes from and where x goes.
 template <typename VT>
 struct SweepArgs {
-    const int32_t* rows;
-    const int64_t *ptr, *end;  // forward: rowptr, rowend; backward: colptr
+    const kc::SweepRow* rows;
     const int32_t* idx;
     const VT* val;
     const double* diag;
-    const int32_t* perm;
     const double* b;  // forward: right-hand side, original order
     double* x;        // backward: solution, original order
     double* y;
@@ -118,18 +116,18 @@ struct SweepArgs {
 
 template <typename VT>
 SweepArgs<VT> fwd_args(const kc_factor* f, const double* b, int ld, int r0, double* y) {
-    return {f->fwd_rows, f->rowptr, f->rowend, f->colidx, static_cast<const VT*>(f->L), f->diag, f->perm, b, nullptr,
-            y, ld, r0};
+    return {f->fwd_desc, f->colidx, static_cast<const VT*>(f->L), f->diag, b, nullptr, y, ld, r0};
 }
 
 // One row of a wide forward level by a wavefront.
 template <typename VT, int NR>
-__device__ __forceinline__ void wide_row(const SweepArgs<VT>& a, int k, int nr, int lane) {
-    const int64_t p0 = a.ptr[k], pd = a.end[k] - 1;  // pd: the diagonal
+__device__ __forceinline__ void wide_row(const SweepArgs<VT>& a, const kc::SweepRow row, int nr, int lane) {
+    const int k = row.k;
+    const int64_t p0 = row.p0, pd = p0 + row.n;  // pd: the diagonal
     const double v = wave_dot<VT, NR>(a.idx, a.val, p0, pd, a.y, a.ld, a.r0, nr, lane);
     if (lane < nr) {
         const double lkk = diag_value(a.val, a.diag, pd, k);
-        const double acc = a.b[int64_t(a.perm[k]) * a.ld + a.r0 + lane] - v;
+        const double acc = a.b[int64_t(row.perm) * a.ld + a.r0 + lane] - v;
         a.y[int64_t(k) * a.ld + a.r0 + lane] = (lkk == 0.0) ? 0.0 : acc / lkk;
     }
 }
@@ -139,16 +137,14 @@ __device__ __forceinline__ void wide_row(const SweepArgs<VT>& a, int k, int nr, 
 // negated).  Entries past the row's end are staged as -0 and +0: fma(-0, +0, acc)
 // changes no acc, so the result is the sequential substitution's bit for bit.
 template <typename VT, int NR, int THREADS, bool FWD>
-__device__ __forceinline__ void sweep_row(const SweepArgs<VT>& a, int k, int nr, double* __restrict__ lds) {
+__device__ __forceinline__ void sweep_row(const SweepArgs<VT>& a, const kc::SweepRow row, int nr,
+                                          double* __restrict__ lds) {
     constexpr int kStride = THREADS + 2;  // rows of consecutive right-hand sides 4 banks apart
     const int tid = threadIdx.x;
     auto sL = [&](int buf) { return lds + buf * THREADS; };
     auto sY = [&](int buf) { return lds + 2 * THREADS + buf * NR * kStride; };
-    const int64_t q0 = a.ptr[k];
-    const int64_t p0 = FWD ? q0 : q0 + 1;
-    const int64_t p1 = FWD ? a.end[k] - 1 : a.ptr[k + 1];
-    const int64_t pd = FWD ? p1 : q0;  // the diagonal
-    const int n = int(p1 - p0);
+    const int k = row.k, n = row.n;
+    const int64_t p0 = row.p0, pd = FWD ? p0 + n : p0 - 1;  // pd: the diagonal
     int ci, cn;
     double lv, ln, v[NR];
     auto entries = [&](int at, int& c, double& l) {
@@ -173,7 +169,7 @@ __device__ __forceinline__ void sweep_row(const SweepArgs<VT>& a, int k, int nr,
     const bool chains = tid < 64 * ((NR + 3) / 4);  // whole wavefronts
     double acc = 0.0, lkk = 1.0;
     if (r < nr) {
-        acc = FWD ? a.b[int64_t(a.perm[k]) * a.ld + a.r0 + r] : a.y[int64_t(k) * a.ld + a.r0 + r];
+        acc = FWD ? a.b[int64_t(row.perm) * a.ld + a.r0 + r] : a.y[int64_t(k) * a.ld + a.r0 + r];
         lkk = diag_value(a.val, a.diag, pd, k);
     }
     if (n > 0) {
@@ -200,7 +196,7 @@ __device__ __forceinline__ void sweep_row(const SweepArgs<VT>& a, int k, int nr,
     if (r < nr && tid % kRowLanes == 0) {
         const double x = lkk == 0.0 ? 0.0 : acc / lkk;
         a.y[int64_t(k) * a.ld + a.r0 + r] = x;
-        if constexpr (!FWD) a.x[int64_t(a.perm[k]) * a.ld + a.r0 + r] = x;
+        if constexpr (!FWD) a.x[int64_t(row.perm) * a.ld + a.r0 + r] = x;
     }
 }
 

@@ -55,11 +55,10 @@ __host__ __device__ constexpr int map_words(int j) { return j / 32 + 1; }
 
 template <typename VT>
 struct TeamArgs {
-    const int64_t* colptr;
+    const kc::TeamUnit* units;  // of the level
     const int32_t* rowidx;
     const uint32_t* csc2csr;
     const int64_t* rowptr;
-    const int64_t* rowend;
     const int32_t* colidx;
     VT* Lv;
     VT* Lcsc;
@@ -105,8 +104,7 @@ __device__ __forceinline__ VT chain(const Pair<VT>* __restrict__ p, int n, VT ac
 // their order are those of ichol_level and L is bitwise the same.  The next
 // chunk's indices and values are on their way while the chains run.
 template <bool COUNT, typename VT, int EPW, int ENT>
-__device__ __forceinline__ void team_unit(const TeamArgs<VT>& a, const kc::Unit* __restrict__ bunits, int64_t ubeg,
-                                          int64_t uend, int cap, int block, unsigned char* smem) {
+__device__ __forceinline__ void team_unit(const TeamArgs<VT>& a, int cap, int block, unsigned char* smem) {
     constexpr int kWalkers = ENT / EPW;
     static_assert(kWalkers + 1 == kTeamThreads / kWave);
     constexpr int kParts = kUnit / ENT;  // workgroups per unit
@@ -114,23 +112,22 @@ __device__ __forceinline__ void team_unit(const TeamArgs<VT>& a, const kc::Unit*
     constexpr int kLoads = EPW / kAtOnce;
     __shared__ double piv;
     __shared__ int piv_zero;
-    const int64_t bu = ubeg + int64_t(block / kParts);
-    if (bu >= uend) return;  // the whole workgroup
+    const kc::TeamUnit un = a.units[block / kParts];
+    const int part = (block % kParts) * ENT;
+    if (part >= un.count) return;  // the whole workgroup: past the column's end
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int lane = threadIdx.x % kWave;
-    const int j = __builtin_amdgcn_readfirstlane(bunits[bu].col);
-    const int first = __builtin_amdgcn_readfirstlane(bunits[bu].first) + int(block % kParts) * ENT;
-    if (a.colptr[j] + first >= a.colptr[j + 1]) return;  // the whole workgroup: past the column's end
-    const int64_t t0 = a.rowptr[j];
-    const int np = int(a.rowend[j] - 1 - t0);
+    const int j = un.j, np = un.np, first = un.first + part;
+    const int64_t t0 = un.t0;
     VT* sval = reinterpret_cast<VT*>(smem);
     Pair<VT>* pairs = reinterpret_cast<Pair<VT>*>(smem + size_t(cap) * sizeof(VT));
     MapWord* map = reinterpret_cast<MapWord*>(smem + size_t(cap) * sizeof(VT) +
                                               sizeof(Pair<VT>) * size_t(ENT) * kPairStride<VT>);
 
     // this wavefront's entries, one per lane: entry e = (k, j), row k from rp, pos entries before (k, j)
-    const int64_t e = a.colptr[j] + first + wave * EPW + lane;
-    const bool mine = wave < kWalkers && lane < EPW && e < a.colptr[j + 1];
+    const int at = part + wave * EPW + lane;
+    const int64_t e = int64_t(un.e0) + at;
+    const bool mine = wave < kWalkers && lane < EPW && at < un.count;
     int k = j, pos = 0;
     uint32_t rp = 0, pend = 0;
     VT acc = VT(0);
@@ -252,10 +249,9 @@ __device__ __forceinline__ void team_unit(const TeamArgs<VT>& a, const kc::Unit*
 }
 
 template <bool COUNT, typename VT, int EPW, int ENT>
-__global__ __launch_bounds__(kTeamThreads) void ichol_team(TeamArgs<VT> a, const kc::Unit* __restrict__ bunits,
-                                                           int64_t ubeg, int64_t uend, int cap) {
+__global__ __launch_bounds__(kTeamThreads) void ichol_team(TeamArgs<VT> a, int cap) {
     extern __shared__ __align__(16) unsigned char smem[];
-    team_unit<COUNT, VT, EPW, ENT>(a, bunits, ubeg, uend, cap, blockIdx.x, smem);
+    team_unit<COUNT, VT, EPW, ENT>(a, cap, blockIdx.x, smem);
 }
 
 // A level of the factorization and, in the workgroups from nteam on, a level of
@@ -263,12 +259,10 @@ __global__ __launch_bounds__(kTeamThreads) void ichol_team(TeamArgs<VT> a, const
 // right-hand sides.  The sweep's level is an earlier one than the factorization's,
 // so neither reads what the other writes.
 template <typename VT, int EPW, int ENT, int NR>
-__global__ __launch_bounds__(kTeamThreads) void ichol_team_fwd(TeamArgs<VT> a, const kc::Unit* __restrict__ bunits,
-                                                               int64_t ubeg, int64_t uend, int cap, int nteam,
-                                                               SweepArgs<VT> sw, int nrhs, int64_t rbeg, int rows) {
+__global__ __launch_bounds__(kTeamThreads) void ichol_team_fwd(TeamArgs<VT> a, int cap, int nteam, SweepArgs<VT> sw, int nrhs, int64_t rbeg, int rows) {
     extern __shared__ __align__(16) unsigned char smem[];
     if (int(blockIdx.x) < nteam) {
-        team_unit<false, VT, EPW, ENT>(a, bunits, ubeg, uend, cap, blockIdx.x, smem);
+        team_unit<false, VT, EPW, ENT>(a, cap, blockIdx.x, smem);
         return;
     }
     const int block = int(blockIdx.x) - nteam;
@@ -283,8 +277,8 @@ template <int V>
 using Int = std::integral_constant<int, V>;
 
 template <typename VT>
-TeamArgs<VT> team_args(const kc_factor* f, int policy, double tau) {
-    return {f->colptr, f->rowidx, f->csc2csr, f->rowptr, f->rowend, f->colidx,
+TeamArgs<VT> team_args(const kc_factor* f, int level, int policy, double tau) {
+    return {f->team_units + f->team_off[size_t(level)], f->rowidx, f->csc2csr, f->rowptr, f->colidx,
             static_cast<VT*>(f->L), static_cast<VT*>(f->Lcsc), f->diag, policy, tau,
             f->counters + kNonpos, f->counters + kShifted, f->counters + kUpdates, f->counters + kNonfinite};
 }
@@ -319,39 +313,41 @@ size_t team_lds(int32_t max_row, int32_t max_col, size_t vt) {
 }
 
 template <typename VT>
-hipError_t launch_team(const kc_factor* f, bool count, int policy, double tau, int64_t ub, int64_t ue,
-                       int32_t max_col, hipStream_t s) {
-    if (ue <= ub) return hipSuccess;
-    const TeamArgs<VT> a = team_args<VT>(f, policy, tau);
-    const size_t lds = team_lds(f->max_row, max_col, sizeof(VT));
+hipError_t launch_team(const kc_factor* f, bool count, int policy, double tau, int level, hipStream_t s) {
+    const int64_t units = f->team_off[size_t(level) + 1] - f->team_off[size_t(level)];
+    if (units <= 0) return hipSuccess;
+    const TeamArgs<VT> a = team_args<VT>(f, level, policy, tau);
+    const size_t lds = team_lds(f->max_row, f->level_last[size_t(level)], sizeof(VT));
     const int32_t cap = team_cap(f->max_row);
-    team_shape(f, ue - ub, [&](auto epw, auto ent) {
+    team_shape(f, units, [&](auto epw, auto ent) {
         constexpr int EPW = decltype(epw)::value, ENT = decltype(ent)::value;
-        const unsigned grid = unsigned(ue - ub) * (kUnit / ENT);
-        if (count) ichol_team<true, VT, EPW, ENT><<<grid, kTeamThreads, lds, s>>>(a, f->bunits[f->order][0], ub, ue, cap);
-        else ichol_team<false, VT, EPW, ENT><<<grid, kTeamThreads, lds, s>>>(a, f->bunits[f->order][0], ub, ue, cap);
+        const unsigned grid = unsigned(units) * (kUnit / ENT);
+        if (count) ichol_team<true, VT, EPW, ENT><<<grid, kTeamThreads, lds, s>>>(a, cap);
+        else ichol_team<false, VT, EPW, ENT><<<grid, kTeamThreads, lds, s>>>(a, cap);
     });
     return hipGetLastError();
 }
 
 template <typename VT>
-hipError_t launch_team_fwd(const kc_factor* f, int policy, double tau, int64_t ub, int64_t ue, int32_t max_col,
-                           const double* b, double* y, int nrhs, int64_t rb, int64_t re, hipStream_t s) {
+hipError_t launch_team_fwd(const kc_factor* f, int policy, double tau, int level, const double* b, double* y, int nrhs,
+                           int64_t rb, int64_t re, hipStream_t s) {
+    const int nl = int(f->team_off.size()) - 1;
     const int64_t rows = re - rb;
-    if (ue <= ub && rows <= 0) return hipSuccess;
-    const TeamArgs<VT> a = team_args<VT>(f, policy, tau);
+    const int64_t units = level < nl ? f->team_off[size_t(level) + 1] - f->team_off[size_t(level)] : 0;
+    if (units <= 0 && rows <= 0) return hipSuccess;
+    const TeamArgs<VT> a = team_args<VT>(f, level, policy, tau);
     const SweepArgs<VT> sw = fwd_args<VT>(f, b, nrhs, 0, y);
     const int32_t cap = team_cap(f->max_row);
     const int64_t passes = (nrhs + kMaxRhs - 1) / kMaxRhs;
-    team_shape(f, ue - ub, [&](auto epw, auto ent) {
+    team_shape(f, units, [&](auto epw, auto ent) {
         constexpr int EPW = decltype(epw)::value, ENT = decltype(ent)::value;
-        const int nteam = int(ue - ub) * (kUnit / ENT);
+        const int nteam = int(units) * (kUnit / ENT);
         auto go = [&](auto w) {
             constexpr int NR = decltype(w)::value;
-            size_t lds = ue > ub ? team_lds(f->max_row, max_col, sizeof(VT)) : 0;
+            size_t lds = units > 0 ? team_lds(f->max_row, f->level_last[size_t(level)], sizeof(VT)) : 0;
             if (rows > 0) lds = std::max(lds, sweep_lds(NR, kTeamThreads) * sizeof(double));
             ichol_team_fwd<VT, EPW, ENT, NR><<<unsigned(nteam) + unsigned(rows * passes), kTeamThreads, lds, s>>>(
-                a, f->bunits[f->order][0], ub, ue, cap, nteam, sw, nrhs, rb, int(std::max<int64_t>(rows, 1)));
+                a, cap, nteam, sw, nrhs, rb, int(std::max<int64_t>(rows, 1)));
         };
         if (nrhs == 1) go(Int<1>());
         else if (nrhs == 2) go(Int<2>());
@@ -361,13 +357,11 @@ hipError_t launch_team_fwd(const kc_factor* f, int policy, double tau, int64_t u
     return hipGetLastError();
 }
 
-template hipError_t launch_team_fwd<double>(const kc_factor*, int, double, int64_t, int64_t, int32_t, const double*,
-                                            double*, int, int64_t, int64_t, hipStream_t);
-template hipError_t launch_team_fwd<float>(const kc_factor*, int, double, int64_t, int64_t, int32_t, const double*,
-                                           double*, int, int64_t, int64_t, hipStream_t);
-template hipError_t launch_team<double>(const kc_factor*, bool, int, double, int64_t, int64_t, int32_t,
-                                         hipStream_t);
-template hipError_t launch_team<float>(const kc_factor*, bool, int, double, int64_t, int64_t, int32_t,
-                                         hipStream_t);
+template hipError_t launch_team_fwd<double>(const kc_factor*, int, double, int, const double*, double*, int, int64_t,
+                                             int64_t, hipStream_t);
+template hipError_t launch_team_fwd<float>(const kc_factor*, int, double, int, const double*, double*, int, int64_t,
+                                             int64_t, hipStream_t);
+template hipError_t launch_team<double>(const kc_factor*, bool, int, double, int, hipStream_t);
+template hipError_t launch_team<float>(const kc_factor*, bool, int, double, int, hipStream_t);
 
 }  // namespace kc
