@@ -14,9 +14,8 @@
 // greedy maximin ordering and exactly S_rho:
 //   dist(a,b) = sqrt(sum_t (a_t - b_t)^2), summed over t ascending, no fma;
 //   (a,b) in S  <=>  dist <= rho * l.
-// Tree pruning uses a box lower bound evaluated with the same operation
-// sequence; rounding is monotone, so the bound never exceeds the distance of
-// any point in the box and no candidate is lost.
+// Tree pruning compares squared box distances with a slack of 1e-12, far above
+// what their order of summation can change, so no candidate is lost.
 //
 // Compiled with -ffp-contract=off.
 #include <algorithm>
@@ -179,24 +178,32 @@ struct KDTree {
         return id;
     }
 
-    // Lower bound on dist(q, y) for y in the node's box, same operation order as dist().
-    double boxdist(int32_t node, const double* q) const {
+    // Whether the node's box lies beyond r of q, given r2 >= r^2 (1 + 1e-12): the
+    // squares are summed four at a time, in whatever order that gives; the slack
+    // covers the rounding, so no point within r is lost.
+    bool box_beyond(int32_t node, const double* q, double r2) const {
         const double* L = &lo[size_t(node) * d];
         const double* H = &hi[size_t(node) * d];
-        double s = 0.0;
-        for (int t = 0; t < d; ++t) {
-            double g = 0.0;
-            if (q[t] < L[t]) g = L[t] - q[t];
-            else if (q[t] > H[t]) g = q[t] - H[t];
-            s += g * g;
+        double s[4] = {0.0, 0.0, 0.0, 0.0};
+        int t = 0;
+        for (; t + 4 <= d; t += 4) {
+            for (int u = 0; u < 4; ++u) {
+                const double g = std::max(std::max(L[t + u] - q[t + u], q[t + u] - H[t + u]), 0.0);
+                s[u] += g * g;
+            }
+            if (t == 4 && (s[0] + s[1]) + (s[2] + s[3]) > r2) return true;
         }
-        return std::sqrt(s);
+        for (; t < d; ++t) {
+            const double g = std::max(std::max(L[t] - q[t], q[t] - H[t]), 0.0);
+            s[0] += g * g;
+        }
+        return (s[0] + s[1]) + (s[2] + s[3]) > r2;
     }
 
-    // Calls leaf(begin, end) for every leaf that may hold a point within r of q and
+    // Calls leaf(begin, end) for every leaf that may hold a point within r of q (r2 >= r^2 (1 + 1e-12)) and
     // whose id range intersects [idlo, idhi].
     template <class F>
-    void visit(const double* q, double r, int32_t idlo, int32_t idhi, F&& leaf) const {
+    void visit(const double* q, double r2, int32_t idlo, int32_t idhi, F&& leaf) const {
         int32_t stack[128];
         int sp = 0;
         stack[sp++] = 0;
@@ -204,7 +211,7 @@ struct KDTree {
             const Node& nd = nodes[stack[--sp]];
             if (nd.maxid < idlo || nd.minid > idhi) continue;
             int32_t id = int32_t(&nd - nodes.data());
-            if (boxdist(id, q) > r) continue;
+            if (box_beyond(id, q, r2)) continue;
             if (nd.left < 0) {
                 leaf(nd.begin, nd.end);
             } else {
@@ -223,7 +230,8 @@ struct KDTree {
     // the maximum of their children.
     template <class F>
     double relax(int32_t id, const double* q, std::vector<double>& ub, F& leaf) const {
-        if (!(boxdist(id, q) < ub[size_t(id)])) return ub[size_t(id)];
+        const double bound = ub[size_t(id)];
+        if (!(bound > 0.0) || box_beyond(id, q, bound * bound * (1.0 + 1e-12))) return bound;
         const Node& nd = nodes[size_t(id)];
         const double u = nd.left < 0 ? leaf(nd.begin, nd.end)
                                      : std::max(relax(nd.left, q, ub, leaf), relax(nd.right, q, ub, leaf));
@@ -231,6 +239,52 @@ struct KDTree {
         return u;
     }
 };
+
+// An upper bound on every s with sqrt(s) <= R after rounding.
+inline double r2_bound(double R) { return R * R * (1.0 + 1e-12) + 1e-300; }
+
+// Squared distances of a leaf's m <= kBlock points from q, the canonical sum of
+// each: dimension after dimension for all points at once, which the compiler turns
+// into vector code (x is dimension-major).  Returns whether some point is still at
+// most R2; the sums only grow, so a leaf whose sums all exceed it is left early.
+constexpr int kBlock = 32;
+inline bool leaf_squares(const double* __restrict__ x, int stride, int m, const double* __restrict__ q, int d,
+                         double R2, double* __restrict__ s) {
+    for (int p = 0; p < m; ++p) s[p] = 0.0;
+    for (int t0 = 0; t0 < d; t0 += 4) {
+        const int t1 = std::min(d, t0 + 4);
+        for (int t = t0; t < t1; ++t) {
+            const double* xt = x + size_t(t) * size_t(stride);
+            const double qt = q[t];
+            for (int p = 0; p < m; ++p) {
+                const double df = xt[p] - qt;
+                s[p] += df * df;
+            }
+        }
+        double least = s[0];
+        for (int p = 1; p < m; ++p) least = std::min(least, s[p]);
+        if (least > R2) return false;
+    }
+    return true;
+}
+
+// The tree's points, each leaf's dimension-major: point t of leaf [b, e) has
+// coordinate c at xt[b d + c (e - b) + t - b].
+std::vector<double> leaf_major(const KDTree& tree, const double* x, int nthreads) {
+    const int d = tree.d;
+    std::vector<double> xt(tree.idx.size() * size_t(d));
+    parallel_for(nthreads, int64_t(tree.nodes.size()), 1 << 10, [&](int64_t a0, int64_t a1, int) {
+        for (int64_t a = a0; a < a1; ++a) {
+            const KDTree::Node& nd = tree.nodes[size_t(a)];
+            if (nd.left >= 0) continue;
+            double* to = xt.data() + size_t(nd.begin) * d;
+            for (int32_t t = nd.begin; t < nd.end; ++t)
+                for (int c = 0; c < d; ++c)
+                    to[size_t(c) * size_t(nd.end - nd.begin) + size_t(t - nd.begin)] = x[size_t(tree.idx[size_t(t)]) * d + c];
+        }
+    });
+    return xt;
+}
 
 // Indexed 4-ary max-heap on (key descending, id ascending), keys stored inline:
 // a level of a sift reads one 64-byte group of children instead of chasing ids
@@ -548,7 +602,8 @@ void maximin_order(const double* x, int64_t n, int32_t d, int nthreads, int32_t*
 
 namespace {
 
-void csr_from_csc(Plan& p, int nthreads) {
+// `sorted`: each column's rows are in order; else they are put in order here (one thread).
+void csr_from_csc(Plan& p, int nthreads, bool sorted = true) {
     // Rows start on multiples of kRowAlign entries and are padded with INT32_MAX.
     // Threads own balanced ranges of columns; a row's entries from thread t are
     // placed after those of threads t' < t, so rows stay sorted by column.
@@ -601,6 +656,15 @@ void csr_from_csc(Plan& p, int nthreads) {
                 }
         }
     });
+    if (!sorted) {  // the rows, in order, handed back to their columns
+        std::vector<int64_t> fill(p.colptr.begin(), p.colptr.end() - 1);
+        for (int64_t k = 0; k < n; ++k)
+            for (int64_t q = p.rowptr[k]; q < p.rowend[k]; ++q) {
+                const int64_t e = fill[size_t(p.colidx[size_t(q)])]++;
+                p.rowidx[size_t(e)] = int32_t(k);
+                p.csc2csr[size_t(e)] = uint32_t(q);
+            }
+    }
     encode_row_deltas(p, nthreads);
 }
 
@@ -621,7 +685,25 @@ inline bool within(const double* a, const double* b, int d, double R, double R2)
     return std::sqrt(s) <= R;
 }
 
-inline double r2_bound(double R) { return R * R * (1.0 + 1e-12) + 1e-300; }
+// Calls hit(id) for every point of the tree with id in [idlo, idhi] and dist(q, x) <= R
+// (the canonical expression); xt holds each leaf's points dimension-major.
+template <class F>
+void each_within(const KDTree& tree, const std::vector<double>& xt, const double* q, double R, int32_t idlo, int32_t idhi,
+            F&& hit) {
+    const int d = tree.d;
+    const double R2 = r2_bound(R);
+    double s[kBlock];
+    tree.visit(q, R2, idlo, idhi, [&](int32_t b, int32_t e) {
+        for (int32_t p0 = b; p0 < e; p0 += kBlock) {
+            const int m = std::min<int>(kBlock, e - p0);
+            if (!leaf_squares(xt.data() + size_t(b) * d + (p0 - b), e - b, m, q, d, R2, s)) continue;
+            for (int p = 0; p < m; ++p) {
+                const int32_t id = tree.idx[size_t(p0 + p)];
+                if (s[p] <= R2 && id >= idlo && id <= idhi && std::sqrt(s[p]) <= R) hit(id);
+            }
+        }
+    });
+}
 
 // Runs scan(i, buf) for i in [0, n) on parallel chunks; scan appends item i's
 // values to buf.  The values are concatenated in order of i into vals, with
@@ -709,42 +791,27 @@ void build_pattern(Plan& p, int nthreads) {
     KDTree tree;
     tree.build(xh, n, d, nthreads);
     p.spatial = tree.idx;  // k-d tree leaf order: positions grouped by region
-    // points copied into tree order, so that scanning a leaf reads contiguous memory
-    const std::vector<int32_t>& idt = tree.idx;
-    std::vector<double> xt(size_t(n) * d);
-    parallel_for(nthreads, n, 1 << 14, [&](int64_t t0, int64_t t1, int) {
-        for (int64_t t = t0; t < t1; ++t)
-            std::copy(xh + size_t(idt[size_t(t)]) * d, xh + size_t(idt[size_t(t)] + 1) * d, xt.begin() + size_t(t) * d);
-    });
-
+    const std::vector<double> xt = leaf_major(tree, xh, nthreads);
+    // One thread leaves the columns as the leaves come and gets their rows in order
+    // from the two transpositions below, which costs less than sorting each column
+    // (8,009 points in R^20: 38 ms of sorts); several threads sort at once.
+    const bool sorted = nthreads > 1 || p.rule != KC_RULE_MAX;
     if (p.rule == KC_RULE_MAX) {
         // column b: the diagonal, then rows a > b with dist(x_a, x_b) <= rho * max(l_a, l_b) = rho * l_b
         collect(nthreads, n, [&](int64_t b, std::vector<int32_t>& out) {
-            const double* xb = xh + size_t(b) * d;
-            const double R = p.rho * p.l[size_t(b)], R2 = r2_bound(R);
             out.push_back(int32_t(b));
             const size_t first = out.size();
-            tree.visit(xb, R, int32_t(b + 1), int32_t(n - 1), [&](int32_t s, int32_t e) {
-                for (int32_t t = s; t < e; ++t) {
-                    const int32_t a = idt[size_t(t)];
-                    if (a > b && within(xt.data() + size_t(t) * d, xb, d, R, R2)) out.push_back(a);
-                }
-            });
-            std::sort(out.begin() + first, out.end());
+            each_within(tree, xt, xh + size_t(b) * d, p.rho * p.l[size_t(b)], int32_t(b + 1), int32_t(n - 1),
+                   [&](int32_t a) { out.push_back(a); });
+            if (sorted) std::sort(out.begin() + first, out.end());
         }, p.colptr, p.rowidx);
     } else {
         // row a: columns b < a with dist(x_a, x_b) <= rho * min(l_a, l_b) = rho * l_a
         std::vector<int64_t> rp;
         std::vector<int32_t> cols;
         collect(nthreads, n, [&](int64_t a, std::vector<int32_t>& out) {
-            const double* xa = xh + size_t(a) * d;
-            const double R = p.rho * p.l[size_t(a)], R2 = r2_bound(R);
-            tree.visit(xa, R, 0, int32_t(a - 1), [&](int32_t s, int32_t e) {
-                for (int32_t t = s; t < e; ++t) {
-                    const int32_t b = idt[size_t(t)];
-                    if (b < a && within(xa, xt.data() + size_t(t) * d, d, R, R2)) out.push_back(b);
-                }
-            });
+            each_within(tree, xt, xh + size_t(a) * d, p.rho * p.l[size_t(a)], 0, int32_t(a - 1),
+                   [&](int32_t b) { out.push_back(b); });
         }, rp, cols);
         // transpose rows into CSC columns (diagonal first, rows ascending)
         std::vector<int64_t> cnt(static_cast<size_t>(n), 1);
@@ -761,7 +828,7 @@ void build_pattern(Plan& p, int nthreads) {
     if (p.colptr[n] >= (int64_t(1) << 32)) return;  // caller reports KC_ERANGE
     p.max_col = 0;
     for (int64_t b = 0; b < n; ++b) p.max_col = std::max(p.max_col, p.colptr[b + 1] - p.colptr[b]);
-    csr_from_csc(p, nthreads);
+    csr_from_csc(p, nthreads, sorted);
 }
 
 void build_schedule(Plan& p, int nthreads) {
@@ -976,7 +1043,7 @@ void supernodal_transform(Plan& p, int nthreads) {
             node[size_t(k)] = s;
             const double R = 0.5 * p.rho * p.l[size_t(k)], R2 = r2_bound(R), lmin = 0.5 * p.l[size_t(k)];
             const double* xk = xh + size_t(k) * d;
-            tree.visit(xk, R, int32_t(k + 1), int32_t(n - 1), [&](int32_t b, int32_t e) {
+            tree.visit(xk, R2, int32_t(k + 1), int32_t(n - 1), [&](int32_t b, int32_t e) {
                 for (int32_t t = b; t < e; ++t) {
                     const int32_t a = tree.idx[t];
                     if (a > k && node[size_t(a)] < 0 && p.l[size_t(a)] >= lmin && within(xh + size_t(a) * d, xk, d, R, R2))
