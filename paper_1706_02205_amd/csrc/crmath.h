@@ -174,11 +174,27 @@ __device__ __forceinline__ double cr_exp(double x, int& hard) {
 }
 
 // Euclidean distance, coordinates summed in ascending order without fusion
-// (the library is compiled with -ffp-contract=off).
+// (the library is compiled with -ffp-contract=off).  Past three coordinates they
+// are requested four at a time: the loop of one load, then its use, waited for
+// memory d times over.
 __device__ __forceinline__ double dist(const double* __restrict__ a, const double* __restrict__ b, int d) {
     double s = 0.0;
-    for (int t = 0; t < d; ++t) {
-        double df = a[t] - b[t];
+    int t = 0;
+    for (; t + 4 <= d; t += 4) {
+        double x[4], y[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            x[u] = a[t + u];
+            y[u] = b[t + u];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const double df = x[u] - y[u];
+            s = s + df * df;
+        }
+    }
+    for (; t < d; ++t) {
+        const double df = a[t] - b[t];
         s = s + df * df;
     }
     return __builtin_sqrt(s);
