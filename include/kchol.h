@@ -197,10 +197,12 @@ kc_status kc_solve_bytes(const kc_factor *f, int32_t nrhs, size_t *bytes);
  * solution component 0.  Requires a completed kc_factorize on the same factor.
  * Forward levels of fewer than 1024 rows and the backward sweep over short
  * columns follow the sequential substitution (bitwise); larger forward levels
- * sum each row across a wavefront, and when a column has more than 2048
- * off-diagonal entries, the columns up to the last such one are summed in
- * fixed pieces combined in a fixed order (deterministic, not bitwise the
- * sequential order). */
+ * sum each row across a wavefront.  When a column has more than 2048
+ * off-diagonal entries, the columns up to the last such one are summed in fixed
+ * pieces combined in a fixed order, and later ones of more than 256 entries
+ * across a workgroup unless the factorization shifted a pivot or left an entry
+ * that is not finite (deterministic, not bitwise the sequential order; in a
+ * batch the columns are told apart by instance). */
 kc_status kc_solve(const kc_factor *f, const double *b_dev, double *x_dev, int32_t nrhs, void *scratch_dev,
                    size_t scratch_bytes, void *stream);
 

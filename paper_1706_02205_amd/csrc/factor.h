@@ -13,6 +13,7 @@
 namespace kc::counter {
 enum Counter {
     kNonpos = 0, kShifted = 1, kUpdates = 2, kExpHard = 3, kNonfinite = 4, kMatchErr = 5, kMatchTotal = 6,
+    kUnsound = 7,  // not a count: whether the factor has shifted pivots or entries that are not finite
     kNumCounters = 8
 };
 }
@@ -72,7 +73,7 @@ struct kc_factor {
     bool use_groups = false;
     int32_t ninst = 1;
     // host schedule
-    std::vector<int64_t> unit_off, fwd_off, short_off, top_off, tchunk_off;
+    std::vector<int64_t> unit_off, fwd_off, short_off, short_sum, top_off, tchunk_off;
     std::vector<int32_t> level_last;  // last column of each level
     int64_t nfine = 0;        // pieces of the top columns' rows below the top block (first in bwd_chunks)
     int64_t max_slots = 0;    // partial sums the backward sweep needs at once

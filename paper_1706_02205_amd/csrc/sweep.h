@@ -11,9 +11,11 @@ namespace kc {
 template <typename VT>
 hipError_t launch_fwd(const kc_factor* f, const double* b, int ld, int r0, int nr, double* y, int64_t rb,
                              int64_t re, hipStream_t s);
-// Columns [cb, ce) of bwd_short: x = (y - L^T x) / L_jj, into y and (original order) x.
+// Columns [cb, ce) of bwd_short: x = (y - L^T x) / L_jj, into y and (original order)
+// x.  Those before cm are summed across a workgroup if the factor is sound, the
+// others in sequence.
 template <typename VT>
 hipError_t launch_bwd_narrow(const kc_factor* f, double* x, int ld, int r0, int nr, double* y, int64_t cb, int64_t ce,
-                             hipStream_t s);
+                             int64_t cm, hipStream_t s);
 
 }  // namespace kc

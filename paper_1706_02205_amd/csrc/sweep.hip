@@ -24,10 +24,18 @@ namespace {
 
 constexpr int kThreads = 256;
 
+// The first nsum rows are columns summed across the workgroup (backward only, sound factors).
 template <typename VT, int NR, bool FWD>
-__global__ __launch_bounds__(kThreads) void sweep_narrow(SweepArgs<VT> a, int64_t beg) {
+__global__ __launch_bounds__(kThreads) void sweep_narrow(SweepArgs<VT> a, int64_t beg, int nsum) {
     __shared__ __align__(16) double lds[sweep_lds(NR, kThreads)];
-    sweep_row<VT, NR, kThreads, FWD>(a, a.rows[beg + int64_t(blockIdx.x)], NR, lds);
+    const kc::SweepRow row = a.rows[beg + int64_t(blockIdx.x)];
+    if constexpr (!FWD) {
+        if (int(blockIdx.x) < nsum && *a.unsound == 0) {
+            sum_column<VT, NR>(a, row, lds);
+            return;
+        }
+    }
+    sweep_row<VT, NR, kThreads, FWD>(a, row, NR, lds);
 }
 
 // Rows of a large level, a wavefront each; every XCD takes one contiguous range.
@@ -38,7 +46,7 @@ __global__ __launch_bounds__(kThreads) void fwd_wide(SweepArgs<VT> a, int64_t be
 }
 
 template <typename VT, bool FWD>
-hipError_t launch(const SweepArgs<VT>& a, int nr, int64_t beg, int64_t end, hipStream_t s) {
+hipError_t launch(const SweepArgs<VT>& a, int nr, int64_t beg, int64_t end, int64_t sums, hipStream_t s) {
     if (end <= beg) return hipSuccess;
     auto go = [&](auto w) {
         constexpr int NR = decltype(w)::value;
@@ -48,7 +56,7 @@ hipError_t launch(const SweepArgs<VT>& a, int nr, int64_t beg, int64_t end, hipS
                 return;
             }
         }
-        sweep_narrow<VT, NR, FWD><<<unsigned(end - beg), kThreads, 0, s>>>(a, beg);
+        sweep_narrow<VT, NR, FWD><<<unsigned(end - beg), kThreads, 0, s>>>(a, beg, int(sums - beg));
     };
     switch (nr) {
         case 1: go(std::integral_constant<int, 1>()); break;
@@ -70,14 +78,15 @@ namespace kc {
 template <typename VT>
 hipError_t launch_fwd(const kc_factor* f, const double* b, int ld, int r0, int nr, double* y, int64_t rb,
                              int64_t re, hipStream_t s) {
-    return launch<VT, true>(fwd_args<VT>(f, b, ld, r0, y), nr, rb, re, s);
+    return launch<VT, true>(fwd_args<VT>(f, b, ld, r0, y), nr, rb, re, rb, s);
 }
 
 template <typename VT>
 hipError_t launch_bwd_narrow(const kc_factor* f, double* x, int ld, int r0, int nr, double* y, int64_t cb, int64_t ce,
-                             hipStream_t s) {
-    const SweepArgs<VT> a{f->bwd_desc, f->rowidx, static_cast<const VT*>(f->Lcsc), f->diag, nullptr, x, y, ld, r0};
-    return launch<VT, false>(a, nr, cb, ce, s);
+                             int64_t cm, hipStream_t s) {
+    const SweepArgs<VT> a{f->bwd_desc, f->rowidx, static_cast<const VT*>(f->Lcsc), f->diag, nullptr, x, y, ld, r0,
+                          f->counters + counter::kUnsound};
+    return launch<VT, false>(a, nr, cb, ce, cm, s);
 }
 
 template hipError_t launch_fwd<double>(const kc_factor*, const double*, int, int, int, double*, int64_t, int64_t,
@@ -85,8 +94,8 @@ template hipError_t launch_fwd<double>(const kc_factor*, const double*, int, int
 template hipError_t launch_fwd<float>(const kc_factor*, const double*, int, int, int, double*, int64_t, int64_t,
                                              hipStream_t);
 template hipError_t launch_bwd_narrow<double>(const kc_factor*, double*, int, int, int, double*, int64_t, int64_t,
-                                              hipStream_t);
+                                              int64_t, hipStream_t);
 template hipError_t launch_bwd_narrow<float>(const kc_factor*, double*, int, int, int, double*, int64_t, int64_t,
-                                             hipStream_t);
+                                             int64_t, hipStream_t);
 
 }  // namespace kc

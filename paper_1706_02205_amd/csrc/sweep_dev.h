@@ -112,11 +112,12 @@ struct SweepArgs {
     double* x;        // backward: solution, original order
     double* y;
     int ld, r0;
+    const unsigned long long* unsound;  // backward: not 0 where every column keeps the sequential order
 };
 
 template <typename VT>
 SweepArgs<VT> fwd_args(const kc_factor* f, const double* b, int ld, int r0, double* y) {
-    return {f->fwd_desc, f->colidx, static_cast<const VT*>(f->L), f->diag, b, nullptr, y, ld, r0};
+    return {f->fwd_desc, f->colidx, static_cast<const VT*>(f->L), f->diag, b, nullptr, y, ld, r0, nullptr};
 }
 
 // One row of a wide forward level by a wavefront.
@@ -197,6 +198,46 @@ __device__ __forceinline__ void sweep_row(const SweepArgs<VT>& a, const kc::Swee
         const double x = lkk == 0.0 ? 0.0 : acc / lkk;
         a.y[int64_t(k) * a.ld + a.r0 + r] = x;
         if constexpr (!FWD) a.x[int64_t(row.perm) * a.ld + a.r0 + r] = x;
+    }
+}
+
+// One backward column by a workgroup of 256: its threads take every 256th entry,
+// each wavefront reduces by a fixed butterfly, and the wavefronts' sums are added in
+// order.  Deterministic, but not the sequential substitution's order.
+template <typename VT, int NR>
+__device__ __forceinline__ void sum_column(const SweepArgs<VT>& a, const kc::SweepRow row, double* __restrict__ lds) {
+    constexpr int kThreads = 256, kWaves = kThreads / 64;
+    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+    const int64_t p0 = row.p0;
+    double* yk = a.y + int64_t(row.k) * a.ld + a.r0 + lane;
+    double own = 0.0, lkk = 1.0;
+    if (wave == 0 && lane < NR) {
+        own = *yk;
+        lkk = diag_value(a.val, a.diag, p0 - 1, row.k);
+    }
+    double s[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) s[r] = 0.0;
+    dot_entries<VT, NR, kThreads>(a.idx, a.val, p0 + threadIdx.x, p0 + row.n, a.y, a.ld, a.r0, s);
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) s[r] += __shfl_xor(s[r], off, 64);
+    if (lane < NR) {
+        double v = s[0];
+#pragma unroll
+        for (int r = 1; r < NR; ++r)
+            if (lane == r) v = s[r];
+        lds[wave * NR + lane] = v;
+    }
+    __syncthreads();
+    if (wave == 0 && lane < NR) {
+        double v = lds[lane];
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w) v += lds[w * NR + lane];
+        const double x = lkk == 0.0 ? 0.0 : (own - v) / lkk;
+        *yk = x;
+        a.x[int64_t(row.perm) * a.ld + a.r0 + lane] = x;
     }
 }
 

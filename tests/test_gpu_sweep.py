@@ -41,3 +41,40 @@ def test_every_row_length_bitwise(K, n, nrhs):
         out = g.launch()
         f.solve(bd)
         assert np.array_equal(out.cpu().numpy(), ref)
+
+
+# A plan with columns of more than 2,048 entries: later columns of more than 256 are summed across a workgroup, within
+# 1e-12 of the largest component; after shifted pivots (here nearly all) every column at or above the top block keeps the
+# sequential order, so that overflow leaves the same infinities and NaN as a level-by-level solve of the same factor.
+@pytest.mark.parametrize("prec,nrhs", [("fp64", 1), ("fp64", 9), ("mixed", 4)])
+def test_summed_columns(K, prec, nrhs):
+    import torch
+    import oracle as O
+    from paper_1706_02205_amd import workloads as W
+    n = 6000
+    x = W.uniform_points(n, 2, 31)
+    plan = K.analyze(x, 6.0)
+    _, _, colptr, _ = plan.export()
+    cols = np.diff(colptr) - 1
+    top = int(np.nonzero(cols > 2048)[0].max()) + 1
+    assert ((cols > 256) & (np.arange(n) >= top)).any()
+    xd = torch.from_numpy(x).cuda()
+    b = W.gaussian_rhs(n, nrhs, 32)
+    bd = torch.from_numpy(b).cuda()
+    f = K.Factor(plan, prec)
+    f.factorize(xd, 0.5, 0.3)
+    P = O.pattern(x, 6.0)
+    ref = O.solve(P, f.export_L(), b)
+    got = f.solve(bd).cpu().numpy()
+    assert np.abs(got - ref).max() <= 1e-12 * np.abs(ref).max()
+    assert np.array_equal(f.factorize_solve(xd, bd, 0.5, 0.3).cpu().numpy(), got)
+    # the note of unsound factors: shifted pivots, then a sound factorization again
+    f.factorize(xd, 0.5, 0.3, "shift", 0.5)
+    assert f.stats().shifted > 0
+    a = f.solve(bd).cpu().numpy()
+    ref = O.solve(P, f.export_L(), b)
+    fine = np.isfinite(ref).all()
+    assert not fine or np.abs(a - ref).max() <= 1e-12 * np.abs(ref).max()
+    f.theta(xd, 0.5, 0.3)
+    assert np.array_equal(f.solve(bd).cpu().numpy(), a, equal_nan=True)
+    assert np.array_equal(f.factorize_solve(xd, bd, 0.5, 0.3).cpu().numpy(), got)
