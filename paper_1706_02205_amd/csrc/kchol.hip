@@ -655,7 +655,11 @@ __device__ __forceinline__ int stage_values(const IcholArgs<VT>& a, int j, VT* s
 // match, and for each set bit of mk takes the next set bit of mj to find L_ji in
 // the staged row -- the same updates in the same order as the index merge, from
 // one bit per walked entry instead of a 16-bit index gap.  A value piece with
-// no set bit is not loaded.  Every loop is bounded by the masks' lengths and
+// no set bit is not loaded.  Bound by memory: the pieces of one factorization are
+// 142 GB of L2 misses at 360,000 grid points in FP64, read at 4.3 TB/s in 33.2 ms,
+// and a level walks a row once if at all, so nothing is shared (the next piece
+// requested ahead, in 107 registers instead of 71: 34.7 -> 37.0 ms where that left
+// enough wavefronts, 38.9 in every level).  Every loop is bounded by the masks' lengths and
 // every read checked against them, so inconsistent masks are counted
 // (kMatchErr), never followed outside row j or the mask buffer.
 template <bool COUNT, typename VT, bool STAGED>
@@ -1318,11 +1322,12 @@ GroupSchedule group_schedule(const kc::Plan& p) {
     return gs;
 }
 
-// Which levels may run by teams (team.hip, which needs every row staged): at most 12 units per CU (360,000 grid points, FP64 with match masks: 34.3
-// ms with levels of up to 3,000 units by teams, 34.6 without any, 40.1 with up to
-// 4,000; 160,000 points without masks: 17.9 ms, 21.8 with up to 1,500, 18.4 with
-// all); and the bitmap of the level's last column small enough that two workgroups
-// share a CU (columns up to about 200,000).
+// Which levels may run by teams (team.hip, which needs every row staged): at most
+// 12 units per CU (360,000 grid points, FP64 with match masks: 34.3 ms with levels
+// of up to 3,000 units by teams, 34.6 without any, 40.1 with up to 4,000; 160,000
+// points without masks: 17.9 ms, 21.8 with up to 1,500, 18.4 with all); and the
+// bitmap of the level's last column small enough that two workgroups share a CU
+// (columns up to about 200,000).
 constexpr int64_t kTeamUnits = 12 * 256;
 constexpr size_t kTeamLds = 72 * 1024;
 
@@ -1795,7 +1800,7 @@ kc_status bwd_levels(const kc_factor* f, double* x, int ld, int r0, double* y, d
         const bool narrow = se - sb <= kNarrowCols;
         if (narrow || sm > sb)
             KC_HIP(kc::launch_bwd_narrow<VT>(f, x, ld, r0, NR, y, sb, narrow ? se : sm, sm, s));
-        if (!narrow) {
+        if (!narrow && se > sm) {
             bwd_solve<VT, NR><<<grid_for(se - sm, kWavesPerBlock), kBlock, 0, s>>>(
                 f->bwd_short, sm, se, f->colptr, f->rowidx, Lc, f->diag, f->perm, ld, r0, y, x);
             KC_LAUNCH_CHECK();

@@ -10,7 +10,9 @@
 // the first (and, past four right-hand sides, the second) runs the previous
 // block's chains, 16 lanes to a right-hand side (row_chain.h).  Measured, a whole
 // solve: 2,000 points 1.33 -> 0.94 ms, 20,011 in 3-D 5.6 -> 3.9 ms, 90,601 grid
-// points with 8 right-hand sides 6.8 -> 4.8 ms, 160,000 with one 5.9 -> 4.3 ms.
+// points with 8 right-hand sides 6.8 -> 4.8 ms, 160,000 with one 5.9 -> 4.3 ms; with the
+// schedules' row pointers and long columns summed across a workgroup 0.72, 3.15,
+// 3.8 and 3.6 ms.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
