@@ -585,8 +585,8 @@ def main():
             "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                          "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
                          "measured_copy_GBps": copy_gbs, "frac_of_copy": achieved / copy_gbs,
-                         "kernel": ("ichol_level (Theta fused, match masks)" if r["match"] else
-                                    "ichol_level (Theta fused, index merge)") + ", one launch per DAG level",
+                         "kernel": ("ichol_level (match masks)" if r["match"] else
+                                    "ichol_level (index merge)") + ", one launch per DAG level, after one of theta_kernel",
                          "launches_per_factorization": launches,
                          "algorithmic_bytes_per_launch": B / launches,
                          "avg_launch_ms": tf / launches * 1e3},
