@@ -14,8 +14,8 @@
 // greedy maximin ordering and exactly S_rho:
 //   dist(a,b) = sqrt(sum_t (a_t - b_t)^2), summed over t ascending, no fma;
 //   (a,b) in S  <=>  dist <= rho * l.
-// Tree pruning compares squared box distances with a slack of 1e-12, far above
-// what their order of summation can change, so no candidate is lost.
+// Tree pruning compares squared box distances with a slack above what their order
+// of summation can change (square_slack), so no candidate is lost.
 //
 // Compiled with -ffp-contract=off.
 #include <algorithm>
@@ -72,6 +72,11 @@ inline double dist(const double* a, const double* b, int d) {
     }
     return std::sqrt(s);
 }
+
+// What two sums of the same d squares, in different orders, can differ by, as a
+// factor: each is off by at most (d + 2) 2^-53 relative.  The 1e-12 leaves room
+// for the roots and for squaring a radius.
+inline double square_slack(int d) { return 1.0 + 1e-12 + double(d) * 0x1p-52; }
 
 // k-d tree over n points (ids 0..n-1 index the point array).
 struct KDTree {
@@ -178,7 +183,7 @@ struct KDTree {
         return id;
     }
 
-    // Whether the node's box lies beyond r of q, given r2 >= r^2 (1 + 1e-12): the
+    // Whether the node's box lies beyond r of q, given r2 >= r^2 square_slack(d): the
     // squares are summed four at a time, in whatever order that gives; the slack
     // covers the rounding, so no point within r is lost.
     bool box_beyond(int32_t node, const double* q, double r2) const {
@@ -200,7 +205,7 @@ struct KDTree {
         return (s[0] + s[1]) + (s[2] + s[3]) > r2;
     }
 
-    // Calls leaf(begin, end) for every leaf that may hold a point within r of q (r2 >= r^2 (1 + 1e-12)) and
+    // Calls leaf(begin, end) for every leaf that may hold a point within r of q (r2 >= r^2 square_slack(d)) and
     // whose id range intersects [idlo, idhi].
     template <class F>
     void visit(const double* q, double r2, int32_t idlo, int32_t idhi, F&& leaf) const {
@@ -231,7 +236,7 @@ struct KDTree {
     template <class F>
     double relax(int32_t id, const double* q, std::vector<double>& ub, F& leaf) const {
         const double bound = ub[size_t(id)];
-        if (!(bound > 0.0) || box_beyond(id, q, bound * bound * (1.0 + 1e-12))) return bound;
+        if (!(bound > 0.0) || box_beyond(id, q, bound * bound * square_slack(d))) return bound;
         const Node& nd = nodes[size_t(id)];
         const double u = nd.left < 0 ? leaf(nd.begin, nd.end)
                                      : std::max(relax(nd.left, q, ub, leaf), relax(nd.right, q, ub, leaf));
@@ -241,7 +246,7 @@ struct KDTree {
 };
 
 // An upper bound on every s with sqrt(s) <= R after rounding.
-inline double r2_bound(double R) { return R * R * (1.0 + 1e-12) + 1e-300; }
+inline double r2_bound(double R, int d) { return R * R * square_slack(d) + 1e-300; }
 
 // Squared distances of a leaf's m <= kBlock points from q, the canonical sum of
 // each: dimension after dimension for all points at once, which the compiler turns
@@ -691,7 +696,7 @@ template <class F>
 void each_within(const KDTree& tree, const std::vector<double>& xt, const double* q, double R, int32_t idlo, int32_t idhi,
             F&& hit) {
     const int d = tree.d;
-    const double R2 = r2_bound(R);
+    const double R2 = r2_bound(R, d);
     double s[kBlock];
     tree.visit(q, R2, idlo, idhi, [&](int32_t b, int32_t e) {
         for (int32_t p0 = b; p0 < e; p0 += kBlock) {
@@ -1041,7 +1046,7 @@ void supernodal_transform(Plan& p, int nthreads) {
             const int32_t s = int32_t(leader.size());
             leader.push_back(k);
             node[size_t(k)] = s;
-            const double R = 0.5 * p.rho * p.l[size_t(k)], R2 = r2_bound(R), lmin = 0.5 * p.l[size_t(k)];
+            const double R = 0.5 * p.rho * p.l[size_t(k)], R2 = r2_bound(R, d), lmin = 0.5 * p.l[size_t(k)];
             const double* xk = xh + size_t(k) * d;
             tree.visit(xk, R2, int32_t(k + 1), int32_t(n - 1), [&](int32_t b, int32_t e) {
                 for (int32_t t = b; t < e; ++t) {
