@@ -201,8 +201,9 @@ kc_status kc_solve_bytes(const kc_factor *f, int32_t nrhs, size_t *bytes);
  * off-diagonal entries, the columns up to the last such one are summed in fixed
  * pieces combined in a fixed order, and later ones of more than 256 entries
  * across a workgroup unless the factorization shifted a pivot or left an entry
- * that is not finite (deterministic, not bitwise the sequential order; in a
- * batch the columns are told apart by instance). */
+ * that is not finite (deterministic, not bitwise the sequential order).  In a
+ * batch all of this goes by instance: each one's solution is bitwise what it
+ * gets alone, as long as no merged forward level reaches 1024 rows. */
 kc_status kc_solve(const kc_factor *f, const double *b_dev, double *x_dev, int32_t nrhs, void *scratch_dev,
                    size_t scratch_bytes, void *stream);
 

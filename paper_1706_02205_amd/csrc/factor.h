@@ -9,13 +9,20 @@
 #include "kchol.h"
 #include "plan.h"
 
-// Device counters of a factor.
+// Device counters of a factor.  From kUnsound on, one per instance, not counts but
+// notes: whether the factorization shifted a pivot of the instance or left an entry
+// of it that is not finite.  A solve with such a factor can overflow, and which
+// components then come out as infinities and which as NaN depends on the order of
+// summation: its backward columns all keep the sequential one (see sum_column).
 namespace kc::counter {
 enum Counter {
     kNonpos = 0, kShifted = 1, kUpdates = 2, kExpHard = 3, kNonfinite = 4, kMatchErr = 5, kMatchTotal = 6,
-    kUnsound = 7,  // not a count: whether the factor has shifted pivots or entries that are not finite
-    kNumCounters = 8
+    kUnsound = 7
 };
+// Notes the instance of column j (inst: the instance of each column, or null for a single problem).
+__device__ __forceinline__ void note_unsound(unsigned long long* counters, const int32_t* inst, int j) {
+    counters[kUnsound + (inst ? inst[j] : 0)] = 1;
+}
 }
 
 struct kc_factor {

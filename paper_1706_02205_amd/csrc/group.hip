@@ -68,7 +68,8 @@ struct GroupArgs {
     float ell;
     int policy;
     double tau;
-    unsigned long long *nonpos, *shifted, *nonfinite;
+    unsigned long long* counters;
+    const int32_t* inst;
 };
 
 // The position of index i among the group's parents, or -1.
@@ -284,9 +285,12 @@ __global__ __launch_bounds__(kThreads) void ichol_group(GroupArgs a, const kc::G
                     zero = !(pd > 0.0);
                 } else if (!(pd > a.tau)) {
                     pd = a.tau;
-                    if (tile == 0) atomicAdd(a.shifted, 1ull);
+                    if (tile == 0) {
+                        atomicAdd(a.counters + kShifted, 1ull);
+                        note_unsound(a.counters, a.inst, g0);
+                    }
                 }
-                if (zero && tile == 0) atomicAdd(a.nonpos, 1ull);
+                if (zero && tile == 0) atomicAdd(a.counters + kNonpos, 1ull);
                 piv[g] = zero ? 0.0 : __builtin_sqrt(pd);
                 pzero[g] = zero;
             }
@@ -319,7 +323,10 @@ __global__ __launch_bounds__(kThreads) void ichol_group(GroupArgs a, const kc::G
         }
     }
     const unsigned long long nf = __ballot(bad);
-    if (nf && lane == 0) atomicAdd(a.nonfinite, (unsigned long long)__popcll(nf));
+    if (nf && lane == 0) {
+        atomicAdd(a.counters + kNonfinite, (unsigned long long)__popcll(nf));
+        note_unsound(a.counters, a.inst, g0);
+    }
 }
 
 // P_G by 256 parents where a level has at most a unit per CU: fewer steps of two
@@ -350,7 +357,7 @@ hipError_t launch_group(const kc_factor* f, int twonu, double ell, int policy, d
     if (ue <= ub) return hipSuccess;
     const GroupArgs a{f->colptr, f->rowidx, f->csc2csr, f->rowptr, f->rowend, f->colidx,
                       static_cast<float*>(f->L), static_cast<float*>(f->Lcsc), f->diag, f->xh, f->d, float(ell),
-                      policy, tau, f->counters + kNonpos, f->counters + kShifted, f->counters + kNonfinite};
+                      policy, tau, f->counters, f->inst};
     if (twonu == 1) return launch<1>(f, a, ub, ue, s);
     if (twonu == 3) return launch<3>(f, a, ub, ue, s);
     return launch<5>(f, a, ub, ue, s);

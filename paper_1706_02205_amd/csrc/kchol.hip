@@ -52,7 +52,7 @@ constexpr int kBlock = 256;                    // 4 wavefronts
 constexpr int kWavesPerBlock = kBlock / kWave;
 constexpr int64_t kLongColumn = 2048;          // backward solve: longer columns are reduced in pieces
 // Columns at or above the top block with more entries than this, where there is a
-// top block and the factor is sound (see note_unsound), are summed across a
+// top block and the instance's factor is sound (see kUnsound), are summed across a
 // workgroup: their sequential chains set the pace of the reverse levels (solve of
 // 20,011 points in 3-D 3.76 -> 3.15 ms, 90,601 grid points with 8 right-hand sides
 // 4.74 -> 3.80, 160,000 with one 4.14 -> 3.59; drawing the columns above 512
@@ -65,16 +65,8 @@ constexpr int64_t kBandRows = 32768;           // rows per band of those pieces 
 // ---------------------------------------------------------------------------
 // small kernels
 __global__ void zero_u64(unsigned long long* p, int n) {
-    int i = threadIdx.x;
+    const int i = int(blockIdx.x * blockDim.x + threadIdx.x);
     if (i < n) p[i] = 0ull;
-}
-
-// Notes whether the factorization shifted a pivot or left an entry that is not
-// finite.  A solve with such a factor can overflow, and which components then come
-// out as infinities and which as NaN depends on the order of summation: it keeps
-// the sequential one (see sum_column).
-__global__ void note_unsound(unsigned long long* counters) {
-    counters[kUnsound] = counters[kShifted] != 0 || counters[kNonfinite] != 0;
 }
 
 __global__ void gather_points(const double* __restrict__ x, const int32_t* __restrict__ perm, int64_t n, int d,
@@ -269,6 +261,7 @@ struct IcholArgs {
     int stage_max;  // rows with more parents are read from device memory, not staged
     int nbuck;  // 0: cursor merge; else buckets of the staged row's directory (a power of 2)
     unsigned long long* counters;
+    const int32_t* inst;
     // match masks (see match_masks_kernel), or null: per CSC entry a word offset and
     // walk end (mmeta), and the mask words (mwords, mwords_n of them)
     const uint64_t* mmeta;
@@ -630,10 +623,16 @@ __device__ __forceinline__ void factor_entries(const IcholArgs<VT>& a, int j, in
     }
     // entries of L that came out inf or NaN (e.g. after a tiny shifted pivot): one atomic per wave
     const unsigned long long nf = __ballot(bad);
-    if (nf && lane == 0) atomicAdd(counters + kNonfinite, (unsigned long long)__popcll(nf));
+    if (nf && lane == 0) {
+        atomicAdd(counters + kNonfinite, (unsigned long long)__popcll(nf));
+        note_unsound(counters, a.inst, j);
+    }
     if (first == 0 && lane == 0) {
         if (zero) atomicAdd(counters + kNonpos, 1ull);
-        if (shifted) atomicAdd(counters + kShifted, 1ull);
+        if (shifted) {
+            atomicAdd(counters + kShifted, 1ull);
+            note_unsound(counters, a.inst, j);
+        }
     }
     if (COUNT) {
         const unsigned long long tot = wave_sum(hits);
@@ -762,12 +761,18 @@ __device__ __forceinline__ void factor_entries_mask(const IcholArgs<VT>& a, int 
         bad = !__builtin_isfinite(out);
     }
     const unsigned long long nf = __ballot(bad);
-    if (nf && lane == 0) atomicAdd(counters + kNonfinite, (unsigned long long)__popcll(nf));
+    if (nf && lane == 0) {
+        atomicAdd(counters + kNonfinite, (unsigned long long)__popcll(nf));
+        note_unsound(counters, a.inst, j);
+    }
     const unsigned long long ni = __ballot(inconsistent);
     if (ni && lane == 0) atomicAdd(counters + kMatchErr, (unsigned long long)__popcll(ni));
     if (first == 0 && lane == 0) {
         if (zero) atomicAdd(counters + kNonpos, 1ull);
-        if (shifted) atomicAdd(counters + kShifted, 1ull);
+        if (shifted) {
+            atomicAdd(counters + kShifted, 1ull);
+            note_unsound(counters, a.inst, j);
+        }
     }
     if (COUNT) {
         const unsigned long long tot = wave_sum(hits);
@@ -1360,7 +1365,7 @@ Layout layout_of(const kc::Plan& p, const BwdSchedule& b, kc_prec prec, const Gr
     };
     const size_t n = size_t(p.n), nnz = size_t(p.nnz()), nnzr = size_t(p.nnz_rows());
     const size_t vt = prec == KC_FP64 ? sizeof(double) : sizeof(float);
-    o.counters = take(kNumCounters * sizeof(unsigned long long));
+    o.counters = take((size_t(kUnsound) + size_t(p.ninst)) * sizeof(unsigned long long));
     o.xh = take(n * p.d * sizeof(double));
     o.perm = take(n * sizeof(int32_t));
     o.colptr = take((n + 1) * sizeof(int64_t));
@@ -1623,6 +1628,7 @@ IcholArgs<VT> ichol_args(const kc_factor* f, int pol, double tau) {
     a.stage_max = f->stage_max;
     a.nbuck = f->nbuck;
     a.counters = f->counters;
+    a.inst = f->inst;
     a.mmeta = f->mmeta;
     a.mwords = f->mwords;
     a.mwords_n = f->mwords_n;
@@ -1747,19 +1753,11 @@ kc_status launch_theta(const kc_factor* f, int tn, double ell, const double* ell
     return KC_OK;
 }
 
-// What every factorization of a plan with a top block ends with.
-kc_status launch_end(const kc_factor* f, hipStream_t s) {
-    if (f->top_off.empty()) return KC_OK;
-    note_unsound<<<1, 1, 0, s>>>(f->counters);
-    KC_LAUNCH_CHECK();
-    return KC_OK;
-}
-
 // What every factorization starts with: counters cleared, the points in maximin
 // order, Theta on S in Lcsc.
 kc_status launch_start(const kc_factor* f, const double* x_dev, int tn, double ell, const double* ells,
                        hipStream_t s) {
-    zero_u64<<<1, 64, 0, s>>>(f->counters, kNumCounters);
+    zero_u64<<<grid_for(kUnsound + f->ninst, 64), 64, 0, s>>>(f->counters, kUnsound + f->ninst);
     KC_LAUNCH_CHECK();
     gather_points<<<grid_for(f->n * f->d, kBlock), kBlock, 0, s>>>(x_dev, f->perm, f->n, f->d, f->xh);
     KC_LAUNCH_CHECK();
@@ -1933,8 +1931,6 @@ template <typename VT>
 kc_status factorize_solve_typed(kc_factor* f, int pol, double tau, const double* b, double* x, int nrhs, double* y,
                                 double* partial, hipStream_t s) {
     auto backward = [&]() {
-        const kc_status ended = launch_end(f, s);
-        if (ended != KC_OK) return ended;
         return for_passes(nrhs, [&](auto w, int r0) {
             constexpr int NR = decltype(w)::value;
             return bwd_levels<VT, NR>(f, x, nrhs, r0, y, partial, s);
@@ -2433,7 +2429,6 @@ static kc_status factorize_impl(kc_factor* f, const double* x_dev, double nu, do
     st = groups_on(f, cnt)      ? launch_groups(f, tn, ell, int(pivot), tau, s)
          : f->prec == KC_FP64 ? launch_levels<double>(f, cnt, int(pivot), tau, s)
                               : launch_levels<float>(f, cnt, int(pivot), tau, s);
-    if (st == KC_OK) st = launch_end(f, s);
     if (st != KC_OK) return st;
     f->factorized = true;
     f->counted = cnt;
@@ -2470,7 +2465,7 @@ kc_status kc_theta(kc_factor* f, const double* x_dev, kc_kernel kernel, double* 
     const int tn = twonu_of(kernel.nu);
     if (!tn || !(kernel.lengthscale > 0.0)) return KC_EINVAL;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    zero_u64<<<1, 64, 0, s>>>(f->counters, kUnsound);  // the counts before it
+    zero_u64<<<1, 64, 0, s>>>(f->counters, kUnsound);  // the counts, not the notes
     KC_LAUNCH_CHECK();
     gather_points<<<grid_for(f->n * f->d, kBlock), kBlock, 0, s>>>(x_dev, f->perm, f->n, f->d, f->xh);
     KC_LAUNCH_CHECK();
@@ -2619,7 +2614,6 @@ kc_status kc_factorize_solve(kc_factor* f, const double* x_dev, kc_kernel kernel
     if (st != KC_OK) return st;
     if (groups_on(f, false)) {  // the group DAG has its own levels: factor, then both sweeps
         st = launch_groups(f, tn, kernel.lengthscale, int(pivot), tau, s);
-        if (st == KC_OK) st = launch_end(f, s);
         if (st == KC_OK) st = solve_typed<float>(f, b_dev, x_out, nrhs, y, partial, s);
     } else {
         st = f->prec == KC_FP64
@@ -2635,7 +2629,7 @@ kc_status kc_factorize_solve(kc_factor* f, const double* x_dev, kc_kernel kernel
 
 kc_status kc_factor_stats(kc_factor* f, kc_factor_stats_t* st) {
     if (!f || !st) return KC_EINVAL;
-    unsigned long long c[kNumCounters];
+    unsigned long long c[kUnsound];
     KC_HIP(hipStreamSynchronize(f->last));
     KC_HIP(hipMemcpy(c, f->counters, sizeof(c), hipMemcpyDeviceToHost));
     st->nonpositive = int64_t(c[kNonpos]);

@@ -26,13 +26,13 @@ namespace {
 
 constexpr int kThreads = 256;
 
-// The first nsum rows are columns summed across the workgroup (backward only, sound factors).
+// The first nsum rows are columns summed across the workgroup (backward only, instances with a sound factor).
 template <typename VT, int NR, bool FWD>
 __global__ __launch_bounds__(kThreads) void sweep_narrow(SweepArgs<VT> a, int64_t beg, int nsum) {
     __shared__ __align__(16) double lds[sweep_lds(NR, kThreads)];
     const kc::SweepRow row = a.rows[beg + int64_t(blockIdx.x)];
     if constexpr (!FWD) {
-        if (int(blockIdx.x) < nsum && *a.unsound == 0) {
+        if (int(blockIdx.x) < nsum && a.unsound[a.inst ? a.inst[row.k] : 0] == 0) {
             sum_column<VT, NR>(a, row, lds);
             return;
         }
@@ -87,7 +87,7 @@ template <typename VT>
 hipError_t launch_bwd_narrow(const kc_factor* f, double* x, int ld, int r0, int nr, double* y, int64_t cb, int64_t ce,
                              int64_t cm, hipStream_t s) {
     const SweepArgs<VT> a{f->bwd_desc, f->rowidx, static_cast<const VT*>(f->Lcsc), f->diag, nullptr, x, y, ld, r0,
-                          f->counters + counter::kUnsound};
+                          f->counters + counter::kUnsound, f->inst};
     return launch<VT, false>(a, nr, cb, ce, cm, s);
 }
 

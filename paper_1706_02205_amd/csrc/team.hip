@@ -65,7 +65,8 @@ struct TeamArgs {
     double* diag;
     int policy;
     double tau;
-    unsigned long long *nonpos, *shifted, *updates, *nonfinite;
+    unsigned long long* counters;
+    const int32_t* inst;
 };
 
 // acc <- fma(-a, b, acc) over n pairs (a multiple of 8) in ascending order, eight
@@ -218,8 +219,11 @@ __device__ __forceinline__ void team_unit(const TeamArgs<VT>& a, int cap, int bl
         if (lane == 0) {
             piv = zero ? 0.0 : __builtin_sqrt(dacc);
             piv_zero = zero;
-            if (first == 0 && zero) atomicAdd(a.nonpos, 1ull);
-            if (first == 0 && shift) atomicAdd(a.shifted, 1ull);
+            if (first == 0 && zero) atomicAdd(a.counters + kNonpos, 1ull);
+            if (first == 0 && shift) {
+                atomicAdd(a.counters + kShifted, 1ull);
+                note_unsound(a.counters, a.inst, j);
+            }
         }
         if (COUNT && first == 0)
             for (int t = lane; t < np; t += kWave) hits += sval[t] != VT(0);  // the pivot's own updates
@@ -240,11 +244,14 @@ __device__ __forceinline__ void team_unit(const TeamArgs<VT>& a, int cap, int bl
         bad = !__builtin_isfinite(out);
     }
     const unsigned long long nf = __ballot(bad);
-    if (nf && lane == 0) atomicAdd(a.nonfinite, (unsigned long long)__popcll(nf));
+    if (nf && lane == 0) {
+        atomicAdd(a.counters + kNonfinite, (unsigned long long)__popcll(nf));
+        note_unsound(a.counters, a.inst, j);
+    }
     if (COUNT) {
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) hits += __shfl_xor(hits, off, kWave);
-        if (lane == 0 && hits) atomicAdd(a.updates, hits);
+        if (lane == 0 && hits) atomicAdd(a.counters + kUpdates, hits);
     }
 }
 
@@ -280,7 +287,7 @@ template <typename VT>
 TeamArgs<VT> team_args(const kc_factor* f, int level, int policy, double tau) {
     return {f->team_units + f->team_off[size_t(level)], f->rowidx, f->csc2csr, f->rowptr, f->colidx,
             static_cast<VT*>(f->L), static_cast<VT*>(f->Lcsc), f->diag, policy, tau,
-            f->counters + kNonpos, f->counters + kShifted, f->counters + kUpdates, f->counters + kNonfinite};
+            f->counters, f->inst};
 }
 
 template <int V>

@@ -1,0 +1,58 @@
+"""Summed backward columns and factors with shifted pivots: such a factor keeps the sequential order, instance by instance."""
+import numpy as np
+import pytest
+
+import oracle as O
+from paper_1706_02205_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def K():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1706_02205_amd as K
+    return K
+
+
+def dev(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+# Three instances in every order, the one with lengthscale 5 shifting some 300 pivots, the other two none (their least
+# pivot is five times tau): each is solved bitwise as alone, by kc_solve, by the fused call and by a captured graph.
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("order", [(0, 1, 2), (2, 0, 1)])
+def test_instance_of_a_batch_with_shifted_pivots_elsewhere(K, prec, order):
+    nu, rho, tau = 0.5, 4.0, 1e-3
+    pts = [W.uniform_points(5000, 2, 4311), W.uniform_points(1200, 2, 4312), W.uniform_points(4000, 2, 4313)]
+    lens = np.array([0.05, 0.3, 5.0])
+    xs, ells = [pts[i] for i in order], lens[list(order)]
+    print(f"[gpu] batch of sound and unsound instances {prec} {order}", flush=True)
+    b = [W.gaussian_rhs(len(x), 3, 4500 + i) for i, x in enumerate(xs)]
+    plan = K.analyze_batched(xs, rho)
+    xd, ed, bd = dev(np.concatenate(xs)), dev(ells), dev(np.concatenate(b))
+    f = K.Factor(plan, prec)
+    f.factorize_batched(xd, nu, ed, "shift", tau)
+    got = f.solve(bd).cpu().numpy()
+    assert np.array_equal(f.factorize_solve(xd, bd, nu, pivot="shift", tau=tau, ell_dev=ed).cpu().numpy(), got)
+    g = f.capture(xd, bd, nu, ell_dev=ed, pivot="shift", tau=tau)
+    for _ in range(3):
+        out = g.launch()
+        f.solve(bd)
+        assert np.array_equal(out.cpu().numpy(), got)
+    o0 = 0
+    for i, (x, ell) in enumerate(zip(xs, ells)):
+        alone_plan = K.analyze(x, rho)
+        alone = K.Factor(alone_plan, prec)
+        alone.factorize(dev(x), nu, float(ell), "shift", tau)
+        assert (alone.stats().shifted > 0) == (ell == 5.0)
+        want = alone.solve(dev(b[i])).cpu().numpy()
+        if len(x) > 2049:  # with columns past the top block that a sound factor sums
+            cols = np.diff(alone_plan.export()[2]) - 1
+            assert ((cols > 256) & (np.arange(len(x)) > np.nonzero(cols > 2048)[0].max())).any()
+        assert np.array_equal(got[o0:o0 + len(x)], want), f"instance {i}"
+        o0 += len(x)
