@@ -56,3 +56,39 @@ def test_instance_of_a_batch_with_shifted_pivots_elsewhere(K, prec, order):
             assert ((cols > 256) & (np.arange(len(x)) > np.nonzero(cols > 2048)[0].max())).any()
         assert np.array_equal(got[o0:o0 + len(x)], want), f"instance {i}"
         o0 += len(x)
+
+
+# Positions past the last long column see no summed piece but these columns, so there the sequential order shows bit for
+# bit: finite after shifted pivots; overflowing, with the oracle's infinities and NaN at their places; and not so for a
+# sound factor, which sums.
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("n,d,rho,nu,ell,tau,kind", [(6000, 2, 6.0, 0.5, 0.3, 0.5, "shifted"),
+                                                     (4000, 3, 3.0, 2.5, 0.2, 1e-9, "overflowing"),
+                                                     (6000, 2, 6.0, 0.5, 0.3, 1e-9, "sound")])
+def test_order_past_the_top_block(K, prec, n, d, rho, nu, ell, tau, kind):
+    print(f"[gpu] order past the top block: {kind} {prec}", flush=True)
+    x = W.uniform_points(n, d, 31)
+    plan = K.analyze(x, rho)
+    perm, _, colptr, _ = plan.export()
+    cols = np.diff(colptr) - 1
+    top = int(np.nonzero(cols > 2048)[0].max()) + 1
+    assert ((cols > 256) & (np.arange(n) >= top)).any()
+    assert np.bincount(plan.levels()).max() < 1024  # no forward level is summed
+    b = W.gaussian_rhs(n, 2, 32)
+    f = K.Factor(plan, prec)
+    f.factorize(dev(x), nu, ell, "shift", tau)
+    st = f.stats()
+    ref = O.solve(O.pattern(x, rho), f.export_L(), b)[perm[top:]]
+    got = f.solve(dev(b)).cpu().numpy()[perm[top:]]
+    if kind == "sound":
+        assert st.shifted == 0 and st.nonfinite == 0
+        assert not np.array_equal(got, ref) and np.abs(got - ref).max() <= 1e-12 * np.abs(ref).max()
+        return
+    assert st.shifted > 0
+    assert np.array_equal(got, ref, equal_nan=True)
+    if kind == "overflowing":
+        assert np.isnan(ref).any() and np.isinf(ref).any()
+        if prec == "fp64":
+            assert np.isfinite(ref).any()
+    else:
+        assert np.isfinite(ref).all()
