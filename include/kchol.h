@@ -272,8 +272,8 @@ kc_status kc_factor_export_L(const kc_factor *f, double *vals);
 void kc_factor_destroy(kc_factor *f);
 
 /* Schedule of the factorization.  Each DAG level runs as its own launch with
- * `wpb` wavefronts (1, 2 or 4) per workgroup (small levels with several
- * wavefronts to each 64 entries, whatever wpb and order), except that every run of
+ * `wpb` wavefronts (1, 2 or 4) per workgroup (small levels by teams, see
+ * kc_factor_use_teams, whatever wpb and order), except that every run of
  * consecutive levels with at most `persist_max` work units (64 entries of a
  * column each) runs as ONE persistent launch: a cooperative grid, resident as a
  * whole, whose wavefronts stride over each level's units with a grid-wide
@@ -292,6 +292,14 @@ void kc_factor_destroy(kc_factor *f);
  * Any pointer of kc_factor_schedule may be NULL. */
 kc_status kc_factor_set_schedule(kc_factor *f, int32_t wpb, int64_t persist_max, kc_unit_order order);
 kc_status kc_factor_schedule(const kc_factor *f, int32_t *wpb, int64_t *persist_max, kc_unit_order *order);
+
+/* Small levels (at most 3072 units, columns up to about 200,000, every row
+ * staged) run by teams: several wavefronts share 64 entries of a column, with the
+ * updates of Section 2.2's algorithm in the same order, so the same L bit for bit.
+ * The default; enable = 0 runs every level by the schedule above, with match
+ * masks if attached (slower in such levels).  Levels in persistent launches never
+ * run by teams. */
+kc_status kc_factor_use_teams(kc_factor *f, int32_t enable);
 
 /* Supernodal groups on the matrix cores (mixed-precision factors of supernodal
  * plans, kc_analyze_supernodal; the default for them).  The block-closed

@@ -246,6 +246,11 @@ class Factor:
         such factors) or entry by entry (enable=False)."""
         _lib.check(_lib.load().kc_factor_use_groups(self._h, int(bool(enable))), "kc_factor_use_groups")
 
+    def use_teams(self, enable: bool = True) -> None:
+        """Run small levels of the factorization by teams of wavefronts (the default) or as large ones run, by the
+        schedule and with match masks if these are attached (enable=False): the same L, slower in such levels."""
+        _lib.check(_lib.load().kc_factor_use_teams(self._h, int(bool(enable))), "kc_factor_use_teams")
+
     def set_stage_limit(self, max_parents: int = -1) -> None:
         """Rows with more than max_parents parents are read from device memory instead of staged in LDS
         (the same L); -1 restores the largest limit the LDS allows."""

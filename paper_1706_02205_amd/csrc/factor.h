@@ -70,6 +70,7 @@ struct kc_factor {
     kc::SweepRow* bwd_desc = nullptr;
     kc::TeamUnit* team_units = nullptr; // units of the levels that may run by teams ...
     std::vector<int64_t> team_off;      // ... where each level's start (nlevels + 1)
+    bool use_teams = true;
     kc::TopCol* bwd_top = nullptr;
     kc::BwdChunk* bwd_chunks = nullptr;
     int32_t* inst = nullptr;   // instance of each position (batches only)

@@ -1682,9 +1682,8 @@ kc_status launch_mask(const kc_factor* f, const IcholArgs<VT>& a, int64_t ub, in
 }
 
 // Whether level v (`units` 64-entry units) runs by teams.
-template <typename VT>
 bool team_level(const kc_factor* f, int v, int64_t units) {
-    return f->max_row <= f->stage_max && units > 0 && f->team_off[size_t(v) + 1] - f->team_off[size_t(v)] == units;
+    return f->use_teams && f->max_row <= f->stage_max && units > 0 && f->team_off[size_t(v) + 1] - f->team_off[size_t(v)] == units;
 }
 
 struct NoAfter {
@@ -1708,7 +1707,7 @@ kc_status launch_levels(const kc_factor* f, bool cnt, int pol, double tau, hipSt
         const int64_t cnt_v = f->unit_off[v + 1] - f->unit_off[v];  // 64-entry units: the grouping criterion
         if (cnt_v > f->persist_max) {
             kc_status st = KC_OK;
-            if (team_level<VT>(f, v, cnt_v))
+            if (team_level(f, v, cnt_v))
                 KC_HIP(kc::launch_team<VT>(f, cnt, pol, tau, v, s));
             else
                 st = go(bo[v], bo[v + 1], v, v + 1, bo[v + 1] - bo[v], false);
@@ -1867,8 +1866,7 @@ bool all_teams(const kc_factor* f) {
     for (size_t v = 0; v < nl; ++v) {
         const int64_t units = f->unit_off[v + 1] - f->unit_off[v];
         if (units <= f->persist_max) return false;
-        if (!(f->prec == KC_FP64 ? team_level<double>(f, int(v), units) : team_level<float>(f, int(v), units)))
-            return false;
+        if (!team_level(f, int(v), units)) return false;
     }
     return true;
 }
@@ -2887,6 +2885,12 @@ kc_status kc_factor_set_stage_limit(kc_factor* f, int32_t max_parents) {
         return KC_EINVAL;
     }
     f->stage_max = max_parents < 0 ? f->cap - 2 : std::min(max_parents, f->cap - 2);
+    return KC_OK;
+}
+
+kc_status kc_factor_use_teams(kc_factor* f, int32_t enable) {
+    if (!f) return KC_EINVAL;
+    f->use_teams = enable != 0;
     return KC_OK;
 }
 

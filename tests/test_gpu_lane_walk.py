@@ -1,0 +1,171 @@
+"""The kernels of large levels at small sizes: with teams switched off every level runs by a lane per entry, staged per
+level, with match masks or merging row indices, under every schedule -- L, pivots and update counts are the oracle's and
+the teams'.  Then what only large plans reach: groups that search for their parents, and factor levels too large to share
+a launch with the forward sweep."""
+import numpy as np
+import pytest
+
+import oracle as O
+from paper_1706_02205_amd import workloads as W
+from test_gpu_parity import CASES, dev, oracle_factor
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def K():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1706_02205_amd as K
+    return K
+
+
+def units_per_level(plan):
+    _, _, colptr, _ = plan.export()
+    return np.bincount(plan.levels(), weights=-(-np.diff(colptr) // 64))
+
+
+@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
+def test_masks_and_index_merge_without_teams(K, case):
+    name, gen, rho, rule, nu, ell, pivot, tau = case
+    print(f"[gpu] lane walk {name}", flush=True)
+    x = gen()
+    P, th, R = oracle_factor(x, rho, rule, nu, ell, O.PIVOT_ZERO if pivot == "zero" else O.PIVOT_SHIFT, tau)
+    plan = K.analyze(x, rho, rule)
+    xd = dev(x)
+    f = K.Factor(plan, "fp64")
+    f.use_teams(False)
+    for masks in (False, True):
+        if masks:
+            f.build_matches()
+        f.factorize(xd, nu, ell, pivot, tau, count_updates=True)
+        st = f.stats()
+        assert np.array_equal(f.export_L(), R.L), f"masks {masks}"
+        assert (st.updates, st.nonpositive, st.shifted) == (R.updates, R.nonpositive, R.shifted)
+        assert st.match_errors == 0 and st.exp_hard == 0
+        f.factorize(xd, nu, ell, pivot, tau)
+        assert np.array_equal(f.export_L(), R.L), f"masks {masks}, not counting"
+    mpiv, mtau = ("shift", 1e-6) if pivot == "zero" else (pivot, tau)
+    m = K.Factor(plan, "mixed")
+    m.factorize(xd, nu, ell, mpiv, mtau, count_updates=True)
+    want, sw = m.export_L(), m.stats()
+    m.use_teams(False)
+    for masks in (False, True):
+        if masks:
+            m.build_matches()
+        m.factorize(xd, nu, ell, mpiv, mtau, count_updates=True)
+        assert np.array_equal(m.export_L(), want, equal_nan=True), f"mixed, masks {masks}"
+        assert m.stats() == sw
+        m.factorize(xd, nu, ell, mpiv, mtau)
+        assert np.array_equal(m.export_L(), want, equal_nan=True), f"mixed, masks {masks}, not counting"
+
+
+# one launch per level: every width and order; 16: small levels in persistent launches, the others staged per level
+@pytest.mark.parametrize("masks", [False, True])
+@pytest.mark.parametrize("wpb,persist_max,order", [(1, 0, "spatial"), (2, 0, "spatial"), (4, 0, "spatial"),
+                                                   (1, 0, "longest"), (2, 0, "longest"), (4, 0, "longest"),
+                                                   (2, 16, "longest")])
+def test_schedules_without_teams(K, wpb, persist_max, order, masks):
+    print(f"[gpu] lane walk schedule wpb={wpb} persist_max={persist_max} order={order} masks={masks}", flush=True)
+    w = W.small_uniform_2d()
+    P, th, R = oracle_factor(w.points, w.rho, "max", w.nu, w.lengthscale)
+    f = K.Factor(K.analyze(w.points, w.rho), "fp64")
+    f.use_teams(False)
+    if masks:
+        f.build_matches()
+    f.set_schedule(wpb, persist_max, order)
+    f.factorize(dev(w.points), w.nu, w.lengthscale, count_updates=True)
+    st = f.stats()
+    assert st.updates == R.updates and st.match_errors == 0
+    assert np.array_equal(f.export_L(), R.L)
+
+
+@pytest.mark.parametrize("limit", [1, 3, 40])
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+def test_index_gap_escapes_without_teams(K, limit, prec):
+    w = W.small_uniform_2d()
+    pol = ("zero", 0.0) if prec == "fp64" else ("shift", 1e-6)
+    plan, xd = K.analyze(w.points, w.rho), dev(w.points)
+    f = K.Factor(plan, prec)
+    f.factorize(xd, w.nu, w.lengthscale, *pol)
+    want = f.export_L()
+    plan.set_delta_limit(limit)
+    g = K.Factor(plan, prec)
+    g.use_teams(False)
+    g.factorize(xd, w.nu, w.lengthscale, *pol)
+    assert np.array_equal(g.export_L(), want)
+
+
+# the fused call on two streams, and a graph of separate launches, as large plans run them; a batch in spatial order
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("nrhs", [1, 8, 11])
+def test_fused_call_and_graph_without_teams(K, prec, nrhs):
+    print(f"[gpu] lane walk fused {prec} nrhs={nrhs}", flush=True)
+    xs = [W.uniform_points(n, 2, 4600 + n) for n in (900, 40, 2000)]
+    plan = K.analyze_batched(xs, 3.0)
+    xd, ed = dev(np.concatenate(xs)), dev(np.array([0.2, 0.3, 0.1]))
+    bd = dev(W.gaussian_rhs(plan.n, nrhs, 4700))
+    pol = dict(pivot="zero", tau=0.0) if prec == "fp64" else dict(pivot="shift", tau=1e-6)
+    f = K.Factor(plan, prec)
+    want = f.factorize_solve(xd, bd, 1.5, ell_dev=ed, **pol).cpu().numpy()
+    L = f.export_L()
+    f.use_teams(False)
+    for masks in (False, True):
+        if masks:
+            f.build_matches()
+        for _ in range(2):
+            assert np.array_equal(f.factorize_solve(xd, bd, 1.5, ell_dev=ed, **pol).cpu().numpy(), want)
+            assert np.array_equal(f.export_L(), L)
+        g = f.capture(xd, bd, 1.5, ell_dev=ed, **pol)
+        for _ in range(3):
+            out = g.launch()
+            f.solve(bd)
+            assert np.array_equal(out.cpu().numpy(), want) and np.array_equal(f.export_L(), L)
+
+
+# levels of more than 4 (2 past four right-hand sides) units per CU run by teams but in a launch of their own, some of
+# them beside forward levels of 1024 rows and more
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("nrhs", [3, 9])
+def test_levels_too_large_to_share_a_launch(K, prec, nrhs):
+    import torch
+    x = W.uniform_points(20000, 2, 3)
+    plan = K.analyze(x, 1.5)
+    units = units_per_level(plan)
+    share = torch.cuda.get_device_properties(0).multi_processor_count * (4 if nrhs <= 4 else 2)
+    print(f"[gpu] split launches {prec} nrhs={nrhs}, levels of {units.max():.0f} units and less", flush=True)
+    assert share < units.max() <= 3072 and units.min() < share
+    rows = np.bincount(plan.levels())
+    assert (units[1:] > share)[rows[:-1] >= 1024].any() and (units[1:] > share)[rows[:-1] < 1024].any()
+    xd, bd = dev(x), dev(W.gaussian_rhs(plan.n, nrhs, 5))
+    f = K.Factor(plan, prec)
+    f.factorize(xd, 0.5, 0.2)
+    want, L = f.solve(bd).cpu().numpy(), f.export_L()
+    assert np.array_equal(f.factorize_solve(xd, bd, 0.5, 0.2).cpu().numpy(), want)
+    assert np.array_equal(f.export_L(), L)
+    f.use_teams(False)
+    assert np.array_equal(f.factorize_solve(xd, bd, 0.5, 0.2).cpu().numpy(), want)
+    assert np.array_equal(f.export_L(), L)
+
+
+# 384,400 columns: a bitmap of all of them leaves no room for the tile (the line is at some 376,000), so a group's parents
+# are searched; rows of more than 128 parents, so in more than one piece.  Rows of the kernel matrix sum to less than 1
+# off the diagonal (0.77 at most), so no pivot is shifted.  Bound as for the bitmap: FP32 updates of |P| parents are off
+# by at most |P| 2^-24, divided by the pivot's root, twice, and carried on (a factor of 10).
+def test_groups_that_search_for_their_parents(K):
+    x = W.jittered_grid(620, 3)
+    plan = K.analyze_supernodal(x, 1.6)
+    most = plan.info()["max_row"]
+    print(f"[gpu] groups by search, rows of up to {most}", flush=True)
+    assert most > 128 and np.diff(plan.supernodes()).max() > 4
+    xd = dev(x)
+    f = K.Factor(plan, "mixed")
+    f.factorize(xd, 0.5, 4e-4, "shift", 1e-6)
+    Lg, sg = f.export_L(), f.stats()
+    f.use_groups(False)
+    f.factorize(xd, 0.5, 4e-4, "shift", 1e-6)
+    Le, se = f.export_L(), f.stats()
+    assert sg.shifted == se.shifted == 0 and sg.nonfinite == 0
+    _, _, colptr, _ = plan.export()
+    assert np.abs(Lg - Le).max() <= 20 * most * 2.0**-24 / Le[colptr[:-1]].min()
