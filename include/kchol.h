@@ -246,7 +246,10 @@ kc_status kc_factorize_solve(kc_factor *f, const double *x_dev, kc_kernel kernel
  * once: one bit per entry of row k before (k,j) and one per parent of j; the
  * factorization then reads one bit instead of a 16-bit index per entry it
  * walks, stops at the last shared parent, and skips value lines holding none.
- * L is bitwise the same either way (same updates, same order).
+ * L is bitwise the same either way (same updates, same order).  Levels that run
+ * by teams (kc_factor_use_teams) read no masks, being faster without: on a plan
+ * whose levels all do, masks cost their buffer and buy nothing.
+ * kc_factor_match_levels tells beforehand.
  *
  * kc_factor_match_bytes: device bytes the masks need -- an 8-byte word per
  * entry of S plus about (pos + np) / 64 8-byte words per entry, pos being the
@@ -255,12 +258,16 @@ kc_status kc_factorize_solve(kc_factor *f, const double *x_dev, kc_kernel kernel
  * once per factor.
  * kc_factor_match_build: builds the masks in the caller-owned buffer buf_dev
  * (>= kc_factor_match_bytes, 256-byte aligned), synchronously on `stream`;
- * later factorizations of this factor use them.  The buffer must stay valid
+ * later factorizations of this factor use them in the levels that
+ * kc_factor_match_levels counts.  The buffer must stay valid
  * while they are attached; buf_dev = NULL detaches them (back to the index
  * merge).  KC_EWORKSPACE for a short or misaligned buffer, KC_ERANGE if a
- * row is too long to stage (more than about 10,000 entries). */
+ * row is too long to stage (more than about 10,000 entries).
+ * kc_factor_match_levels: levels of the factorization that read masks once these
+ * are attached, under the factor's current settings (0: none would). */
 kc_status kc_factor_match_bytes(kc_factor *f, void *stream, size_t *bytes);
 kc_status kc_factor_match_build(kc_factor *f, void *buf_dev, size_t bytes, void *stream);
+kc_status kc_factor_match_levels(const kc_factor *f, int32_t *levels);
 
 /* Synchronises the factor's last stream and reports pivot statistics. */
 kc_status kc_factor_stats(kc_factor *f, kc_factor_stats_t *stats);

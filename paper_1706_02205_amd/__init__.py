@@ -360,9 +360,16 @@ class Factor:
                    "kc_factor_match_bytes")
         return int(nb.value)
 
+    def match_levels(self) -> int:
+        """Levels of the factorization that read match masks once these are built; 0: they would buy nothing."""
+        n = C.c_int32()
+        _lib.check(_lib.load().kc_factor_match_levels(self._h, C.byref(n)), "kc_factor_match_levels")
+        return int(n.value)
+
     def build_matches(self, stream=None) -> int:
         """Build the match masks (symbolic, once per pattern) in a torch-allocated buffer kept by this
-        object; later factorizations use them and give bitwise the same L.  Returns their bytes."""
+        object; later factorizations use them where match_levels() says and give bitwise the same L.
+        Returns their bytes."""
         import torch
         need = self.match_bytes(stream)
         self._matches = torch.empty(max(need, 256), dtype=torch.uint8, device="cuda")

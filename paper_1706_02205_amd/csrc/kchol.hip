@@ -2894,6 +2894,17 @@ kc_status kc_factor_use_teams(kc_factor* f, int32_t enable) {
     return KC_OK;
 }
 
+kc_status kc_factor_match_levels(const kc_factor* f, int32_t* levels) {
+    if (!f || !levels) return KC_EINVAL;
+    *levels = 0;
+    if (groups_on(f, false)) return KC_OK;
+    for (size_t v = 0; v + 1 < f->unit_off.size(); ++v) {
+        const int64_t units = f->unit_off[v + 1] - f->unit_off[v];
+        if (units <= f->persist_max || !team_level(f, int(v), units)) ++*levels;
+    }
+    return KC_OK;
+}
+
 kc_status kc_factor_use_groups(kc_factor* f, int32_t enable) {
     if (!f) return KC_EINVAL;
     if (enable && !f->groups) {

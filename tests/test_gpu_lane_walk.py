@@ -34,8 +34,11 @@ def test_masks_and_index_merge_without_teams(K, case):
     P, th, R = oracle_factor(x, rho, rule, nu, ell, O.PIVOT_ZERO if pivot == "zero" else O.PIVOT_SHIFT, tau)
     plan = K.analyze(x, rho, rule)
     xd = dev(x)
+    nl = plan.info()["nlevels"]
     f = K.Factor(plan, "fp64")
+    assert f.match_levels() == 0  # every level of these plans runs by teams, which read no masks
     f.use_teams(False)
+    assert f.match_levels() == nl
     for masks in (False, True):
         if masks:
             f.build_matches()
@@ -140,6 +143,7 @@ def test_levels_too_large_to_share_a_launch(K, prec, nrhs):
     assert (units[1:] > share)[rows[:-1] >= 1024].any() and (units[1:] > share)[rows[:-1] < 1024].any()
     xd, bd = dev(x), dev(W.gaussian_rhs(plan.n, nrhs, 5))
     f = K.Factor(plan, prec)
+    assert f.match_levels() == 0
     f.factorize(xd, 0.5, 0.2)
     want, L = f.solve(bd).cpu().numpy(), f.export_L()
     assert np.array_equal(f.factorize_solve(xd, bd, 0.5, 0.2).cpu().numpy(), want)
@@ -161,6 +165,7 @@ def test_groups_that_search_for_their_parents(K):
     assert most > 128 and np.diff(plan.supernodes()).max() > 4
     xd = dev(x)
     f = K.Factor(plan, "mixed")
+    assert f.match_levels() == 0
     f.factorize(xd, 0.5, 4e-4, "shift", 1e-6)
     Lg, sg = f.export_L(), f.stats()
     f.use_groups(False)
