@@ -1938,9 +1938,7 @@ kc_status factorize_solve_typed(kc_factor* f, int pol, double tau, const double*
         const kc_status st = factorize_forward<VT>(f, pol, tau, b, nrhs, y, s);
         return st != KC_OK ? st : backward();
     }
-    const kc_status made = make_aux(f);
-    if (made != KC_OK) return made;
-    hipStream_t aux = f->aux;
+    hipStream_t aux = f->aux;  // make_aux was called
     hipEvent_t ev = f->aux_ev;
     auto after = [&](int l0, int l1) -> kc_status {
         KC_HIP(hipEventRecord(ev, s));
@@ -2608,7 +2606,9 @@ kc_status kc_factorize_solve(kc_factor* f, const double* x_dev, kc_kernel kernel
     double* y = static_cast<double*>(scratch_dev);
     double* partial = reinterpret_cast<double*>(static_cast<char*>(scratch_dev) +
                                                 align256(size_t(f->n) * size_t(nrhs) * sizeof(double)));
-    kc_status st = launch_start(f, x_dev, tn, ell_dev ? 0.0 : kernel.lengthscale, ell_dev, s);
+    kc_status st = KC_OK;
+    if (!groups_on(f, false) && !all_teams(f)) st = make_aux(f);  // a refusal leaves the factor as it was
+    if (st == KC_OK) st = launch_start(f, x_dev, tn, ell_dev ? 0.0 : kernel.lengthscale, ell_dev, s);
     if (st != KC_OK) return st;
     if (groups_on(f, false)) {  // the group DAG has its own levels: factor, then both sweeps
         st = launch_groups(f, tn, kernel.lengthscale, int(pivot), tau, s);
