@@ -2218,13 +2218,14 @@ kc_status kc_factor_create(const kc_plan* plan, kc_prec prec, void* ws_dev, size
     const kc::Plan& p = plan->p;
     BwdSchedule bs;
     GroupSchedule gs;
+    Layout o;
     try {
         bs = backward_schedule(p);
         if (prec == KC_MIXED) gs = group_schedule(p);
+        o = layout_of(p, bs, prec, gs);
     } catch (const std::bad_alloc&) {
         return KC_ENOMEM;
     }
-    const Layout o = layout_of(p, bs, prec, gs);
     if (ws_bytes < o.total) {
         kc::set_error("kc_factor_create: workspace holds " + std::to_string(ws_bytes) + " bytes, needs " +
                       std::to_string(o.total));
@@ -2293,17 +2294,21 @@ kc_status kc_factor_create(const kc_plan* plan, kc_prec prec, void* ws_dev, size
     f->fwd_desc = reinterpret_cast<kc::SweepRow*>(base + o.fdesc);
     f->bwd_desc = reinterpret_cast<kc::SweepRow*>(base + o.bdesc);
     f->team_units = reinterpret_cast<kc::TeamUnit*>(base + o.team);
-    f->team_off = team_offsets(p, vt);
     f->inst = p.ninst > 1 ? reinterpret_cast<int32_t*>(base + o.inst) : nullptr;
     f->ninst = p.ninst;
-    f->unit_off = p.unit_off;
-    f->fwd_off = p.fwd_off;
-    f->level_last.assign(size_t(p.nlevels), 0);
-    for (int64_t j = 0; j < p.n; ++j) f->level_last[size_t(p.level[size_t(j)])] = int32_t(j);
-    f->short_off = bs.short_off;
-    f->short_sum = bs.short_sum;
-    f->top_off = bs.top_off;
-    f->tchunk_off = bs.tchunk_off;
+    try {
+        f->team_off = team_offsets(p, vt);
+        f->unit_off = p.unit_off;
+        f->fwd_off = p.fwd_off;
+        f->level_last.assign(size_t(p.nlevels), 0);
+        for (int64_t j = 0; j < p.n; ++j) f->level_last[size_t(p.level[size_t(j)])] = int32_t(j);
+        f->short_off = bs.short_off;
+        f->short_sum = bs.short_sum;
+        f->top_off = bs.top_off;
+        f->tchunk_off = bs.tchunk_off;
+    } catch (const std::bad_alloc&) {
+        return KC_ENOMEM;
+    }
     f->nfine = bs.nfine;
     f->max_slots = bs.max_slots;
 
