@@ -64,9 +64,8 @@ struct kc_factor {
     kc::Unit* bunits_alt[3] = {nullptr, nullptr, nullptr};
     int64_t* boff_dev[3] = {nullptr, nullptr, nullptr};
     std::vector<int64_t> boff[3];
-    int32_t* fwd_rows = nullptr;
     int32_t* bwd_short = nullptr;
-    kc::SweepRow* fwd_desc = nullptr;   // fwd_rows and bwd_short with their pointers
+    kc::SweepRow* fwd_desc = nullptr;   // rows by level, and bwd_short, with their pointers
     kc::SweepRow* bwd_desc = nullptr;
     kc::TeamUnit* team_units = nullptr; // units of the levels that may run by teams ...
     std::vector<int64_t> team_off;      // ... where each level's start (nlevels + 1)

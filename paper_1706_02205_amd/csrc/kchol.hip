@@ -1336,10 +1336,14 @@ GroupSchedule group_schedule(const kc::Plan& p) {
 constexpr int64_t kTeamUnits = 12 * 256;
 constexpr size_t kTeamLds = 72 * 1024;
 
-// Units of each level that may, as offsets (a level that may not has none).
-std::vector<int64_t> team_offsets(const kc::Plan& p, size_t vt) {
+std::vector<int32_t> last_columns(const kc::Plan& p) {
     std::vector<int32_t> last(size_t(p.nlevels), 0);
     for (int64_t j = 0; j < p.n; ++j) last[size_t(p.level[size_t(j)])] = int32_t(j);
+    return last;
+}
+
+// Units of each level that may, as offsets (a level that may not has none); last: last_columns(p).
+std::vector<int64_t> team_offsets(const kc::Plan& p, const std::vector<int32_t>& last, size_t vt) {
     std::vector<int64_t> off(size_t(p.nlevels) + 1, 0);
     for (int32_t v = 0; v < p.nlevels; ++v) {
         const int64_t units = p.unit_off[size_t(v) + 1] - p.unit_off[size_t(v)];
@@ -1351,8 +1355,7 @@ std::vector<int64_t> team_offsets(const kc::Plan& p, size_t vt) {
 
 struct Layout {
     size_t counters, xh, perm, colptr, rowidx, csc2csr, rowptr, rowend, colidx, cdelta, escptr, esc, L, Lcsc, diag,
-        units, unit_off, bunits[2][3], boff[3], fwd, bshort,
-        blong, bchunks, inst, groups, gunits, fdesc, bdesc, team, total;
+        units, unit_off, bunits[2][3], boff[3], bshort, blong, bchunks, inst, groups, gunits, fdesc, bdesc, team, total;
 };
 
 Layout layout_of(const kc::Plan& p, const BwdSchedule& b, kc_prec prec, const GroupSchedule& gs = GroupSchedule()) {
@@ -1389,7 +1392,6 @@ Layout layout_of(const kc::Plan& p, const BwdSchedule& b, kc_prec prec, const Gr
         for (int r = 0; r < 2; ++r) o.bunits[r][w] = take(nb * sizeof(Unit));
         o.boff[w] = take((size_t(p.nlevels) + 1) * sizeof(int64_t));
     }
-    o.fwd = take(n * sizeof(int32_t));
     o.bshort = take(b.shortc.size() * sizeof(int32_t));
     o.blong = take(b.topc.size() * sizeof(kc::TopCol));
     o.bchunks = take(b.chunks.size() * sizeof(kc::BwdChunk));
@@ -1398,7 +1400,7 @@ Layout layout_of(const kc::Plan& p, const BwdSchedule& b, kc_prec prec, const Gr
     o.gunits = take(prec == KC_MIXED ? gs.units.size() * sizeof(int2) : 0);
     o.fdesc = take(n * sizeof(kc::SweepRow));
     o.bdesc = take(b.shortc.size() * sizeof(kc::SweepRow));
-    o.team = take(size_t(team_offsets(p, vt).back()) * sizeof(kc::TeamUnit));
+    o.team = take(size_t(team_offsets(p, last_columns(p), vt).back()) * sizeof(kc::TeamUnit));
     o.total = at;
     return o;
 }
@@ -2287,7 +2289,6 @@ kc_status kc_factor_create(const kc_plan* plan, kc_prec prec, void* ws_dev, size
         f->bunits_alt[w] = f->bunits[KC_ORDER_LONGEST][w];
         f->boff_dev[w] = reinterpret_cast<int64_t*>(base + o.boff[w]);
     }
-    f->fwd_rows = reinterpret_cast<int32_t*>(base + o.fwd);
     f->bwd_short = reinterpret_cast<int32_t*>(base + o.bshort);
     f->bwd_top = reinterpret_cast<kc::TopCol*>(base + o.blong);
     f->bwd_chunks = reinterpret_cast<kc::BwdChunk*>(base + o.bchunks);
@@ -2297,11 +2298,10 @@ kc_status kc_factor_create(const kc_plan* plan, kc_prec prec, void* ws_dev, size
     f->inst = p.ninst > 1 ? reinterpret_cast<int32_t*>(base + o.inst) : nullptr;
     f->ninst = p.ninst;
     try {
-        f->team_off = team_offsets(p, vt);
+        f->level_last = last_columns(p);
+        f->team_off = team_offsets(p, f->level_last, vt);
         f->unit_off = p.unit_off;
         f->fwd_off = p.fwd_off;
-        f->level_last.assign(size_t(p.nlevels), 0);
-        for (int64_t j = 0; j < p.n; ++j) f->level_last[size_t(p.level[size_t(j)])] = int32_t(j);
         f->short_off = bs.short_off;
         f->short_sum = bs.short_sum;
         f->top_off = bs.top_off;
@@ -2354,7 +2354,6 @@ kc_status kc_factor_create(const kc_plan* plan, kc_prec prec, void* ws_dev, size
         KC_HIP(hipMemcpyAsync(f->boff_dev[w], f->boff[w].data(), f->boff[w].size() * sizeof(int64_t),
                               hipMemcpyHostToDevice, s));
     }
-    KC_HIP(hipMemcpyAsync(f->fwd_rows, p.fwd_rows.data(), n * sizeof(int32_t), hipMemcpyHostToDevice, s));
     if (!bs.shortc.empty())
         KC_HIP(hipMemcpyAsync(f->bwd_short, bs.shortc.data(), bs.shortc.size() * sizeof(int32_t),
                               hipMemcpyHostToDevice, s));
@@ -2374,9 +2373,11 @@ kc_status kc_factor_create(const kc_plan* plan, kc_prec prec, void* ws_dev, size
                               hipMemcpyHostToDevice, s));
         KC_HIP(hipMemcpyAsync(f->gunits, gs.units.data(), gs.units.size() * sizeof(int2), hipMemcpyHostToDevice, s));
     }
-    // the schedules once more with the rows' pointers beside them, from what was uploaded
-    const unsigned nb = grid_for(p.n, kBlock);
-    fill_fwd_desc<<<nb, kBlock, 0, s>>>(f->fwd_rows, p.n, f->rowptr, f->rowend, f->perm, f->fwd_desc);
+    // the schedules with the rows' pointers beside them, from what was uploaded; the
+    // rows by level pass through L's region (64 entries a row and more, not yet in use)
+    int32_t* rows = static_cast<int32_t*>(f->L);
+    KC_HIP(hipMemcpyAsync(rows, p.fwd_rows.data(), n * sizeof(int32_t), hipMemcpyHostToDevice, s));
+    fill_fwd_desc<<<grid_for(p.n, kBlock), kBlock, 0, s>>>(rows, p.n, f->rowptr, f->rowend, f->perm, f->fwd_desc);
     KC_LAUNCH_CHECK();
     if (!bs.shortc.empty()) {
         const int64_t ns = int64_t(bs.shortc.size());

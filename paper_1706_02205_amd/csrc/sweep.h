@@ -7,7 +7,7 @@
 
 namespace kc {
 
-// Rows [rb, re) of fwd_rows, one level: y = (P b - L y) / L_kk for right-hand sides r0 .. r0 + nr - 1 (nr <= 8).
+// Rows [rb, re) of fwd_desc, one level: y = (P b - L y) / L_kk for right-hand sides r0 .. r0 + nr - 1 (nr <= 8).
 template <typename VT>
 hipError_t launch_fwd(const kc_factor* f, const double* b, int ld, int r0, int nr, double* y, int64_t rb,
                              int64_t re, hipStream_t s);

@@ -44,7 +44,7 @@ __global__ __launch_bounds__(kThreads) void sweep_narrow(SweepArgs<VT> a, int64_
 template <typename VT, int NR>
 __global__ __launch_bounds__(kThreads) void fwd_wide(SweepArgs<VT> a, int64_t beg, int64_t end) {
     const int64_t t = beg + int64_t(xcd_block()) * (kThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
-    if (t < end) wide_row<VT, NR>(a, a.rows[t], NR, threadIdx.x % 64);
+    if (t < end) wide_row<VT, NR>(a, a.rows[t], threadIdx.x % 64);
 }
 
 template <typename VT, bool FWD>

@@ -35,7 +35,7 @@ __device__ __forceinline__ double diag_value(const VT* Lv, const double* diag, i
 template <typename VT, int NR, int STRIDE = 64>
 __device__ __forceinline__ void dot_entries(const int32_t* __restrict__ rowidx, const VT* __restrict__ Lcsc, int64_t e,
                                             int64_t e1, const double* __restrict__ y, int ld, int r0,
-                                            double (&s)[NR], int nr = NR) {
+                                            double (&s)[NR]) {
     constexpr int kDepth = 4;
     int ci[kDepth];
 #pragma unroll
@@ -58,7 +58,7 @@ __device__ __forceinline__ void dot_entries(const int32_t* __restrict__ rowidx, 
                 l[u] = double(Lcsc[e + int64_t(u) * STRIDE]);
                 const double* xk = y + int64_t(ci[u]) * ld + r0;
 #pragma unroll
-                for (int r = 0; r < NR; ++r) v[u][r] = r < nr ? xk[r] : 0.0;
+                for (int r = 0; r < NR; ++r) v[u][r] = xk[r];
             }
         }
 #pragma unroll
@@ -82,11 +82,11 @@ constexpr int64_t kWideRows = 1024;
 
 template <typename VT, int NR>
 __device__ __forceinline__ double wave_dot(const int32_t* __restrict__ idx, const VT* __restrict__ val, int64_t b0,
-                                           int64_t b1, const double* __restrict__ src, int ld, int r0, int nr, int lane) {
+                                           int64_t b1, const double* __restrict__ src, int ld, int r0, int lane) {
     double s[NR];
 #pragma unroll
     for (int r = 0; r < NR; ++r) s[r] = 0.0;
-    dot_entries<VT, NR>(idx, val, b0 + lane, b1, src, ld, r0, s, nr);
+    dot_entries<VT, NR>(idx, val, b0 + lane, b1, src, ld, r0, s);
 #pragma unroll
     for (int r = 0; r < NR; ++r)
 #pragma unroll
@@ -124,11 +124,11 @@ SweepArgs<VT> fwd_args(const kc_factor* f, const double* b, int ld, int r0, doub
 
 // One row of a wide forward level by a wavefront.
 template <typename VT, int NR>
-__device__ __forceinline__ void wide_row(const SweepArgs<VT>& a, const kc::SweepRow row, int nr, int lane) {
+__device__ __forceinline__ void wide_row(const SweepArgs<VT>& a, const kc::SweepRow row, int lane) {
     const int k = row.k;
     const int64_t p0 = row.p0, pd = p0 + row.n;  // pd: the diagonal
-    const double v = wave_dot<VT, NR>(a.idx, a.val, p0, pd, a.y, a.ld, a.r0, nr, lane);
-    if (lane < nr) {
+    const double v = wave_dot<VT, NR>(a.idx, a.val, p0, pd, a.y, a.ld, a.r0, lane);
+    if (lane < NR) {
         const double lkk = diag_value(a.val, a.diag, pd, k);
         const double acc = a.b[int64_t(row.perm) * a.ld + a.r0 + lane] - v;
         a.y[int64_t(k) * a.ld + a.r0 + lane] = (lkk == 0.0) ? 0.0 : acc / lkk;

@@ -290,9 +290,6 @@ TeamArgs<VT> team_args(const kc_factor* f, int level, int policy, double tau) {
             f->counters, f->inst};
 }
 
-template <int V>
-using Int = std::integral_constant<int, V>;
-
 // The split of a level.  At most a quarter of a unit per CU: 16 entries to a
 // workgroup, 4 to a wavefront, so that the chains' LDS reads (a whole instruction
 // for a wavefront's few entries) spread over more CUs.  Up to 2 units per CU: 32
