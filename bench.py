@@ -2,7 +2,7 @@
 
 Workload (default): 10^6 points on a jittered 1000x1000 grid over [0,1]^2,
 Matern nu=1/2 with lengthscale 0.1, rho = 4, maximin ordering, max-rule pattern,
-8 N(0,1) right-hand sides.  One step = Theta on S fused into ICHOL(0) (one
+8 N(0,1) right-hand sides.  One step = Theta on S (one launch) and ICHOL(0) (one
 launch per DAG level) + the forward and backward triangular solves for all
 right-hand sides.  Points, pattern and right-hand sides are resident in HBM
 before timing starts; the host analysis (ordering, pattern, schedule), the
@@ -585,8 +585,8 @@ def main():
             "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                          "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
                          "measured_copy_GBps": copy_gbs, "frac_of_copy": achieved / copy_gbs,
-                         "kernel": ("ichol_level (match masks)" if r["match"] else
-                                    "ichol_level (index merge)") + ", one launch per DAG level, after one of theta_kernel",
+                         "kernel": ("ichol_level (match masks)" if r["match"] else "ichol_level (index merge)") +
+                                   ", ichol_team in small levels; one launch per DAG level, after one of theta_kernel",
                          "launches_per_factorization": launches,
                          "algorithmic_bytes_per_launch": B / launches,
                          "avg_launch_ms": tf / launches * 1e3},

@@ -655,10 +655,12 @@ __device__ __forceinline__ int stage_values(const IcholArgs<VT>& a, int j, VT* s
 // the staged row -- the same updates in the same order as the index merge, from
 // one bit per walked entry instead of a 16-bit index gap.  A value piece with
 // no set bit is not loaded.  Bound by memory: the pieces of one factorization are
-// 142 GB of L2 misses at 360,000 grid points in FP64, read at 4.3 TB/s in 33.2 ms,
-// and a level walks a row once if at all, so nothing is shared (the next piece
-// requested ahead, in 107 registers instead of 71: 34.7 -> 37.0 ms where that left
-// enough wavefronts, 38.9 in every level).  Every loop is bounded by the masks' lengths and
+// 142 GB of L2 misses at 360,000 grid points in FP64, read at 4.3 TB/s in 33.2 ms.
+// Little of that could be shared: a level walks a row 1.2 times on average and at
+// most 4 times, 116 GB of value lines in all, 96 GB if each met its row in the cache
+// (the rest are the masks, the staged rows and the entries' own data).  (The next
+// piece requested ahead, in 107 registers instead of 71: 34.7 -> 37.0 ms where that
+// left enough wavefronts, 38.9 in every level.)  Every loop is bounded by the masks' lengths and
 // every read checked against them, so inconsistent masks are counted
 // (kMatchErr), never followed outside row j or the mask buffer.
 template <bool COUNT, typename VT, bool STAGED>
@@ -1328,7 +1330,8 @@ GroupSchedule group_schedule(const kc::Plan& p) {
 }
 
 // Which levels may run by teams (team.hip, which needs every row staged): at most
-// 12 units per CU (360,000 grid points, FP64 with match masks: 34.3 ms with levels
+// 12 units for each of the 256 CUs -- a number, since the workspace that holds the
+// units is sized without a device -- (360,000 grid points, FP64 with match masks: 34.3 ms with levels
 // of up to 3,000 units by teams, 34.6 without any, 40.1 with up to 4,000; 160,000
 // points without masks: 17.9 ms, 21.8 with up to 1,500, 18.4 with all); and the
 // bitmap of the level's last column small enough that two workgroups share a CU

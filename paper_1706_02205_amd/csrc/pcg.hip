@@ -30,7 +30,7 @@ void set_error(const std::string& msg);
 namespace {
 
 constexpr int kRows = 256;       // rows (threads) per block
-constexpr int kTileJ = 256;      // columns staged per LDS tile (at most)
+constexpr int kTileJ = 256;      // columns staged per LDS tile (at most; 512 where 16 wavefronts share them)
 constexpr int kDotBlocks = 512;  // fixed grid of the dot-product reduction
 
 // exp(x) for -707 <= x <= 0 by table lookup and a short polynomial (Tang's
@@ -130,6 +130,8 @@ __device__ __forceinline__ double matern_fast(double a, const double* __restrict
 // 150,000 the two are equal, at 10^6 128 rows take 1.02 s, 32 rows 1.08 s).  With
 // 20 or more coordinates in registers the lines lie at 6,000 and 30,000 (20-D:
 // 9,001 points 500 us by 16 rows, 510 by 32, 981 by 128; 40,000 8.8, 7.0, 6.4 ms).
+// The lines are rows, measured on 256 CUs, and not workgroups per CU: a row's work
+// grows with n too, and with it what a split's start and end cost beside it.
 // Reading a row's coordinates through the cache for every quad, as any d above 3
 // once did, took 7.1 ms and 42 ms there.  The split sums are the more accurate ones
 // (against 80-bit sums, 100,000 points in 3-D: 1.2e-14 of the norm by 128 rows,
@@ -333,7 +335,7 @@ hipError_t launch_matvec_d(const double* x, int64_t n, int d, double scale, cons
         auto go = [&](auto nb, auto gr, auto se, auto sp) {
             constexpr int NB = decltype(nb)::value, G = decltype(gr)::value, SETS = decltype(se)::value,
                           SPLIT = decltype(sp)::value;
-            // column tile: a multiple of 4, at most kTileJ (64 per wavefront of a split), with the LDS footprint
+            // column tile: a multiple of 4, at most kTileJ (and 32 per wavefront of a split), with the LDS footprint
             // within 64 KiB and at least the wavefronts' sums
             const int most = ((kMfmaLds / int(sizeof(double)) - kExpSize) / (D + kMfmaRhs)) & ~3;
             const int tj = std::min(std::max(kTileJ, 32 * SPLIT), most);

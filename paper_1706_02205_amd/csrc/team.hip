@@ -293,8 +293,8 @@ TeamArgs<VT> team_args(const kc_factor* f, int level, int policy, double tau) {
 // The split of a level.  At most a quarter of a unit per CU: 16 entries to a
 // workgroup, 4 to a wavefront, so that the chains' LDS reads (a whole instruction
 // for a wavefront's few entries) spread over more CUs.  Up to 2 units per CU: 32
-// and 8; whole units of 9 wavefronts ran one to a CU there, and a level of 257
-// units took twice as long as one of 256 (2,000 points 0.565 -> 0.516 ms, 20,011
+// and 8, in five wavefronts as everywhere: whole units of 64 and 8, in nine, ran one
+// to a CU, and a level of 257 units took twice as long as one of 256 (2,000 points 0.565 -> 0.516 ms, 20,011
 // in 3-D 5.35 -> 5.19 ms with both).  Beyond, 64 and 16: half as many chain reads
 // per update (160,000 grid points: 17.9 ms against 20.3 ms with 8 entries to a
 // wavefront; 32: 19.5 ms).
