@@ -17,7 +17,8 @@
 namespace kc::counter {
 enum Counter {
     kNonpos = 0, kShifted = 1, kUpdates = 2, kExpHard = 3, kNonfinite = 4, kMatchErr = 5, kMatchTotal = 6,
-    kUnsound = 7
+    kNumCounts = 7,
+    kUnsound = 32  // in a line of its own: stores beside the counts' atomics held up every level
 };
 // Notes the instance of column j (inst: the instance of each column, or null for a single problem).
 __device__ __forceinline__ void note_unsound(unsigned long long* counters, const int32_t* inst, int j) {

@@ -2470,7 +2470,7 @@ kc_status kc_theta(kc_factor* f, const double* x_dev, kc_kernel kernel, double* 
     const int tn = twonu_of(kernel.nu);
     if (!tn || !(kernel.lengthscale > 0.0)) return KC_EINVAL;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    zero_u64<<<1, 64, 0, s>>>(f->counters, kUnsound);  // the counts, not the notes
+    zero_u64<<<1, 64, 0, s>>>(f->counters, kNumCounts);  // not the notes
     KC_LAUNCH_CHECK();
     gather_points<<<grid_for(f->n * f->d, kBlock), kBlock, 0, s>>>(x_dev, f->perm, f->n, f->d, f->xh);
     KC_LAUNCH_CHECK();
@@ -2636,7 +2636,7 @@ kc_status kc_factorize_solve(kc_factor* f, const double* x_dev, kc_kernel kernel
 
 kc_status kc_factor_stats(kc_factor* f, kc_factor_stats_t* st) {
     if (!f || !st) return KC_EINVAL;
-    unsigned long long c[kUnsound];
+    unsigned long long c[kNumCounts];
     KC_HIP(hipStreamSynchronize(f->last));
     KC_HIP(hipMemcpy(c, f->counters, sizeof(c), hipMemcpyDeviceToHost));
     st->nonpositive = int64_t(c[kNonpos]);

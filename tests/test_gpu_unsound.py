@@ -58,6 +58,30 @@ def test_instance_of_a_batch_with_shifted_pivots_elsewhere(K, prec, order):
         o0 += len(x)
 
 
+# Notes beyond the 64 values that one workgroup clears: the long instance last of 2, 33 and 70, unsound and sound again.
+@pytest.mark.parametrize("count", [2, 33, 70])
+def test_notes_of_many_instances_are_cleared(K, count):
+    nu, rho, x = 0.5, 4.0, W.uniform_points(5000, 2, 4311)
+    print(f"[gpu] notes of {count} instances", flush=True)
+    xs = [W.uniform_points(3 + i % 5, 2, i) for i in range(count - 1)] + [x]
+    b = W.gaussian_rhs(sum(map(len, xs)), 2, 4600)
+    xd, ed, bd = dev(np.concatenate(xs)), dev(np.full(count, 0.05)), dev(b)
+    f = K.Factor(K.analyze_batched(xs, rho), "fp64")
+    f.factorize_batched(xd, nu, ed, "shift", 1e-3)
+    assert f.stats().shifted == 0
+    want = f.solve(bd).cpu().numpy()
+    alone = K.Factor(K.analyze(x, rho), "fp64")
+    alone.factorize(dev(x), nu, 0.05, "shift", 1e-3)
+    assert np.array_equal(want[-len(x):], alone.solve(dev(b[-len(x):])).cpu().numpy())
+    f.factorize_batched(xd, nu, ed, "shift", 0.5)
+    assert f.stats().shifted > 0
+    alone.factorize(dev(x), nu, 0.05, "shift", 0.5)
+    got = f.solve(bd).cpu().numpy()
+    assert np.array_equal(got[-len(x):], alone.solve(dev(b[-len(x):])).cpu().numpy())
+    f.factorize_batched(xd, nu, ed, "shift", 1e-3)
+    assert np.array_equal(f.solve(bd).cpu().numpy(), want)
+
+
 # Positions past the last long column see no summed piece but these columns, so there the sequential order shows bit for
 # bit: finite after shifted pivots; overflowing, with the oracle's infinities and NaN at their places; and not so for a
 # sound factor, which sums.
