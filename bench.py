@@ -178,7 +178,7 @@ def run_gpu(w, prec, steps, warmup, plan, pivot, tau, pcg_tol, keep_L=False, mat
     return dict(wall=wall, wall_fused=wall_fused, t_factor=t_fac, t_solve=t_sol, updates=st.updates, rank=st2.rank,
                 nonpositive=st2.nonpositive, shifted=st2.shifted, exp_hard=st2.exp_hard, nonfinite=st2.nonfinite,
                 match_errors=st2.match_errors, t_upload=t_upload, t_index=t_index, match=match,
-                workspace_bytes=f.workspace_bytes, refine=refine, L=f.export_L() if keep_L else None,
+                workspace_bytes=f.workspace_bytes, refine=refine, lane_levels=f.match_levels(), L=f.export_L() if keep_L else None,
                 schedule=dict(zip(("waves_per_block", "persist_max", "unit_order"), f.schedule())))
 
 
@@ -578,6 +578,7 @@ def main():
         launches = info["nlevels"]
         achieved = (B / launches) / (tf / launches) / 1e9
         traffic = measured_traffic(prec, w.name)
+        walk = "ichol_level (match masks)" if r["match"] else "ichol_level (index merge)"
         entries[prec] = {
             "value": nnz / step_s, "ms_per_step": step_s * 1e3,
             "step_ms": {"factorize_then_solve": step_sep * 1e3, "factorize_solve_fused": step_fused * 1e3},
@@ -585,8 +586,9 @@ def main():
             "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                          "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
                          "measured_copy_GBps": copy_gbs, "frac_of_copy": achieved / copy_gbs,
-                         "kernel": ("ichol_level (match masks)" if r["match"] else "ichol_level (index merge)") +
-                                   ", ichol_team in small levels; one launch per DAG level, after one of theta_kernel",
+                         "kernel": (walk if r["lane_levels"] == launches else "ichol_team" if not r["lane_levels"] else
+                                    f"{walk} in {r['lane_levels']} levels, ichol_team in the others") +
+                                   ", one launch per DAG level, after one of theta_kernel",
                          "launches_per_factorization": launches,
                          "algorithmic_bytes_per_launch": B / launches,
                          "avg_launch_ms": tf / launches * 1e3},
