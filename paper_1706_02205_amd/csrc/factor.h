@@ -74,6 +74,7 @@ struct kc_factor {
     kc::TopCol* bwd_top = nullptr;
     kc::BwdChunk* bwd_chunks = nullptr;
     int32_t* inst = nullptr;   // instance of each position (batches only)
+    int64_t nmarked = 0;       // rows of bwd_desc that carry their instance's note (all, if columns are summed)
     // supernodal groups on the matrix cores (mixed precision, supernodal plans)
     kc::GroupDesc* groups = nullptr;
     int2* gunits = nullptr;

@@ -162,6 +162,18 @@ __global__ void fill_bwd_desc(const int32_t* __restrict__ cols, int64_t n, const
     out[t] = kc::SweepRow{uint32_t(colptr[j] + 1), int32_t(colptr[j + 1] - colptr[j] - 1), j, perm[j]};
 }
 
+// The notes of unsound instances, put into the rows of the backward sweep, so that a
+// workgroup has its row's note with the row (read beside it, through the row's
+// instance, a solve of 48 problems took 1.543 ms, so 1.531).
+__global__ void mark_rows(kc::SweepRow* __restrict__ rows, int64_t n, const int32_t* __restrict__ inst,
+                          const unsigned long long* __restrict__ counters) {
+    const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (t >= n) return;
+    const int was = rows[t].n, len = was < 0 ? ~was : was;
+    const int now = counters[kUnsound + (inst ? inst[rows[t].k] : 0)] ? ~len : len;
+    if (now != was) rows[t].n = now;
+}
+
 __global__ void fill_team_units(const Unit* __restrict__ units, int64_t n, const int64_t* __restrict__ colptr,
                                 const int64_t* __restrict__ rowptr, const int64_t* __restrict__ rowend,
                                 kc::TeamUnit* __restrict__ out) {
@@ -1757,6 +1769,14 @@ kc_status launch_theta(const kc_factor* f, int tn, double ell, const double* ell
     return KC_OK;
 }
 
+// What every factorization ends with: its notes in the sweep's rows, where some level has summed columns.
+kc_status launch_end(const kc_factor* f, hipStream_t s) {
+    if (f->nmarked <= 0) return KC_OK;
+    mark_rows<<<grid_for(f->nmarked, kBlock), kBlock, 0, s>>>(f->bwd_desc, f->nmarked, f->inst, f->counters);
+    KC_LAUNCH_CHECK();
+    return KC_OK;
+}
+
 // What every factorization starts with: counters cleared, the points in maximin
 // order, Theta on S in Lcsc.
 kc_status launch_start(const kc_factor* f, const double* x_dev, int tn, double ell, const double* ells,
@@ -1934,6 +1954,8 @@ template <typename VT>
 kc_status factorize_solve_typed(kc_factor* f, int pol, double tau, const double* b, double* x, int nrhs, double* y,
                                 double* partial, hipStream_t s) {
     auto backward = [&]() {
+        const kc_status ended = launch_end(f, s);
+        if (ended != KC_OK) return ended;
         return for_passes(nrhs, [&](auto w, int r0) {
             constexpr int NR = decltype(w)::value;
             return bwd_levels<VT, NR>(f, x, nrhs, r0, y, partial, s);
@@ -2300,6 +2322,8 @@ kc_status kc_factor_create(const kc_plan* plan, kc_prec prec, void* ws_dev, size
     f->team_units = reinterpret_cast<kc::TeamUnit*>(base + o.team);
     f->inst = p.ninst > 1 ? reinterpret_cast<int32_t*>(base + o.inst) : nullptr;
     f->ninst = p.ninst;
+    for (size_t v = 0; v < bs.short_sum.size(); ++v)
+        if (bs.short_sum[v] > bs.short_off[v]) f->nmarked = int64_t(bs.shortc.size());
     try {
         f->level_last = last_columns(p);
         f->team_off = team_offsets(p, f->level_last, vt);
@@ -2434,6 +2458,7 @@ static kc_status factorize_impl(kc_factor* f, const double* x_dev, double nu, do
     st = groups_on(f, cnt)      ? launch_groups(f, tn, ell, int(pivot), tau, s)
          : f->prec == KC_FP64 ? launch_levels<double>(f, cnt, int(pivot), tau, s)
                               : launch_levels<float>(f, cnt, int(pivot), tau, s);
+    if (st == KC_OK) st = launch_end(f, s);
     if (st != KC_OK) return st;
     f->factorized = true;
     f->counted = cnt;
@@ -2621,6 +2646,7 @@ kc_status kc_factorize_solve(kc_factor* f, const double* x_dev, kc_kernel kernel
     if (st != KC_OK) return st;
     if (groups_on(f, false)) {  // the group DAG has its own levels: factor, then both sweeps
         st = launch_groups(f, tn, kernel.lengthscale, int(pivot), tau, s);
+        if (st == KC_OK) st = launch_end(f, s);
         if (st == KC_OK) st = solve_typed<float>(f, b_dev, x_out, nrhs, y, partial, s);
     } else {
         st = f->prec == KC_FP64

@@ -22,7 +22,7 @@ constexpr int kRowAlign = 64;
 // the row's pointers).  Filled on the device when a factor is created.
 struct alignas(16) SweepRow {
     uint32_t p0;    // first entry: of the row without its diagonal (forward), of the column below it (backward)
-    int32_t n;      // entries
+    int32_t n;      // entries; ~entries where the instance is unsound (bwd_desc only, see mark_rows)
     int32_t k;      // position
     int32_t perm;   // original index
 };

@@ -30,9 +30,11 @@ constexpr int kThreads = 256;
 template <typename VT, int NR, bool FWD>
 __global__ __launch_bounds__(kThreads) void sweep_narrow(SweepArgs<VT> a, int64_t beg, int nsum) {
     __shared__ __align__(16) double lds[sweep_lds(NR, kThreads)];
-    const kc::SweepRow row = a.rows[beg + int64_t(blockIdx.x)];
+    kc::SweepRow row = a.rows[beg + int64_t(blockIdx.x)];
     if constexpr (!FWD) {
-        if (int(blockIdx.x) < nsum && a.unsound[a.inst ? a.inst[row.k] : 0] == 0) {
+        const bool unsound = row.n < 0;
+        row.n = max(row.n, ~row.n);
+        if (int(blockIdx.x) < nsum && !unsound) {
             sum_column<VT, NR>(a, row, lds);
             return;
         }
@@ -86,8 +88,7 @@ hipError_t launch_fwd(const kc_factor* f, const double* b, int ld, int r0, int n
 template <typename VT>
 hipError_t launch_bwd_narrow(const kc_factor* f, double* x, int ld, int r0, int nr, double* y, int64_t cb, int64_t ce,
                              int64_t cm, hipStream_t s) {
-    const SweepArgs<VT> a{f->bwd_desc, f->rowidx, static_cast<const VT*>(f->Lcsc), f->diag, nullptr, x, y, ld, r0,
-                          f->counters + counter::kUnsound, f->inst};
+    const SweepArgs<VT> a{f->bwd_desc, f->rowidx, static_cast<const VT*>(f->Lcsc), f->diag, nullptr, x, y, ld, r0};
     return launch<VT, false>(a, nr, cb, ce, cm, s);
 }
 

@@ -112,14 +112,11 @@ struct SweepArgs {
     double* x;        // backward: solution, original order
     double* y;
     int ld, r0;
-    // backward: per instance, not 0 where every column keeps the sequential order
-    const unsigned long long* unsound;
-    const int32_t* inst;  // null: a single instance
 };
 
 template <typename VT>
 SweepArgs<VT> fwd_args(const kc_factor* f, const double* b, int ld, int r0, double* y) {
-    return {f->fwd_desc, f->colidx, static_cast<const VT*>(f->L), f->diag, b, nullptr, y, ld, r0, nullptr, nullptr};
+    return {f->fwd_desc, f->colidx, static_cast<const VT*>(f->L), f->diag, b, nullptr, y, ld, r0};
 }
 
 // One row of a wide forward level by a wavefront.
