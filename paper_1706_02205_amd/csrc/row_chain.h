@@ -8,7 +8,7 @@
 // use it) and 9.3 for the fma alone.  All 64 lanes must be active.  The leading s_nop keeps the two wait states
 // that a broadcast needs after its source was written by a vector instruction.  The
 // steps are aligned to their 8 bytes: where a change elsewhere in the kernel left
-// them across 8-byte boundaries, a solve of 48 problems took 1.574 ms, not 1.520.
+// them across 8-byte boundaries, a solve of 48 problems took 1.574 ms, not 1.530.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -19,8 +19,8 @@ namespace kcdev {
 
 constexpr int kRowLanes = 16;
 
-// Steps 0 .. 7.
-__device__ __forceinline__ void row_chain_low(double& acc, double a, double b) {
+// The 16 steps in one block, so that nothing writes a source between the wait and a broadcast.
+__device__ __forceinline__ void row_chain_steps(double& acc, double a, double b) {
     double t;
     asm volatile(
         "s_nop 1\n\t"
@@ -41,15 +41,6 @@ __device__ __forceinline__ void row_chain_low(double& acc, double a, double b) {
         "v_fmac_f64_dpp %0, %3, %1 row_newbcast:6 row_mask:0xf bank_mask:0xf\n\t"
         "v_mov_b64_dpp %1, %2 row_newbcast:7 row_mask:0xf bank_mask:0xf\n\t"
         "v_fmac_f64_dpp %0, %3, %1 row_newbcast:7 row_mask:0xf bank_mask:0xf\n\t"
-        : "+v"(acc), "=&v"(t)
-        : "v"(a), "v"(b));
-}
-// Steps 8 .. 15.
-__device__ __forceinline__ void row_chain_high(double& acc, double a, double b) {
-    double t;
-    asm volatile(
-        "s_nop 1\n\t"
-        ".p2align 3\n\t"
         "v_mov_b64_dpp %1, %2 row_newbcast:8 row_mask:0xf bank_mask:0xf\n\t"
         "v_fmac_f64_dpp %0, %3, %1 row_newbcast:8 row_mask:0xf bank_mask:0xf\n\t"
         "v_mov_b64_dpp %1, %2 row_newbcast:9 row_mask:0xf bank_mask:0xf\n\t"
@@ -79,8 +70,7 @@ __device__ __forceinline__ double row_chain(const double* __restrict__ a, const 
         const int next = (t + kRowLanes < m ? t + kRowLanes : 0) + s;
         const double an = a[next], bn = b[next];
         keep_loads_above();
-        row_chain_low(acc, av, bv);
-        row_chain_high(acc, av, bv);
+        row_chain_steps(acc, av, bv);
         av = an;
         bv = bn;
     }
